@@ -10,22 +10,20 @@
 //                                equispaced nodes (spacing h / p) per axis;
 //                                FFT size F = smallest power of two >= 2 N.
 //   count / scan / scatter       the points sorted by box (counting sort).
-//   accum_kernel                 one thread per box sums its points' charges
+//   accum_kernel                 16 lanes per box sum its points' charges
 //                                1, z_x, z_y (z = y - centre) times the
 //                                tensor Lagrange weights into the box's
 //                                p x p nodes, in 64-bit fixed point (exact,
 //                                so independent of the order the scatter
 //                                leaves: deterministic), and writes them;
 //                                every node belongs to exactly one box.
-//   load_kernel                  three complex F x F grids, zero-padded /
-//                                wrapped (circular convolution = linear for
-//                                F >= 2N): W0, W1 + i W2, and K1 + i K2 with
-//                                K1 = 1 / (1 + r^2), K2 = K1^2 at the node
-//                                offsets.
-//   2-D FFT (FP64)               row FFTs in LDS, an in-place transpose, row
-//                                FFTs again.  The kernels are even, so their
-//                                spectra are real: FFT(W0) (K1^ + i K2^)
-//                                transforms back to phi1 + i phi2 and
+//   rows_fwd / cols / rows_inv   the 2-D circular convolution by FP64 FFTs
+//                                (equal to the linear one for F >= 2N) of
+//                                three complex grids: W0, W1 + i W2, and
+//                                K1 + i K2 with K1 = 1 / (1 + r^2), K2 = K1^2
+//                                at the node offsets.  The kernels are even,
+//                                so their spectra are real: FFT(W0) (K1^ + i
+//                                K2^) transforms back to phi1 + i phi2 and
 //                                (W1^ + i W2^) K2^ to phi3x + i phi3y -- three
 //                                forward and two inverse transforms.
 //   gather_kernel                each point interpolates the four node
@@ -35,6 +33,8 @@
 // Every size is read from the parameters on the device; the launches and
 // the workspace are sized for the largest FFT the caller allows.
 #include <math.h>
+
+#include <type_traits>
 
 #include "common.hpp"
 #include "klgrad.hpp"
@@ -46,7 +46,6 @@ constexpr int FI_GRID = 512;    // blocks of the point passes (and Z partials)
 constexpr int FI_MAX_P = 5;     // interpolation nodes per box and axis
 constexpr int FI_MIN_FFT = 64;  // FFT sizes: powers of two in [64, 4096]
 constexpr int FI_MAX_FFT = 4096;
-constexpr int FI_TILE = 32;     // transpose tile
 
 struct FiParams {
   double lo, h, c, scale;  // domain origin, box side, centre, fixed-point scale
@@ -77,11 +76,14 @@ __global__ __launch_bounds__(256) void fi_bbox_kernel(const float2* __restrict__
   }
 }
 
-// One block: reduce the bounding box and fix the grid.  min and max are
-// exact in any order; range and h are FP64 operations on those floats.
+// One block: reduce the bounding box, fix the grid and fill the FFTs' twiddle
+// table.  min and max are exact in any order; range and h are FP64
+// operations on those floats.
 __global__ __launch_bounds__(256) void fi_params_kernel(const float* __restrict__ part, int nb, int64_t n, int p,
                                                         int min_boxes, float max_box_width, int max_fft,
-                                                        FiParams* __restrict__ out) {
+                                                        FiParams* __restrict__ out, double2* __restrict__ tw,
+                                                        int* __restrict__ nheavy) {
+  __shared__ int size;
   float mn = INFINITY, mx = -INFINITY;
   for (int b = threadIdx.x; b < nb; b += 256) {
     mn = fminf(mn, part[2 * b]);
@@ -95,43 +97,65 @@ __global__ __launch_bounds__(256) void fi_params_kernel(const float* __restrict_
     smx[threadIdx.x >> 6] = mx;
   }
   __syncthreads();
-  if (threadIdx.x != 0) return;
-  double lo = double(fminf(fminf(smn[0], smn[1]), fminf(smn[2], smn[3])));
-  const double hi = double(fmaxf(fmaxf(smx[0], smx[1]), fmaxf(smx[2], smx[3])));
-  double rng = hi - lo;
-  if (!isfinite(lo) || !isfinite(rng)) {  // non-finite input: any valid grid (results are not finite)
-    lo = 0.0;
-    rng = 1e-3;
+  if (threadIdx.x == 0) {
+    double lo = double(fminf(fminf(smn[0], smn[1]), fminf(smn[2], smn[3])));
+    const double hi = double(fmaxf(fmaxf(smx[0], smx[1]), fmaxf(smx[2], smx[3])));
+    double rng = hi - lo;
+    if (!isfinite(lo) || !isfinite(rng)) {  // non-finite input: any valid grid (results are not finite)
+      lo = 0.0;
+      rng = 1e-3;
+    }
+    if (!(rng > 0.0)) rng = 1e-3;
+    double Bd = ceil(rng / double(max_box_width));
+    Bd = fmax(Bd, double(min_boxes));
+    Bd = fmin(Bd, double(max_fft / (2 * p)));
+    const int B = int(Bd);
+    const int N = p * B;
+    int F = FI_MIN_FFT, logF = 6;
+    while (F < 2 * N) {
+      F <<= 1;
+      ++logF;
+    }
+    FiParams P;
+    P.lo = lo;
+    P.h = rng / double(B);
+    P.c = lo + 0.5 * rng;
+    // fixed point: every node sum is at most n (|z| + 1) times the square of
+    // the largest Lagrange weight on [0, 1] (1.5, 1.88, 2.19, 3.28 for
+    // p = 2 .. 5: squared < 16); keep it below 2^62
+    const double bound = double(n) * (0.5 * rng + 1.0) * 16.0;
+    P.scale = exp2(floor(log2(4.611686018427388e18 / bound)));
+    P.B = B;
+    P.N = N;
+    P.F = F;
+    P.logF = logF;
+    *out = P;
+    *nheavy = 0;
+    size = F;
   }
-  if (!(rng > 0.0)) rng = 1e-3;
-  double Bd = ceil(rng / double(max_box_width));
-  Bd = fmax(Bd, double(min_boxes));
-  Bd = fmin(Bd, double(max_fft / (2 * p)));
-  const int B = int(Bd);
-  const int N = p * B;
-  int F = FI_MIN_FFT, logF = 6;
-  while (F < 2 * N) {
-    F <<= 1;
-    ++logF;
+  __syncthreads();
+  // the FFTs' twiddles exp(-2 pi i k / F)
+  for (int k = threadIdx.x; k < size; k += 256) {
+    double sn, cs;
+    sincospi(-2.0 * double(k) / double(size), &sn, &cs);
+    tw[k] = make_double2(cs, sn);
   }
-  FiParams P;
-  P.lo = lo;
-  P.h = rng / double(B);
-  P.c = lo + 0.5 * rng;
-  // fixed point: every node sum is at most n (|z| + 1) times the square of
-  // the largest Lagrange weight on [0, 1] (1.5, 1.88, 2.19, 3.28 for
-  // p = 2 .. 5: squared < 16); keep it below 2^62
-  const double bound = double(n) * (0.5 * rng + 1.0) * 16.0;
-  P.scale = exp2(floor(log2(4.611686018427388e18 / bound)));
-  P.B = B;
-  P.N = N;
-  P.F = F;
-  P.logF = logF;
-  *out = P;
 }
 
-// Box index and Lagrange weights of one coordinate (the same FP64
-// operations as the definition: t = (y - lo) / h, b = floor(t) clamped).
+// 1 / prod_{m != k} (t_k - t_m) of the nodes t_k = (k + 1/2) / P: the
+// Lagrange weights as products without divisions.
+template <int P>
+__device__ __forceinline__ constexpr double fi_denom(int k) {
+  double d = 1.0;
+  for (int m = 0; m < P; ++m)
+    if (m != k) d *= double(k - m);
+  double pw = 1.0;
+  for (int m = 1; m < P; ++m) pw *= double(P);
+  return pw / d;
+}
+
+// Box index and Lagrange weights of one coordinate (t = (y - lo) / h, b =
+// floor(t) clamped, as in the definition).
 template <int P>
 __device__ __forceinline__ int fi_weights(float y, const FiParams& g, double (&L)[P]) {
   const double t = (double(y) - g.lo) / g.h;
@@ -139,14 +163,10 @@ __device__ __forceinline__ int fi_weights(float y, const FiParams& g, double (&L
   const double u = t - bd;
 #pragma unroll
   for (int k = 0; k < P; ++k) {
-    double v = 1.0;
-    const double tk = (double(k) + 0.5) / double(P);
+    double v = fi_denom<P>(k);
 #pragma unroll
-    for (int m = 0; m < P; ++m) {
-      if (m == k) continue;
-      const double tm = (double(m) + 0.5) / double(P);
-      v *= (u - tm) / (tk - tm);
-    }
+    for (int m = 0; m < P; ++m)
+      if (m != k) v *= u - (double(m) + 0.5) / double(P);
     L[k] = v;
   }
   return int(bd);
@@ -238,16 +258,19 @@ __global__ __launch_bounds__(256) void fi_scatter_kernel(const float2* __restric
   }
 }
 
-// Points per thread of the node sums.  A box holding more (a compact or
-// clustered embedding can put most points in a few boxes) is split into
-// chunks of this many points, one thread each, so no thread walks a long
-// box alone.
-constexpr int FI_HEAVY = 64;
+// Node sums.  16 lanes (a DPP row) share a box: each adds its points'
+// charges 1, z_x, z_y times the tensor Lagrange weights in registers, 64-bit
+// fixed point, then the 16 sums are added by row rotations (integers: exact
+// in any order).  A box of more than FI_HEAVY points (a compact or clustered
+// embedding can put most points in a few boxes) is cut into chunks of
+// FI_HEAVY points, listed by the pass over the boxes and added by a second
+// kernel.  One thread per box (64-point chunks) took 183 + 97 us at 10^6
+// points in 13,000 boxes and 78 us at 70,000: a thread walked its 8 to 64
+// points one dependent gather after another, on a third of the chip's
+// wavefronts; 16 lanes take 32 + 19 us and 9 us.
+constexpr int FI_HEAVY = 256;
+constexpr int FI_BATCH = 4;  // points of a lane in flight
 
-// Adds the charges 1, z_x, z_y of the sorted points [e0, e1) (one box)
-// times the tensor Lagrange weights to acc, in fixed point.  The point
-// indices and positions are loaded eight at a time, so the loads of a batch
-// are in flight together (the sums keep their order).
 template <int P>
 __device__ __forceinline__ void fi_accum_point(float2 y, const FiParams& g, long long (&acc)[3][P][P]) {
   double Lx[P], Ly[P];
@@ -266,249 +289,449 @@ __device__ __forceinline__ void fi_accum_point(float2 y, const FiParams& g, long
   }
 }
 
+// Sums over the sorted points [e0, e1) of one box by the 16 lanes of a row;
+// every lane ends with the total.
 template <int P>
 __device__ __forceinline__ void fi_accum_range(const float2* __restrict__ Y, const FiParams& g,
                                                const int32_t* __restrict__ order, int64_t e0, int64_t e1,
                                                long long (&acc)[3][P][P]) {
-  constexpr int BT = 8;
-  int64_t e = e0;
-  for (; e + BT <= e1; e += BT) {
-    int32_t ix[BT];
-    float2 yv[BT];
 #pragma unroll
-    for (int u = 0; u < BT; ++u) ix[u] = order[e + u];
+  for (int c = 0; c < 3; ++c)
 #pragma unroll
-    for (int u = 0; u < BT; ++u) yv[u] = Y[ix[u]];
+    for (int kx = 0; kx < P; ++kx)
 #pragma unroll
-    for (int u = 0; u < BT; ++u) fi_accum_point<P>(yv[u], g, acc);
+      for (int ky = 0; ky < P; ++ky) acc[c][kx][ky] = 0;
+  for (int64_t e = e0 + (lane_id() & 15); e < e1; e += 16 * FI_BATCH) {
+    int32_t ix[FI_BATCH];
+    float2 yv[FI_BATCH];
+#pragma unroll
+    for (int u = 0; u < FI_BATCH; ++u) ix[u] = order[e + 16 * u < e1 ? e + 16 * u : e];
+#pragma unroll
+    for (int u = 0; u < FI_BATCH; ++u) yv[u] = Y[ix[u]];
+#pragma unroll
+    for (int u = 0; u < FI_BATCH; ++u)
+      if (e + 16 * u < e1) fi_accum_point<P>(yv[u], g, acc);
   }
-  for (; e < e1; ++e) fi_accum_point<P>(Y[order[e]], g, acc);
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+#pragma unroll
+    for (int kx = 0; kx < P; ++kx)
+#pragma unroll
+      for (int ky = 0; ky < P; ++ky) {
+        uint64_t v = uint64_t(acc[c][kx][ky]);
+        auto rot = [&](auto ctrl) {
+          constexpr int C = decltype(ctrl)::value;
+          v += (uint64_t(uint32_t(dpp_i<C>(int(uint32_t(v >> 32))))) << 32) | uint32_t(dpp_i<C>(int(uint32_t(v))));
+        };
+        rot(std::integral_constant<int, 0x128>{});
+        rot(std::integral_constant<int, 0x124>{});
+        rot(std::integral_constant<int, 0x122>{});
+        rot(std::integral_constant<int, 0x121>{});
+        acc[c][kx][ky] = (long long)v;
+      }
 }
 
-// Node sums of box b (thread b < B^2): channel c at G + c N^2, node
-// (gx, gy) at gx N + gy.  A box of more than FI_HEAVY points gets zeros
-// here; its chunks are added by fi_accum_heavy_kernel.
+// Node sums of every box: channel c at G + c N^2, node (gx, gy) at gx N +
+// gy.  A heavy box gets zeros here and its chunks in `heavy` (box and chunk
+// number; their order follows the counter's atomics and reaches no result).
 template <int P>
 __global__ __launch_bounds__(256) void fi_accum_kernel(const float2* __restrict__ Y,
                                                        const FiParams* __restrict__ gp,
                                                        const int64_t* __restrict__ off,
                                                        const int32_t* __restrict__ order,
-                                                       unsigned long long* __restrict__ G) {
+                                                       unsigned long long* __restrict__ G, int* __restrict__ nheavy,
+                                                       int2* __restrict__ heavy) {
   const FiParams g = *gp;
-  const int64_t nb = int64_t(g.B) * g.B;
+  const int nb = g.B * g.B;
   const int64_t NN = int64_t(g.N) * g.N;
-  for (int64_t b = gtid(); b < nb; b += int64_t(gridDim.x) * 256) {
+  const int sl = lane_id() & 15;
+  // whole rows of 16 lanes run or stop together
+  for (int b = int(gtid() >> 4); b < nb; b += int(gridDim.x) * 16) {
+    const int64_t e0 = off[b], e1 = off[b + 1];
+    const bool light = e1 - e0 <= FI_HEAVY;
+    if (!light && sl == 0) {
+      const int nc = int((e1 - e0 + FI_HEAVY - 1) / FI_HEAVY);
+      const int at = atomicAdd(nheavy, nc);
+      for (int c = 0; c < nc; ++c) heavy[at + c] = make_int2(b, c);
+    }
     long long acc[3][P][P];
+    fi_accum_range<P>(Y, g, order, e0, light ? e1 : e0, acc);
+    const int bx = b / g.B, by = b % g.B;
 #pragma unroll
     for (int c = 0; c < 3; ++c)
 #pragma unroll
       for (int kx = 0; kx < P; ++kx)
 #pragma unroll
-        for (int ky = 0; ky < P; ++ky) acc[c][kx][ky] = 0;
-    const int64_t e0 = off[b], e1 = off[b + 1];
-    if (e1 - e0 <= FI_HEAVY) fi_accum_range<P>(Y, g, order, e0, e1, acc);
-    const int bx = int(b / g.B), by = int(b % g.B);
-#pragma unroll
-    for (int kx = 0; kx < P; ++kx) {
-#pragma unroll
-      for (int ky = 0; ky < P; ++ky) {
-        const int64_t node = int64_t(P * bx + kx) * g.N + (P * by + ky);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) G[c * NN + node] = (unsigned long long)acc[c][kx][ky];
-      }
-    }
+        for (int ky = 0; ky < P; ++ky)
+          if (sl == (c * P * P + kx * P + ky) % 16)
+            G[c * NN + int64_t(P * bx + kx) * g.N + (P * by + ky)] = (unsigned long long)acc[c][kx][ky];
   }
 }
 
-// nch[b] = FI_HEAVY-point chunks of box b when it holds more than FI_HEAVY
-// points, else 0 (b < nbox, the workspace's box count).
-__global__ __launch_bounds__(256) void fi_chunks_kernel(const FiParams* __restrict__ gp,
-                                                        const int* __restrict__ cnt, int64_t nbox,
-                                                        int* __restrict__ nch) {
-  const FiParams g = *gp;
-  const int64_t nb = int64_t(g.B) * g.B;
-  for (int64_t b = gtid(); b < nbox; b += int64_t(gridDim.x) * 256)
-    nch[b] = (b < nb && cnt[b] > FI_HEAVY) ? (cnt[b] + FI_HEAVY - 1) / FI_HEAVY : 0;
-}
-
-// The chunks of the heavy boxes, one thread each: chunk c belongs to the box
-// b with choff[b] <= c < choff[b + 1] (binary search) and covers its sorted
-// points off[b] + FI_HEAVY (c - choff[b]) onwards.  Chunks of one box are
-// consecutive, so a wave's chunks usually share a box: then its sums are
-// added across the wave (integer shuffles, exact) and one lane adds them
-// to the box's nodes; otherwise every lane adds its own.  The nodes were
-// zeroed by fi_accum_kernel; the integer sums are exact in any order.
+// The listed chunks, 16 lanes each, added to the nodes their box zeroed.
+// The four rows of a wave add their sums first when they share the box.
 template <int P>
 __global__ __launch_bounds__(256) void fi_accum_heavy_kernel(const float2* __restrict__ Y,
                                                              const FiParams* __restrict__ gp,
                                                              const int64_t* __restrict__ off,
                                                              const int32_t* __restrict__ order,
-                                                             const int64_t* __restrict__ choff, int64_t nbox,
+                                                             const int* __restrict__ nheavy,
+                                                             const int2* __restrict__ heavy,
                                                              unsigned long long* __restrict__ G) {
   const FiParams g = *gp;
-  const int64_t H = choff[nbox];
+  const int H = *nheavy;
   const int64_t NN = int64_t(g.N) * g.N;
-  for (int64_t base = int64_t(blockIdx.x) * 256; base < H; base += int64_t(gridDim.x) * 256) {
-    const int64_t c = base + threadIdx.x;
+  const int lane = lane_id(), sl = lane & 15;
+  for (int c0 = int(gtid() >> 6) * 4; c0 < H; c0 += int(gridDim.x) * 16) {  // whole waves
+    const int c = c0 + (lane >> 4);
     const bool act = c < H;
-    int64_t b = -1;
+    const int2 hb = heavy[act ? c : c0];
+    const int64_t e0 = off[hb.x] + int64_t(FI_HEAVY) * hb.y;
+    const int64_t e1 = e0 + FI_HEAVY < off[hb.x + 1] ? e0 + FI_HEAVY : off[hb.x + 1];
     long long acc[3][P][P];
+    fi_accum_range<P>(Y, g, order, e0, act ? e1 : e0, acc);
+    const bool one = __ballot(hb.x == __builtin_amdgcn_readfirstlane(hb.x)) == ~uint64_t(0);
+    const int bx = hb.x / g.B, by = hb.x % g.B;
 #pragma unroll
     for (int q = 0; q < 3; ++q)
 #pragma unroll
       for (int kx = 0; kx < P; ++kx)
 #pragma unroll
-        for (int ky = 0; ky < P; ++ky) acc[q][kx][ky] = 0;
-    if (act) {
-      int64_t lo = 0, hi = nbox;  // last b with choff[b] <= c
-      while (hi - lo > 1) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (choff[mid] <= c) lo = mid;
-        else hi = mid;
-      }
-      b = lo;
-      const int64_t e0 = off[b] + FI_HEAVY * (c - choff[b]);
-      const int64_t e1 = e0 + FI_HEAVY < off[b + 1] ? e0 + FI_HEAVY : off[b + 1];
-      fi_accum_range<P>(Y, g, order, e0, e1, acc);
-    }
-    // one box across the wave's active lanes?
-    int64_t bmin = act ? b : INT64_MAX, bmax = act ? b : -1;
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-      const int64_t o1 = int64_t(shfl_xor_u64(uint64_t(bmin), m)), o2 = int64_t(shfl_xor_u64(uint64_t(bmax), m));
-      bmin = o1 < bmin ? o1 : bmin;
-      bmax = o2 > bmax ? o2 : bmax;
-    }
-    const bool one = bmin == bmax;
-    const int64_t bb = one ? bmin : b;
-    const int bx = int(bb / g.B), by = int(bb % g.B);
-#pragma unroll
-    for (int kx = 0; kx < P; ++kx) {
-#pragma unroll
-      for (int ky = 0; ky < P; ++ky) {
-        const int64_t node = int64_t(P * bx + kx) * g.N + (P * by + ky);
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
+        for (int ky = 0; ky < P; ++ky) {
           uint64_t v = uint64_t(acc[q][kx][ky]);
-          if (one) {
-#pragma unroll
-            for (int m = 1; m < 64; m <<= 1) v += shfl_xor_u64(v, m);
-            if (lane_id() == 0) atomicAdd(&G[q * NN + node], (unsigned long long)v);
-          } else if (act) {
-            atomicAdd(&G[q * NN + node], (unsigned long long)v);
+          if (one) {  // wave-uniform
+            v += shfl_xor_u64(v, 16);
+            v += shfl_xor_u64(v, 32);
           }
+          if ((one ? lane : sl) == (q * P * P + kx * P + ky) % 16 && act)
+            atomicAdd(&G[q * NN + int64_t(P * bx + kx) * g.N + (P * by + ky)], (unsigned long long)v);
         }
-      }
-    }
-  }
-}
-
-// The three F x F complex grids: W0, W1 + i W2 (zero-padded) and K1 + i K2
-// at the wrapped node offsets.  Plane ch at Cg + ch * plane, row-major with
-// row stride F.
-__global__ __launch_bounds__(256) void fi_load_kernel(const unsigned long long* __restrict__ G,
-                                                      const FiParams* __restrict__ gp, int p,
-                                                      double2* __restrict__ Cg, int64_t plane) {
-  const FiParams g = *gp;
-  const int F = g.F, N = g.N;
-  const int64_t NN = int64_t(N) * N;
-  const double inv = 1.0 / g.scale;
-  const double delta = g.h / double(p);
-  for (int64_t t = gtid(); t < int64_t(F) * F; t += int64_t(gridDim.x) * 256) {
-    const int ix = int(t / F), iy = int(t % F);
-    double w0 = 0.0, w1 = 0.0, w2 = 0.0;
-    if (ix < N && iy < N) {
-      const int64_t node = int64_t(ix) * N + iy;
-      w0 = double((long long)G[node]) * inv;
-      w1 = double((long long)G[NN + node]) * inv;
-      w2 = double((long long)G[2 * NN + node]) * inv;
-    }
-    const bool vx = ix < N || ix > F - N, vy = iy < N || iy > F - N;
-    double k1 = 0.0;
-    if (vx && vy) {
-      const double dx = delta * double(ix < N ? ix : ix - F), dy = delta * double(iy < N ? iy : iy - F);
-      k1 = 1.0 / (1.0 + dx * dx + dy * dy);
-    }
-    Cg[t] = make_double2(w0, 0.0);
-    Cg[plane + t] = make_double2(w1, w2);
-    Cg[2 * plane + t] = make_double2(k1, k1 * k1);
   }
 }
 
 // --- FFT ---------------------------------------------------------------
 
-// Length-F complex DFT of every row of nch planes (sign -1 forward, +1
-// inverse, unnormalised): radix-2 decimation in time in LDS, the input
-// loaded in bit-reversed order; twiddles exp(sign 2 pi i k / len) from
-// sincospi.  Rows are dealt to the blocks round robin.
-__global__ __launch_bounds__(256) void fi_fft_rows_kernel(double2* __restrict__ Cg, int64_t plane, int nch,
-                                                          const FiParams* __restrict__ gp, double sign) {
-  extern __shared__ double2 sbuf[];
-  const int F = gp->F, logF = gp->logF;
-  const int64_t rows = int64_t(nch) * F;
-  for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
-    double2* row = Cg + (r / F) * plane + (r % F) * int64_t(F);
-    for (int i = threadIdx.x; i < F; i += 256) sbuf[__brev(unsigned(i)) >> (32 - logF)] = row[i];
-    __syncthreads();
-    for (int half = 1; half < F; half <<= 1) {
-      for (int j = threadIdx.x; j < F / 2; j += 256) {
-        const int k = j & (half - 1);
-        const int i0 = ((j - k) << 1) + k, i1 = i0 + half;
-        double sn, cs;
-        sincospi(sign * double(k) / double(half), &sn, &cs);
-        const double2 a = sbuf[i0], b = sbuf[i1];
-        const double2 bw = make_double2(b.x * cs - b.y * sn, b.x * sn + b.y * cs);
-        sbuf[i0] = make_double2(a.x + bw.x, a.y + bw.y);
-        sbuf[i1] = make_double2(a.x - bw.x, a.y - bw.y);
+// 2-D circular convolution on the F x F grid in three passes, with no
+// transposes and no work on the zero padding (N <= F / 2 of F rows and
+// columns hold data):
+//   fi_rows_fwd_kernel  length-F FFTs of the N nonzero rows of W0, W1 + i W2
+//                       and K1 + i K2, their elements taken from the node
+//                       sums and the kernel's definition on the way in;
+//   fi_cols_kernel      per column: the three column FFTs (K's rows mirrored:
+//                       it is even), the products W0^ (K1^ + i K2^) and
+//                       (W1^ + i W2^) K2^ (K1^, K2^ are real), and the two
+//                       inverse column FFTs, of which N rows are kept;
+//   fi_rows_inv_kernel  the inverse row FFTs of those N rows, of which N
+//                       columns are kept (the only ones the gather reads).
+// What bounds it: latency and LDS round trips, the data (3 N F complex
+// numbers, 17 MB at F = 1024) staying in L2 / MALL.  A block works on 4096
+// complex numbers in 64 KB of LDS, L = 4096 / F lines together, so two
+// blocks share a CU and a wave's accesses of a column pass cover L adjacent
+// columns; a thread holds 16 elements in registers (radix 8, the factor 2 or
+// 4 that is left over first in the forward and last in the inverse
+// direction, so that a column's spectrum goes from the forward FFT's last
+// pass to the inverse's first in registers).  Twiddles: one table of exp(-2 pi i k /
+// F) per call, the powers 2 .. 7 by multiplication.
+// Measured at F = 1024 (70,001 and 10^6 points): 17 + 46 + 12 us for the
+// three passes, against 250 us for radix-2 row passes with a sincospi per
+// butterfly over all F rows, transposes, a load and a product pass (eight
+// launches); a call at 70,001 points 0.43 -> 0.20 ms with the new node sums.
+constexpr int FI_PTS = 4096;  // complex numbers per block
+
+__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
+  return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+}
+__device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
+__device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
+__device__ __forceinline__ double2 cmuli(double2 a) { return make_double2(a.y, -a.x); }  // -i a
+
+// Forward DFTs of length 2, 4 and 8 in natural order.
+__device__ __forceinline__ void dft2(double2& a, double2& b) {
+  const double2 t = b;
+  b = csub(a, t);
+  a = cadd(a, t);
+}
+__device__ __forceinline__ void dft4(double2& a, double2& b, double2& c, double2& d) {
+  dft2(a, c);
+  dft2(b, d);
+  d = cmuli(d);
+  dft2(a, b);
+  dft2(c, d);
+  const double2 t = b;
+  b = c;
+  c = t;
+}
+__device__ __forceinline__ void dft8(double2* v) {
+  constexpr double H = 0.70710678118654752440;
+  dft4(v[0], v[2], v[4], v[6]);
+  dft4(v[1], v[3], v[5], v[7]);
+  // v[0 2 4 6] = even bins 0..3, v[1 3 5 7] = odd bins 0..3
+  v[3] = make_double2(H * (v[3].x + v[3].y), H * (v[3].y - v[3].x));
+  v[5] = cmuli(v[5]);
+  v[7] = make_double2(H * (v[7].y - v[7].x), -H * (v[7].x + v[7].y));
+  double2 o[8];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    o[k] = cadd(v[2 * k], v[2 * k + 1]);
+    o[k + 4] = csub(v[2 * k], v[2 * k + 1]);
+  }
+#pragma unroll
+  for (int k = 0; k < 8; ++k) v[k] = o[k];
+}
+
+// A block's lines of F complex numbers.  Butterfly q of a radix-R pass is
+// number q / L of line q % L (neighbouring lanes take neighbouring lines,
+// then neighbouring elements).  In LDS element i of a line sits at i with its
+// low three bits changed by the next three and by the line, so that 8
+// lanes (16 bytes each, one LDS cycle) never share a bank.
+struct FiLines {
+  int logF, logL, lsh;
+  double2* s;
+  const double2* tw;
+  __device__ __forceinline__ int at(int line, int i) const {
+    return (line << logF) + (i ^ ((i >> 3) & 7) ^ ((line << lsh) & 7));
+  }
+  __device__ __forceinline__ int line(int q) const { return q & ((1 << logL) - 1); }
+  __device__ __forceinline__ int num(int q) const { return q >> logL; }
+};
+__device__ __forceinline__ FiLines fi_lines(int logF, double2* s, const double2* tw) {
+  return FiLines{logF, 12 - logF, logF > 9 ? logF - 9 : 0, s, tw};
+}
+
+// threadIdx.x, opaque at every use: the LDS addresses of a pass are then
+// formed where they are used (kept across the passes, the dozens of them
+// spilled).
+__device__ __forceinline__ int fi_tid() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
+// Pass of radix R over the 16 elements a thread holds, v[u R + r] = element
+// num + r F / R of butterfly u (q = tid + 256 u): twiddles for sub-transforms
+// of length Ns = 2^logNs, then the length-R DFTs.
+template <int R>
+__device__ __forceinline__ void fi_pass(const FiLines& f, double2 (&v)[16], int logNs) {
+  constexpr int logR = R == 8 ? 3 : (R == 4 ? 2 : 1);
+  const int t = fi_tid();
+#pragma unroll
+  for (int u = 0; u < 16 / R; ++u) {
+    double2* w = v + u * R;
+    if (logNs > 0) {
+      const int k = f.num(t + 256 * u) & ((1 << logNs) - 1);
+      const double2 w1 = f.tw[k << (f.logF - logR - logNs)];
+      double2 p = w1;
+#pragma unroll
+      for (int r = 1; r < R; ++r) {
+        w[r] = cmul(w[r], p);
+        if (r + 1 < R) p = cmul(p, w1);
       }
-      __syncthreads();
     }
-    for (int i = threadIdx.x; i < F; i += 256) row[i] = sbuf[i];
-    __syncthreads();
+    if constexpr (R == 8) dft8(w);
+    else if constexpr (R == 4) dft4(w[0], w[1], w[2], w[3]);
+    else dft2(w[0], w[1]);
+    if (R > 2) __builtin_amdgcn_sched_barrier(0);  // one butterfly's temporaries at a time
+  }
+}
+// The pass's outputs to LDS (Stockham order), and the next pass's inputs.
+template <int R>
+__device__ __forceinline__ void fi_store(const FiLines& f, const double2 (&v)[16], int logNs) {
+  const int t = fi_tid();
+#pragma unroll
+  for (int u = 0; u < 16 / R; ++u) {
+    const int q = t + 256 * u, ln = f.line(q), j = f.num(q);
+    const int k = j & ((1 << logNs) - 1);
+#pragma unroll
+    for (int r = 0; r < R; ++r) f.s[f.at(ln, (j - k) * R + k + (r << logNs))] = v[u * R + r];
+  }
+}
+template <int R>
+__device__ __forceinline__ void fi_fetch(const FiLines& f, double2 (&v)[16]) {
+  constexpr int logR = R == 8 ? 3 : (R == 4 ? 2 : 1);
+  const int t = fi_tid();
+#pragma unroll
+  for (int u = 0; u < 16 / R; ++u) {
+    const int q = t + 256 * u, ln = f.line(q), j = f.num(q);
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[u * R + r] = f.s[f.at(ln, j + (r << (f.logF - logR)))];
   }
 }
 
-// In-place transpose of nch F x F planes: a block swaps tile (a, b) with
-// tile (b, a), a <= b, through LDS.
-__global__ __launch_bounds__(256) void fi_transpose_kernel(double2* __restrict__ Cg, int64_t plane, int nch,
-                                                           const FiParams* __restrict__ gp) {
-  __shared__ double2 ta[FI_TILE][FI_TILE + 1], tb[FI_TILE][FI_TILE + 1];
-  const int F = gp->F;
-  const int T = F / FI_TILE;
-  const int64_t pairs = int64_t(T) * (T + 1) / 2;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-  for (int64_t w = blockIdx.x; w < pairs * nch; w += gridDim.x) {
-    const int ch = int(w / pairs);
-    int64_t q = w % pairs;
-    int a = 0;  // q -> (a, b), a <= b, row-major over a
-    while (q >= T - a) {
-      q -= T - a;
-      ++a;
-    }
-    const int b = a + int(q);
-    double2* base = Cg + ch * plane;
-    for (int y = ty; y < FI_TILE; y += 8) {
-      ta[y][tx] = base[int64_t(a * FI_TILE + y) * F + b * FI_TILE + tx];
-      tb[y][tx] = base[int64_t(b * FI_TILE + y) * F + a * FI_TILE + tx];
-    }
+// Forward FFT of the elements get(line, i), which go through LDS first (in
+// registers from the start, their addresses made the kernels spill); the
+// result is left in registers: v[8 u + r] = bin num + r F / 8 of butterfly u.
+template <typename Get>
+__device__ __forceinline__ void fi_forward(const FiLines& f, double2 (&v)[16], Get get) {
+#pragma unroll 4
+  for (int e = threadIdx.x; e < FI_PTS; e += 256) f.s[f.at(f.line(e), f.num(e))] = get(f.line(e), f.num(e));
+  __syncthreads();
+  const int rem = f.logF % 3;
+  int logNs = 0;
+  if (rem == 1) {
+    fi_fetch<2>(f, v);
+    fi_pass<2>(f, v, 0);
     __syncthreads();
-    for (int y = ty; y < FI_TILE; y += 8) {
-      base[int64_t(b * FI_TILE + y) * F + a * FI_TILE + tx] = ta[tx][y];
-      base[int64_t(a * FI_TILE + y) * F + b * FI_TILE + tx] = tb[tx][y];
-    }
+    fi_store<2>(f, v, 0);
     __syncthreads();
+    logNs = 1;
+  } else if (rem == 2) {
+    fi_fetch<4>(f, v);
+    fi_pass<4>(f, v, 0);
+    __syncthreads();
+    fi_store<4>(f, v, 0);
+    __syncthreads();
+    logNs = 2;
+  }
+#pragma unroll 1
+  for (;;) {
+    fi_fetch<8>(f, v);
+    __syncthreads();  // every element read
+    fi_pass<8>(f, v, logNs);
+    if (logNs + 3 >= f.logF) break;
+    fi_store<8>(f, v, logNs);
+    __syncthreads();
+    logNs += 3;
   }
 }
 
-// Spectra: plane 0 <- W0^ (K1^ + i K2^), plane 1 <- (W1^ + i W2^) K2^, with
-// K2^ = Im of plane 2 (K1^, K2^ real).
-__global__ __launch_bounds__(256) void fi_mult_kernel(double2* __restrict__ Cg, int64_t plane,
-                                                      const FiParams* __restrict__ gp) {
-  const int64_t FF = int64_t(gp->F) * gp->F;
-  for (int64_t t = gtid(); t < FF; t += int64_t(gridDim.x) * 256) {
-    const double2 w0 = Cg[t], w12 = Cg[plane + t], k = Cg[2 * plane + t];
-    Cg[t] = make_double2(w0.x * k.x - w0.y * k.y, w0.x * k.y + w0.y * k.x);
-    Cg[plane + t] = make_double2(w12.x * k.y, w12.y * k.y);
+// Inverse FFT (unnormalised) of the spectrum in registers, laid out as
+// fi_forward leaves it; put(line, i, value) takes the results, from LDS.
+// Taken as the conjugate of the forward FFT of the conjugate.
+template <typename Put>
+__device__ __forceinline__ void fi_inverse(const FiLines& f, double2 (&v)[16], Put put) {
+#pragma unroll
+  for (int e = 0; e < 16; ++e) v[e].y = -v[e].y;
+  const int rem = f.logF % 3;
+  int logNs = 0;
+#pragma unroll 1
+  for (;;) {
+    fi_pass<8>(f, v, logNs);
+    if (logNs + 3 >= f.logF) break;
+    fi_store<8>(f, v, logNs);
+    __syncthreads();
+    logNs += 3;
+    if (logNs + rem == f.logF && rem != 0) break;
+    fi_fetch<8>(f, v);
+    __syncthreads();
+  }
+  if (rem == 0) {
+    fi_store<8>(f, v, f.logF - 3);
+  } else if (rem == 1) {
+    fi_fetch<2>(f, v);
+    __syncthreads();
+    fi_pass<2>(f, v, f.logF - 1);
+    fi_store<2>(f, v, f.logF - 1);
+  } else {
+    fi_fetch<4>(f, v);
+    __syncthreads();
+    fi_pass<4>(f, v, f.logF - 2);
+    fi_store<4>(f, v, f.logF - 2);
+  }
+  __syncthreads();
+#pragma unroll 4
+  for (int e = threadIdx.x; e < FI_PTS; e += 256) {
+    const double2 z = f.s[f.at(f.line(e), f.num(e))];
+    put(f.line(e), f.num(e), make_double2(z.x, -z.y));
+  }
+  __syncthreads();
+}
+
+// Row FFTs: plane ch at Cg + ch * plane, rows 0 .. N - 1 with row stride F.
+__global__ __launch_bounds__(256, 2) void fi_rows_fwd_kernel(const unsigned long long* __restrict__ G,
+                                                             const FiParams* __restrict__ gp, int p,
+                                                             const double2* __restrict__ tw,
+                                                             double2* __restrict__ Cg, int64_t plane) {
+  __shared__ double2 s[FI_PTS];
+  const FiParams g = *gp;
+  const FiLines f = fi_lines(g.logF, s, tw);
+  const int F = g.F, N = g.N;
+  const int64_t NN = int64_t(N) * N;
+  const int groups = (N + (1 << f.logL) - 1) >> f.logL;  // groups of L rows, per plane
+  const double inv = 1.0 / g.scale;
+  const double delta = g.h / double(p);
+  for (int w = blockIdx.x; w < 3 * groups; w += gridDim.x) {
+    const int ch = w / groups, r0 = (w - ch * groups) << f.logL;
+    double2* Cp = Cg + ch * plane;
+    double2 v[16];
+    fi_forward(f, v, [&](int ln, int i) {
+      const int row = r0 + ln;
+      double2 z = make_double2(0.0, 0.0);
+      if (row >= N) return z;
+      if (ch < 2) {
+        if (i < N) {
+          const int node = row * N + i;
+          if (ch == 0) z.x = double((long long)G[node]) * inv;
+          else z = make_double2(double((long long)G[NN + node]) * inv, double((long long)G[2 * NN + node]) * inv);
+        }
+      } else if (i < N || i > F - N) {
+        const double dx = delta * double(row), dy = delta * double(i < N ? i : i - F);
+        const double k1 = 1.0 / (1.0 + dx * dx + dy * dy);
+        z = make_double2(k1, k1 * k1);
+      }
+      return z;
+    });
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int q = int(threadIdx.x) + 256 * u, row = r0 + f.line(q), j = f.num(q);
+      if (row >= N) continue;
+#pragma unroll
+      for (int r = 0; r < 8; ++r) Cp[row * F + j + (r << (f.logF - 3))] = v[8 * u + r];
+    }
+  }
+}
+
+__global__ __launch_bounds__(256, 2) void fi_cols_kernel(const FiParams* __restrict__ gp,
+                                                         const double2* __restrict__ tw, double2* __restrict__ Cg,
+                                                         int64_t plane) {
+  __shared__ double2 s[FI_PTS];
+  const FiLines f = fi_lines(gp->logF, s, tw);
+  const int F = gp->F, N = gp->N;
+  const int groups = F >> f.logL;  // (L = 4096 / F divides F = 64 .. 4096)
+  for (int w = blockIdx.x; w < groups; w += gridDim.x) {
+    const int c0 = w << f.logL;
+    double2 kh[16], v[16];
+    const double2* Kp = Cg + 2 * plane + c0;
+    fi_forward(f, kh, [&](int ln, int i) {
+      const int row = i < N ? i : F - i;
+      return row < N ? Kp[row * F + ln] : make_double2(0.0, 0.0);
+    });
+#pragma unroll 1
+    for (int ch = 0; ch < 2; ++ch) {
+      double2* Cp = Cg + ch * plane + c0;
+      fi_forward(f, v, [&](int ln, int i) {
+        return i < N ? Cp[i * F + ln] : make_double2(0.0, 0.0);
+      });
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        v[e] = ch == 0 ? cmul(v[e], kh[e]) : make_double2(v[e].x * kh[e].y, v[e].y * kh[e].y);
+      fi_inverse(f, v, [&](int ln, int i, double2 z) {
+        if (i < N) Cp[i * F + ln] = z;
+      });
+    }
+  }
+}
+
+__global__ __launch_bounds__(256, 2) void fi_rows_inv_kernel(const FiParams* __restrict__ gp,
+                                                             const double2* __restrict__ tw,
+                                                             double2* __restrict__ Cg, int64_t plane) {
+  __shared__ double2 s[FI_PTS];
+  const FiLines f = fi_lines(gp->logF, s, tw);
+  const int F = gp->F, N = gp->N;
+  const int groups = (N + (1 << f.logL) - 1) >> f.logL;
+  for (int w = blockIdx.x; w < 2 * groups; w += gridDim.x) {
+    const int ch = w / groups, r0 = (w - ch * groups) << f.logL;
+    double2* Cp = Cg + ch * plane;
+    double2 v[16];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int q = int(threadIdx.x) + 256 * u, row = r0 + f.line(q), j = f.num(q);
+#pragma unroll
+      for (int r = 0; r < 8; ++r)
+        v[8 * u + r] = row < N ? Cp[row * F + j + (r << (f.logF - 3))] : make_double2(0.0, 0.0);
+    }
+    fi_inverse(f, v, [&](int ln, int i, double2 z) {
+      if (i < N && r0 + ln < N) Cp[(r0 + ln) * F + i] = z;
+    });
   }
 }
 
@@ -558,7 +781,7 @@ __global__ __launch_bounds__(256) void fi_gather_kernel(const float2* __restrict
 }
 
 struct FiPlan {
-  size_t o_part, o_par, o_G, o_C, o_R, o_Zb, o_kl, o_cnt, o_cur, o_off, o_bsum, o_ord, o_nch, o_choff, bytes;
+  size_t o_part, o_par, o_tw, o_G, o_C, o_R, o_Zb, o_kl, o_cnt, o_off, o_bsum, o_ord, o_nheavy, o_heavy, bytes;
   int64_t plane, nbox;  // nbox: boxes of the largest grid (B <= max_fft / 4)
 };
 
@@ -567,17 +790,18 @@ FiPlan fi_plan(int64_t n, int max_fft) {
   Carve c;
   const int64_t Nmax = max_fft / 2;
   const int64_t Bmax = max_fft / 4;  // p >= 2
-  L.plane = int64_t(max_fft) * max_fft;
+  L.plane = Nmax * max_fft;  // rows past N <= F / 2 hold no data
   L.nbox = Bmax * Bmax;
   L.o_part = c.take(sizeof(float) * 2 * FI_GRID);
   L.o_par = c.take(sizeof(FiParams));
-  L.o_cnt = c.take(sizeof(int) * size_t(L.nbox));
-  L.o_cur = c.take(sizeof(int) * size_t(L.nbox));
+  L.o_tw = c.take(sizeof(double2) * size_t(max_fft));
+  L.o_cnt = c.take(sizeof(int) * 2 * size_t(L.nbox));  // counts, then the scatter's cursors
   L.o_off = c.take(sizeof(int64_t) * size_t(L.nbox + 1));
   L.o_bsum = c.take(sizeof(int64_t) * (size_t(ceil_div(L.nbox + 1, SCAN_CHUNK)) + 1));
   L.o_ord = c.take(sizeof(int32_t) * size_t(n));
-  L.o_nch = c.take(sizeof(int) * size_t(L.nbox));
-  L.o_choff = c.take(sizeof(int64_t) * size_t(L.nbox + 1));
+  L.o_nheavy = c.take(sizeof(int));
+  // a heavy box of m > FI_HEAVY points has fewer than 2 m / FI_HEAVY chunks
+  L.o_heavy = c.take(sizeof(int2) * size_t(2 * ceil_div(n, FI_HEAVY)));
   L.o_G = c.take(sizeof(unsigned long long) * 3 * size_t(Nmax) * size_t(Nmax));
   L.o_C = c.take(sizeof(double2) * 3 * size_t(L.plane));
   L.o_R = c.take(sizeof(float2) * size_t(n));
@@ -588,44 +812,38 @@ FiPlan fi_plan(int64_t n, int max_fft) {
 }
 
 template <int P>
-int fi_launch_points(bool spread, const float2* Y, int64_t n, const FiParams* par, const int64_t* off,
-                     const int32_t* order, const int64_t* choff, int64_t nbox, unsigned long long* G,
-                     const double2* Cg, int64_t plane, float2* R, double* Zb, hipStream_t s) {
-  if (spread) {
-    hipLaunchKernelGGL(fi_accum_kernel<P>, dim3(unsigned(ceil_div(nbox, 256))), dim3(256), 0, s, Y, par, off, order,
-                       G);
-    TSNE_CHECK_LAUNCH();
-    // at most n / FI_HEAVY + (heavy boxes <= n / FI_HEAVY) chunks
-    const int64_t blocks = ceil_div(2 * ceil_div(n, FI_HEAVY), 256);
-    hipLaunchKernelGGL(fi_accum_heavy_kernel<P>, dim3(unsigned(blocks < 4096 ? blocks : 4096)), dim3(256), 0, s, Y,
-                       par, off, order, choff, nbox, G);
-  } else {
-    hipLaunchKernelGGL(fi_gather_kernel<P>, dim3(FI_GRID), dim3(256), 0, s, Y, n, par, Cg, plane, R, Zb);
-  }
+int fi_spread(const float2* Y, int64_t n, const FiParams* par, const int64_t* off, const int32_t* order,
+              int64_t nbox, int* nheavy, int2* heavy, unsigned long long* G, hipStream_t s) {
+  const int64_t blocks = ceil_div(nbox, 16);
+  hipLaunchKernelGGL(fi_accum_kernel<P>, dim3(unsigned(blocks < 2048 ? blocks : 2048)), dim3(256), 0, s, Y, par, off,
+                     order, G, nheavy, heavy);
+  TSNE_CHECK_LAUNCH();
+  const int64_t hblocks = ceil_div(2 * ceil_div(n, FI_HEAVY), 16);
+  hipLaunchKernelGGL(fi_accum_heavy_kernel<P>, dim3(unsigned(hblocks < 2048 ? hblocks : 2048)), dim3(256), 0, s, Y,
+                     par, off, order, nheavy, heavy, G);
   TSNE_CHECK_LAUNCH();
   return TSNE_OK;
 }
 
-int fi_points(int p, bool spread, const float2* Y, int64_t n, const FiParams* par, const int64_t* off,
-              const int32_t* order, const int64_t* choff, int64_t nbox, unsigned long long* G, const double2* Cg,
-              int64_t plane, float2* R,
-              double* Zb, hipStream_t s) {
-  switch (p) {
-    case 2: return fi_launch_points<2>(spread, Y, n, par, off, order, choff, nbox, G, Cg, plane, R, Zb, s);
-    case 3: return fi_launch_points<3>(spread, Y, n, par, off, order, choff, nbox, G, Cg, plane, R, Zb, s);
-    case 4: return fi_launch_points<4>(spread, Y, n, par, off, order, choff, nbox, G, Cg, plane, R, Zb, s);
-    default: return fi_launch_points<5>(spread, Y, n, par, off, order, choff, nbox, G, Cg, plane, R, Zb, s);
-  }
+template <int P>
+int fi_collect(const float2* Y, int64_t n, const FiParams* par, const double2* Cg, int64_t plane, float2* R,
+               double* Zb, hipStream_t s) {
+  hipLaunchKernelGGL(fi_gather_kernel<P>, dim3(FI_GRID), dim3(256), 0, s, Y, n, par, Cg, plane, R, Zb);
+  TSNE_CHECK_LAUNCH();
+  return TSNE_OK;
 }
 
-int fi_fft2(double2* Cg, int64_t plane, int nch, const FiParams* par, int max_fft, double sign, hipStream_t s) {
-  const size_t lds = sizeof(double2) * size_t(max_fft);
-  const unsigned rgrid = unsigned(max_fft < 2048 ? 2048 : max_fft);
-  hipLaunchKernelGGL(fi_fft_rows_kernel, dim3(rgrid), dim3(256), lds, s, Cg, plane, nch, par, sign);
+// The convolution: G to the potentials' planes 0 and 1 of Cg.  The grids
+// cover the largest transform; the kernels stop at the sizes in par.
+int fi_convolve(const unsigned long long* G, const FiParams* par, int p, const double2* tw, double2* Cg,
+                int64_t plane, int max_fft, hipStream_t s) {
+  auto blocks = [](int64_t b) { return dim3(unsigned(b < 1024 ? b : 1024)); };
+  const int64_t rows = ceil_div(int64_t(max_fft) * (max_fft / 2), FI_PTS);  // groups of rows of a plane
+  hipLaunchKernelGGL(fi_rows_fwd_kernel, blocks(3 * rows), dim3(256), 0, s, G, par, p, tw, Cg, plane);
   TSNE_CHECK_LAUNCH();
-  hipLaunchKernelGGL(fi_transpose_kernel, dim3(4096), dim3(256), 0, s, Cg, plane, nch, par);
+  hipLaunchKernelGGL(fi_cols_kernel, blocks(2 * rows), dim3(256), 0, s, par, tw, Cg, plane);
   TSNE_CHECK_LAUNCH();
-  hipLaunchKernelGGL(fi_fft_rows_kernel, dim3(rgrid), dim3(256), lds, s, Cg, plane, nch, par, sign);
+  hipLaunchKernelGGL(fi_rows_inv_kernel, blocks(2 * rows), dim3(256), 0, s, par, tw, Cg, plane);
   TSNE_CHECK_LAUNCH();
   return TSNE_OK;
 }
@@ -661,40 +879,42 @@ extern "C" int tsne_kl_grad_fft(const float* Y, int64_t n, const int64_t* row_pt
   double* Zb = reinterpret_cast<double*>(ws + L.o_Zb);
   double* klp = reinterpret_cast<double*>(ws + L.o_kl);
   int* cnt = reinterpret_cast<int*>(ws + L.o_cnt);
-  int* cur = reinterpret_cast<int*>(ws + L.o_cur);
+  int* cur = cnt + L.nbox;
   int64_t* off = reinterpret_cast<int64_t*>(ws + L.o_off);
   int64_t* bsum = reinterpret_cast<int64_t*>(ws + L.o_bsum);
   int32_t* order = reinterpret_cast<int32_t*>(ws + L.o_ord);
-  int* nch = reinterpret_cast<int*>(ws + L.o_nch);
-  int64_t* choff = reinterpret_cast<int64_t*>(ws + L.o_choff);
+  double2* tw = reinterpret_cast<double2*>(ws + L.o_tw);
+  int* nheavy = reinterpret_cast<int*>(ws + L.o_nheavy);
+  int2* heavy = reinterpret_cast<int2*>(ws + L.o_heavy);
 
   hipLaunchKernelGGL(fi_bbox_kernel, dim3(FI_GRID), dim3(256), 0, s, Y2, n, part);
   TSNE_CHECK_LAUNCH();
   hipLaunchKernelGGL(fi_params_kernel, dim3(1), dim3(256), 0, s, part, FI_GRID, n, n_interp, min_boxes,
-                     max_box_width, max_fft, par);
+                     max_box_width, max_fft, par, tw, nheavy);
   TSNE_CHECK_LAUNCH();
   // counting sort of the points by box, then the per-box node sums
-  if ((rc = launch_fill<int>(cnt, L.nbox, 0, s))) return rc;
-  if ((rc = launch_fill<int>(cur, L.nbox, 0, s))) return rc;
+  if ((rc = launch_fill<int>(cnt, 2 * L.nbox, 0, s))) return rc;
   const dim3 pgrid(unsigned(ceil_div(n, 256) < FI_CBLOCKS ? ceil_div(n, 256) : FI_CBLOCKS));
   hipLaunchKernelGGL(fi_count_kernel, pgrid, dim3(256), 0, s, Y2, n, par, cnt);
   TSNE_CHECK_LAUNCH();
   if ((rc = exclusive_scan<int>(cnt, L.nbox, off, bsum, s))) return rc;
   hipLaunchKernelGGL(fi_scatter_kernel, pgrid, dim3(256), 0, s, Y2, n, par, off, cur, order);
   TSNE_CHECK_LAUNCH();
-  // the chunks of the heavy boxes (more than FI_HEAVY points), listed by a scan
-  const int64_t bgrid = ceil_div(L.nbox, 256) < 4096 ? ceil_div(L.nbox, 256) : 4096;
-  hipLaunchKernelGGL(fi_chunks_kernel, dim3(unsigned(bgrid)), dim3(256), 0, s, par, cnt, L.nbox, nch);
-  TSNE_CHECK_LAUNCH();
-  if ((rc = exclusive_scan<int>(nch, L.nbox, choff, bsum, s))) return rc;
-  if ((rc = fi_points(n_interp, true, Y2, n, par, off, order, choff, L.nbox, G, Cg, L.plane, R, Zb, s))) return rc;
-  hipLaunchKernelGGL(fi_load_kernel, dim3(4096), dim3(256), 0, s, G, par, n_interp, Cg, L.plane);
-  TSNE_CHECK_LAUNCH();
-  if ((rc = fi_fft2(Cg, L.plane, 3, par, max_fft, -1.0, s))) return rc;
-  hipLaunchKernelGGL(fi_mult_kernel, dim3(4096), dim3(256), 0, s, Cg, L.plane, par);
-  TSNE_CHECK_LAUNCH();
-  if ((rc = fi_fft2(Cg, L.plane, 2, par, max_fft, 1.0, s))) return rc;
-  if ((rc = fi_points(n_interp, false, Y2, n, par, off, order, choff, L.nbox, G, Cg, L.plane, R, Zb, s))) return rc;
+  switch (n_interp) {
+    case 2: rc = fi_spread<2>(Y2, n, par, off, order, L.nbox, nheavy, heavy, G, s); break;
+    case 3: rc = fi_spread<3>(Y2, n, par, off, order, L.nbox, nheavy, heavy, G, s); break;
+    case 4: rc = fi_spread<4>(Y2, n, par, off, order, L.nbox, nheavy, heavy, G, s); break;
+    default: rc = fi_spread<5>(Y2, n, par, off, order, L.nbox, nheavy, heavy, G, s);
+  }
+  if (rc) return rc;
+  if ((rc = fi_convolve(G, par, n_interp, tw, Cg, L.plane, max_fft, s))) return rc;
+  switch (n_interp) {
+    case 2: rc = fi_collect<2>(Y2, n, par, Cg, L.plane, R, Zb, s); break;
+    case 3: rc = fi_collect<3>(Y2, n, par, Cg, L.plane, R, Zb, s); break;
+    case 4: rc = fi_collect<4>(Y2, n, par, Cg, L.plane, R, Zb, s); break;
+    default: rc = fi_collect<5>(Y2, n, par, Cg, L.plane, R, Zb, s);
+  }
+  if (rc) return rc;
   // the attraction takes the rows in box order (a spatial order of Y: rows
   // that share P-neighbours run together, so their y_j gathers hit L2); the
   // order within a box follows the scatter's atomics, so a requested KL, whose

@@ -159,3 +159,43 @@ def test_fft_grad_clustered_embedding(dev):
     assert abs(Z - Zo) <= 1e-9 * Zo
     g2, Z2, _ = gpu_fft(dev, Y, So, 1.0)
     assert np.array_equal(g, g2) and Z == Z2
+
+
+# Every transform size (the passes differ by log2 F mod 3 and by the number of
+# rows a block takes), each with the grid at its fullest (N = F / 2) and just
+# past the size below (N = F / 4 + p).  Z and the repulsion are FP64 sums on
+# both sides (1e-9); the gradient carries FP32 attraction terms.
+@pytest.mark.parametrize("F", [64, 128, 256, 512, 1024, 2048, 4096])
+@pytest.mark.parametrize("full", [True, False])
+def test_fft_grad_every_transform_size(dev, F, full):
+    say("fft grad transform size", F, full)
+    n, p = 1201, 2
+    _, _, _, S = random_graph_P(n, 10, 3.0, 21)
+    So = widen(S)
+    Y = synth.random_embedding(n, 4.0, 3100 + F)
+    B = F // (2 * p) if full else F // (4 * p) + 1
+    kw = dict(min_boxes=B, max_box_width=1e6, max_fft=F)
+    g, Z, kl = gpu_fft(dev, Y, So, 1.0, n_interp=p, **kw)
+    go, Zo, klo = I.kl_grad(Y, So, 1.0, p=p, **kw)
+    assert rel(g, go) <= GRAD_RTOL, rel(g, go)
+    assert abs(Z - Zo) <= 1e-9 * Zo
+    assert abs(kl - klo) <= 1e-5 * max(1.0, abs(klo))
+
+
+@pytest.mark.parametrize("p", [2, 3, 4, 5])
+def test_fft_grad_box_occupancies(dev, p):
+    # boxes holding 1, 15 .. 17 points (the 16 lanes of a box), 63 .. 65 (the
+    # points in flight), 255 .. 257 and 511 .. 513 (the chunks of a heavy box)
+    say("fft grad box occupancies", p)
+    counts = [1, 15, 16, 17, 63, 64, 65, 255, 256, 257, 511, 512, 513, 2049]
+    rng = np.random.default_rng(31)
+    Y = np.concatenate([[-8.0, 2.0 * (q % 7)] + rng.uniform(0.2, 0.7, (m, 2)) + [2.0 * (q // 7), 0.0]
+                        for q, m in enumerate(counts)])
+    Y = rng.permutation(np.concatenate([Y, [[-10.0, -10.0], [30.0, 30.0]]])).astype(np.float32)
+    _, _, _, S = random_graph_P(Y.shape[0], 10, 3.0, 22)
+    So = widen(S)
+    kw = dict(min_boxes=40, max_box_width=1.0, max_fft=512)
+    g, Z, kl = gpu_fft(dev, Y, So, 1.0, n_interp=p, **kw)
+    go, Zo, klo = I.kl_grad(Y, So, 1.0, p=p, **kw)
+    assert rel(g, go) <= GRAD_RTOL, rel(g, go)
+    assert abs(Z - Zo) <= 1e-9 * Zo
