@@ -180,82 +180,68 @@ __device__ __forceinline__ int fi_box(float y, const FiParams& g) {
   return int(fmin(fmax(floor(t), 0.0), double(g.B - 1)));
 }
 
-// Counting sort of the points by box, with the counts gathered per block:
-// a block counts its points in an LDS table (open addressing, at most
+// Counting sort of the points by box, with the counts gathered per block: a
+// block counts its FI_CPTS points in an LDS table (open addressing, at most
 // FI_PROBE probes; a key that finds no slot is counted in global memory
-// directly) and adds each distinct box once.  When most points fall in a
-// few boxes (a compact or clustered embedding) this replaces the
-// contended global atomics on those boxes' counters by one per block.
-constexpr int FI_TBL = 4096;      // LDS slots per block
+// directly) and adds each distinct box once.  When most points fall in a few
+// boxes (a compact or clustered embedding) this replaces the contended
+// global atomics on those boxes' counters by one per block.  The atomics
+// return each point's rank within its box, so that the scatter after the
+// prefix sum is a plain pass (counting and hashing a second time there took
+// 75 us at 10^6 points).
+constexpr int FI_CPPT = 4;              // points per thread
+constexpr int FI_CPTS = 256 * FI_CPPT;  // points per block
+constexpr int FI_TBL = 2048;            // LDS slots per block
 constexpr int FI_PROBE = 8;
-constexpr int FI_CBLOCKS = 1024;  // blocks of the counting kernels
 
-__device__ __forceinline__ int fi_tbl_find(int* tkey, int key, bool insert) {
+__device__ __forceinline__ int fi_tbl_find(int* tkey, int key) {
   const uint32_t h = uint32_t(key) * 2654435761u;
   for (int q = 0; q < FI_PROBE; ++q) {
     const int slot = int((h + uint32_t(q)) & (FI_TBL - 1));
-    const int prev = insert ? atomicCAS(&tkey[slot], -1, key) : tkey[slot];
-    if (prev == key || (insert && prev == -1)) return slot;
-    if (!insert && prev == -1) return -1;
+    const int prev = atomicCAS(&tkey[slot], -1, key);
+    if (prev == key || prev == -1) return slot;
   }
   return -1;
 }
 
 __global__ __launch_bounds__(256) void fi_count_kernel(const float2* __restrict__ Y, int64_t n,
-                                                       const FiParams* __restrict__ gp, int* __restrict__ cnt) {
+                                                       const FiParams* __restrict__ gp, int* __restrict__ cnt,
+                                                       int2* __restrict__ where) {
   __shared__ int tkey[FI_TBL], tcnt[FI_TBL];
   const FiParams g = *gp;
   for (int q = threadIdx.x; q < FI_TBL; q += 256) {
     tkey[q] = -1;
     tcnt[q] = 0;
   }
+  const int64_t i0 = int64_t(blockIdx.x) * FI_CPTS + threadIdx.x;
+  float2 y[FI_CPPT];
+#pragma unroll
+  for (int u = 0; u < FI_CPPT; ++u) y[u] = Y[i0 + 256 * u < n ? i0 + 256 * u : n - 1];
   __syncthreads();
-  for (int64_t i = gtid(); i < n; i += int64_t(gridDim.x) * 256) {
-    const float2 y = Y[i];
-    const int b = fi_box(y.x, g) * g.B + fi_box(y.y, g);
-    const int slot = fi_tbl_find(tkey, b, true);
-    if (slot >= 0) atomicAdd(&tcnt[slot], 1);
-    else atomicAdd(&cnt[b], 1);
+  int box[FI_CPPT], slot[FI_CPPT], rank[FI_CPPT];
+#pragma unroll
+  for (int u = 0; u < FI_CPPT; ++u) {
+    if (i0 + 256 * u >= n) continue;
+    box[u] = fi_box(y[u].x, g) * g.B + fi_box(y[u].y, g);
+    slot[u] = fi_tbl_find(tkey, box[u]);
+    rank[u] = slot[u] >= 0 ? atomicAdd(&tcnt[slot[u]], 1) : atomicAdd(&cnt[box[u]], 1);
   }
   __syncthreads();
   for (int q = threadIdx.x; q < FI_TBL; q += 256)
-    if (tcnt[q]) atomicAdd(&cnt[tkey[q]], tcnt[q]);
+    if (tcnt[q]) tcnt[q] = atomicAdd(&cnt[tkey[q]], tcnt[q]);  // the block's start within the box
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < FI_CPPT; ++u)
+    if (i0 + 256 * u < n) where[i0 + 256 * u] = make_int2(box[u], rank[u] + (slot[u] >= 0 ? tcnt[slot[u]] : 0));
 }
 
-// The same table, twice over the block's points: first the counts, then one
-// global reservation per box (the block's range within the box), then each
-// point's position (the range's start plus its rank).  A key without a slot
-// takes its position from the global cursor directly, in both passes alike.
-__global__ __launch_bounds__(256) void fi_scatter_kernel(const float2* __restrict__ Y, int64_t n,
-                                                         const FiParams* __restrict__ gp,
-                                                         const int64_t* __restrict__ off, int* __restrict__ cur,
+__global__ __launch_bounds__(256) void fi_scatter_kernel(int64_t n, const int2* __restrict__ where,
+                                                         const int64_t* __restrict__ off,
                                                          int32_t* __restrict__ order) {
-  __shared__ int tkey[FI_TBL], tcnt[FI_TBL], tbase[FI_TBL];
-  const FiParams g = *gp;
-  for (int q = threadIdx.x; q < FI_TBL; q += 256) {
-    tkey[q] = -1;
-    tcnt[q] = 0;
-  }
-  __syncthreads();
-  for (int64_t i = gtid(); i < n; i += int64_t(gridDim.x) * 256) {
-    const float2 y = Y[i];
-    const int b = fi_box(y.x, g) * g.B + fi_box(y.y, g);
-    const int slot = fi_tbl_find(tkey, b, true);
-    if (slot >= 0) atomicAdd(&tcnt[slot], 1);
-  }
-  __syncthreads();
-  for (int q = threadIdx.x; q < FI_TBL; q += 256) {
-    tbase[q] = tcnt[q] ? atomicAdd(&cur[tkey[q]], tcnt[q]) : 0;
-    tcnt[q] = 0;
-  }
-  __syncthreads();
-  for (int64_t i = gtid(); i < n; i += int64_t(gridDim.x) * 256) {
-    const float2 y = Y[i];
-    const int b = fi_box(y.x, g) * g.B + fi_box(y.y, g);
-    const int slot = fi_tbl_find(tkey, b, false);
-    const int pos = slot >= 0 ? tbase[slot] + atomicAdd(&tcnt[slot], 1) : atomicAdd(&cur[b], 1);
-    order[off[b] + pos] = int32_t(i);
-  }
+  const int64_t i = gtid();
+  if (i >= n) return;
+  const int2 w = where[i];
+  order[off[w.x] + w.y] = int32_t(i);
 }
 
 // Node sums.  16 lanes (a DPP row) share a box: each adds its points'
@@ -424,19 +410,19 @@ __global__ __launch_bounds__(256) void fi_accum_heavy_kernel(const float2* __res
 //   fi_rows_inv_kernel  the inverse row FFTs of those N rows, of which N
 //                       columns are kept (the only ones the gather reads).
 // What bounds it: latency and LDS round trips, the data (3 N F complex
-// numbers, 17 MB at F = 1024) staying in L2 / MALL.  A block works on 4096
-// complex numbers in 64 KB of LDS, L = 4096 / F lines together, so two
-// blocks share a CU and a wave's accesses of a column pass cover L adjacent
-// columns; a thread holds 16 elements in registers (radix 8, the factor 2 or
-// 4 that is left over first in the forward and last in the inverse
-// direction, so that a column's spectrum goes from the forward FFT's last
-// pass to the inverse's first in registers).  Twiddles: one table of exp(-2 pi i k /
+// numbers, 17 MB at F = 1024) staying in L2 / MALL.  A block of T threads
+// works on 8 T complex numbers in LDS (T = 256: 32 KB, for transforms up to
+// 2048; T = 512 for 4096), L = 8 T / F lines together, and a thread holds 8
+// elements in registers: radix 8, the factor 2 or 4 that is left over first
+// in the forward and last in the inverse direction, so that a column's
+// spectrum goes from the forward FFT's last pass to the inverse's first in
+// registers.  (16 elements per thread halve the wavefronts and spilled the
+// column pass: 46 us.)  Twiddles: one table of exp(-2 pi i k /
 // F) per call, the powers 2 .. 7 by multiplication.
-// Measured at F = 1024 (70,001 and 10^6 points): 17 + 46 + 12 us for the
+// Measured at F = 1024 (70,001 and 10^6 points): 11 + 31 + 11 us for the
 // three passes, against 250 us for radix-2 row passes with a sincospi per
 // butterfly over all F rows, transposes, a load and a product pass (eight
-// launches); a call at 70,001 points 0.43 -> 0.20 ms with the new node sums.
-constexpr int FI_PTS = 4096;  // complex numbers per block
+// launches).
 
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
   return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
@@ -494,8 +480,9 @@ struct FiLines {
   __device__ __forceinline__ int line(int q) const { return q & ((1 << logL) - 1); }
   __device__ __forceinline__ int num(int q) const { return q >> logL; }
 };
-__device__ __forceinline__ FiLines fi_lines(int logF, double2* s, const double2* tw) {
-  return FiLines{logF, 12 - logF, logF > 9 ? logF - 9 : 0, s, tw};
+__device__ __forceinline__ FiLines fi_lines(int logPts, int logF, double2* s, const double2* tw) {
+  const int logL = logPts - logF;
+  return FiLines{logF, logL, logL < 3 ? 3 - logL : 0, s, tw};
 }
 
 // threadIdx.x, opaque at every use: the LDS addresses of a pass are then
@@ -510,15 +497,15 @@ __device__ __forceinline__ int fi_tid() {
 // Pass of radix R over the 16 elements a thread holds, v[u R + r] = element
 // num + r F / R of butterfly u (q = tid + 256 u): twiddles for sub-transforms
 // of length Ns = 2^logNs, then the length-R DFTs.
-template <int R>
-__device__ __forceinline__ void fi_pass(const FiLines& f, double2 (&v)[16], int logNs) {
+template <int T, int R>
+__device__ __forceinline__ void fi_pass(const FiLines& f, double2 (&v)[8], int logNs) {
   constexpr int logR = R == 8 ? 3 : (R == 4 ? 2 : 1);
   const int t = fi_tid();
 #pragma unroll
-  for (int u = 0; u < 16 / R; ++u) {
+  for (int u = 0; u < 8 / R; ++u) {
     double2* w = v + u * R;
     if (logNs > 0) {
-      const int k = f.num(t + 256 * u) & ((1 << logNs) - 1);
+      const int k = f.num(t + T * u) & ((1 << logNs) - 1);
       const double2 w1 = f.tw[k << (f.logF - logR - logNs)];
       double2 p = w1;
 #pragma unroll
@@ -534,24 +521,24 @@ __device__ __forceinline__ void fi_pass(const FiLines& f, double2 (&v)[16], int 
   }
 }
 // The pass's outputs to LDS (Stockham order), and the next pass's inputs.
-template <int R>
-__device__ __forceinline__ void fi_store(const FiLines& f, const double2 (&v)[16], int logNs) {
+template <int T, int R>
+__device__ __forceinline__ void fi_store(const FiLines& f, const double2 (&v)[8], int logNs) {
   const int t = fi_tid();
 #pragma unroll
-  for (int u = 0; u < 16 / R; ++u) {
-    const int q = t + 256 * u, ln = f.line(q), j = f.num(q);
+  for (int u = 0; u < 8 / R; ++u) {
+    const int q = t + T * u, ln = f.line(q), j = f.num(q);
     const int k = j & ((1 << logNs) - 1);
 #pragma unroll
     for (int r = 0; r < R; ++r) f.s[f.at(ln, (j - k) * R + k + (r << logNs))] = v[u * R + r];
   }
 }
-template <int R>
-__device__ __forceinline__ void fi_fetch(const FiLines& f, double2 (&v)[16]) {
+template <int T, int R>
+__device__ __forceinline__ void fi_fetch(const FiLines& f, double2 (&v)[8]) {
   constexpr int logR = R == 8 ? 3 : (R == 4 ? 2 : 1);
   const int t = fi_tid();
 #pragma unroll
-  for (int u = 0; u < 16 / R; ++u) {
-    const int q = t + 256 * u, ln = f.line(q), j = f.num(q);
+  for (int u = 0; u < 8 / R; ++u) {
+    const int q = t + T * u, ln = f.line(q), j = f.num(q);
 #pragma unroll
     for (int r = 0; r < R; ++r) v[u * R + r] = f.s[f.at(ln, j + (r << (f.logF - logR)))];
   }
@@ -560,35 +547,35 @@ __device__ __forceinline__ void fi_fetch(const FiLines& f, double2 (&v)[16]) {
 // Forward FFT of the elements get(line, i), which go through LDS first (in
 // registers from the start, their addresses made the kernels spill); the
 // result is left in registers: v[8 u + r] = bin num + r F / 8 of butterfly u.
-template <typename Get>
-__device__ __forceinline__ void fi_forward(const FiLines& f, double2 (&v)[16], Get get) {
+template <int T, typename Get>
+__device__ __forceinline__ void fi_forward(const FiLines& f, double2 (&v)[8], Get get) {
 #pragma unroll 4
-  for (int e = threadIdx.x; e < FI_PTS; e += 256) f.s[f.at(f.line(e), f.num(e))] = get(f.line(e), f.num(e));
+  for (int e = threadIdx.x; e < 8 * T; e += T) f.s[f.at(f.line(e), f.num(e))] = get(f.line(e), f.num(e));
   __syncthreads();
   const int rem = f.logF % 3;
   int logNs = 0;
   if (rem == 1) {
-    fi_fetch<2>(f, v);
-    fi_pass<2>(f, v, 0);
+    fi_fetch<T, 2>(f, v);
+    fi_pass<T, 2>(f, v, 0);
     __syncthreads();
-    fi_store<2>(f, v, 0);
+    fi_store<T, 2>(f, v, 0);
     __syncthreads();
     logNs = 1;
   } else if (rem == 2) {
-    fi_fetch<4>(f, v);
-    fi_pass<4>(f, v, 0);
+    fi_fetch<T, 4>(f, v);
+    fi_pass<T, 4>(f, v, 0);
     __syncthreads();
-    fi_store<4>(f, v, 0);
+    fi_store<T, 4>(f, v, 0);
     __syncthreads();
     logNs = 2;
   }
 #pragma unroll 1
   for (;;) {
-    fi_fetch<8>(f, v);
+    fi_fetch<T, 8>(f, v);
     __syncthreads();  // every element read
-    fi_pass<8>(f, v, logNs);
+    fi_pass<T, 8>(f, v, logNs);
     if (logNs + 3 >= f.logF) break;
-    fi_store<8>(f, v, logNs);
+    fi_store<T, 8>(f, v, logNs);
     __syncthreads();
     logNs += 3;
   }
@@ -597,39 +584,39 @@ __device__ __forceinline__ void fi_forward(const FiLines& f, double2 (&v)[16], G
 // Inverse FFT (unnormalised) of the spectrum in registers, laid out as
 // fi_forward leaves it; put(line, i, value) takes the results, from LDS.
 // Taken as the conjugate of the forward FFT of the conjugate.
-template <typename Put>
-__device__ __forceinline__ void fi_inverse(const FiLines& f, double2 (&v)[16], Put put) {
+template <int T, typename Put>
+__device__ __forceinline__ void fi_inverse(const FiLines& f, double2 (&v)[8], Put put) {
 #pragma unroll
-  for (int e = 0; e < 16; ++e) v[e].y = -v[e].y;
+  for (int e = 0; e < 8; ++e) v[e].y = -v[e].y;
   const int rem = f.logF % 3;
   int logNs = 0;
 #pragma unroll 1
   for (;;) {
-    fi_pass<8>(f, v, logNs);
+    fi_pass<T, 8>(f, v, logNs);
     if (logNs + 3 >= f.logF) break;
-    fi_store<8>(f, v, logNs);
+    fi_store<T, 8>(f, v, logNs);
     __syncthreads();
     logNs += 3;
     if (logNs + rem == f.logF && rem != 0) break;
-    fi_fetch<8>(f, v);
+    fi_fetch<T, 8>(f, v);
     __syncthreads();
   }
   if (rem == 0) {
-    fi_store<8>(f, v, f.logF - 3);
+    fi_store<T, 8>(f, v, f.logF - 3);
   } else if (rem == 1) {
-    fi_fetch<2>(f, v);
+    fi_fetch<T, 2>(f, v);
     __syncthreads();
-    fi_pass<2>(f, v, f.logF - 1);
-    fi_store<2>(f, v, f.logF - 1);
+    fi_pass<T, 2>(f, v, f.logF - 1);
+    fi_store<T, 2>(f, v, f.logF - 1);
   } else {
-    fi_fetch<4>(f, v);
+    fi_fetch<T, 4>(f, v);
     __syncthreads();
-    fi_pass<4>(f, v, f.logF - 2);
-    fi_store<4>(f, v, f.logF - 2);
+    fi_pass<T, 4>(f, v, f.logF - 2);
+    fi_store<T, 4>(f, v, f.logF - 2);
   }
   __syncthreads();
 #pragma unroll 4
-  for (int e = threadIdx.x; e < FI_PTS; e += 256) {
+  for (int e = threadIdx.x; e < 8 * T; e += T) {
     const double2 z = f.s[f.at(f.line(e), f.num(e))];
     put(f.line(e), f.num(e), make_double2(z.x, -z.y));
   }
@@ -637,13 +624,14 @@ __device__ __forceinline__ void fi_inverse(const FiLines& f, double2 (&v)[16], P
 }
 
 // Row FFTs: plane ch at Cg + ch * plane, rows 0 .. N - 1 with row stride F.
-__global__ __launch_bounds__(256, 2) void fi_rows_fwd_kernel(const unsigned long long* __restrict__ G,
+template <int T>
+__global__ __launch_bounds__(T, 4) void fi_rows_fwd_kernel(const unsigned long long* __restrict__ G,
                                                              const FiParams* __restrict__ gp, int p,
                                                              const double2* __restrict__ tw,
                                                              double2* __restrict__ Cg, int64_t plane) {
-  __shared__ double2 s[FI_PTS];
+  __shared__ double2 s[8 * T];
   const FiParams g = *gp;
-  const FiLines f = fi_lines(g.logF, s, tw);
+  const FiLines f = fi_lines(T == 256 ? 11 : 12, g.logF, s, tw);
   const int F = g.F, N = g.N;
   const int64_t NN = int64_t(N) * N;
   const int groups = (N + (1 << f.logL) - 1) >> f.logL;  // groups of L rows, per plane
@@ -652,8 +640,8 @@ __global__ __launch_bounds__(256, 2) void fi_rows_fwd_kernel(const unsigned long
   for (int w = blockIdx.x; w < 3 * groups; w += gridDim.x) {
     const int ch = w / groups, r0 = (w - ch * groups) << f.logL;
     double2* Cp = Cg + ch * plane;
-    double2 v[16];
-    fi_forward(f, v, [&](int ln, int i) {
+    double2 v[8];
+    fi_forward<T>(f, v, [&](int ln, int i) {
       const int row = r0 + ln;
       double2 z = make_double2(0.0, 0.0);
       if (row >= N) return z;
@@ -670,66 +658,64 @@ __global__ __launch_bounds__(256, 2) void fi_rows_fwd_kernel(const unsigned long
       }
       return z;
     });
+    const int row = r0 + f.line(threadIdx.x), j = f.num(threadIdx.x);
+    if (row < N) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int q = int(threadIdx.x) + 256 * u, row = r0 + f.line(q), j = f.num(q);
-      if (row >= N) continue;
-#pragma unroll
-      for (int r = 0; r < 8; ++r) Cp[row * F + j + (r << (f.logF - 3))] = v[8 * u + r];
+      for (int r = 0; r < 8; ++r) Cp[row * F + j + (r << (f.logF - 3))] = v[r];
     }
   }
 }
 
-__global__ __launch_bounds__(256, 2) void fi_cols_kernel(const FiParams* __restrict__ gp,
+template <int T>
+__global__ __launch_bounds__(T, 3) void fi_cols_kernel(const FiParams* __restrict__ gp,
                                                          const double2* __restrict__ tw, double2* __restrict__ Cg,
                                                          int64_t plane) {
-  __shared__ double2 s[FI_PTS];
-  const FiLines f = fi_lines(gp->logF, s, tw);
+  __shared__ double2 s[8 * T];
+  const FiLines f = fi_lines(T == 256 ? 11 : 12, gp->logF, s, tw);
   const int F = gp->F, N = gp->N;
-  const int groups = F >> f.logL;  // (L = 4096 / F divides F = 64 .. 4096)
+  const int groups = (F + (1 << f.logL) - 1) >> f.logL;
   for (int w = blockIdx.x; w < groups; w += gridDim.x) {
-    const int c0 = w << f.logL;
-    double2 kh[16], v[16];
+    // groups that share lines of memory on one XCD (workgroups are dealt to
+    // the 8 of them round-robin)
+    const int c0 = (groups % 8 == 0 ? w % 8 * (groups / 8) + w / 8 : w) << f.logL;
+    double2 kh[8], v[8];
     const double2* Kp = Cg + 2 * plane + c0;
-    fi_forward(f, kh, [&](int ln, int i) {
+    fi_forward<T>(f, kh, [&](int ln, int i) {
       const int row = i < N ? i : F - i;
       return row < N ? Kp[row * F + ln] : make_double2(0.0, 0.0);
     });
 #pragma unroll 1
     for (int ch = 0; ch < 2; ++ch) {
       double2* Cp = Cg + ch * plane + c0;
-      fi_forward(f, v, [&](int ln, int i) {
+      fi_forward<T>(f, v, [&](int ln, int i) {
         return i < N ? Cp[i * F + ln] : make_double2(0.0, 0.0);
       });
 #pragma unroll
-      for (int e = 0; e < 16; ++e)
+      for (int e = 0; e < 8; ++e)
         v[e] = ch == 0 ? cmul(v[e], kh[e]) : make_double2(v[e].x * kh[e].y, v[e].y * kh[e].y);
-      fi_inverse(f, v, [&](int ln, int i, double2 z) {
+      fi_inverse<T>(f, v, [&](int ln, int i, double2 z) {
         if (i < N) Cp[i * F + ln] = z;
       });
     }
   }
 }
 
-__global__ __launch_bounds__(256, 2) void fi_rows_inv_kernel(const FiParams* __restrict__ gp,
+template <int T>
+__global__ __launch_bounds__(T, 4) void fi_rows_inv_kernel(const FiParams* __restrict__ gp,
                                                              const double2* __restrict__ tw,
                                                              double2* __restrict__ Cg, int64_t plane) {
-  __shared__ double2 s[FI_PTS];
-  const FiLines f = fi_lines(gp->logF, s, tw);
+  __shared__ double2 s[8 * T];
+  const FiLines f = fi_lines(T == 256 ? 11 : 12, gp->logF, s, tw);
   const int F = gp->F, N = gp->N;
   const int groups = (N + (1 << f.logL) - 1) >> f.logL;
   for (int w = blockIdx.x; w < 2 * groups; w += gridDim.x) {
     const int ch = w / groups, r0 = (w - ch * groups) << f.logL;
     double2* Cp = Cg + ch * plane;
-    double2 v[16];
+    double2 v[8];
+    const int row = r0 + f.line(threadIdx.x), j = f.num(threadIdx.x);
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int q = int(threadIdx.x) + 256 * u, row = r0 + f.line(q), j = f.num(q);
-#pragma unroll
-      for (int r = 0; r < 8; ++r)
-        v[8 * u + r] = row < N ? Cp[row * F + j + (r << (f.logF - 3))] : make_double2(0.0, 0.0);
-    }
-    fi_inverse(f, v, [&](int ln, int i, double2 z) {
+    for (int r = 0; r < 8; ++r) v[r] = row < N ? Cp[row * F + j + (r << (f.logF - 3))] : make_double2(0.0, 0.0);
+    fi_inverse<T>(f, v, [&](int ln, int i, double2 z) {
       if (i < N && r0 + ln < N) Cp[(r0 + ln) * F + i] = z;
     });
   }
@@ -781,7 +767,7 @@ __global__ __launch_bounds__(256) void fi_gather_kernel(const float2* __restrict
 }
 
 struct FiPlan {
-  size_t o_part, o_par, o_tw, o_G, o_C, o_R, o_Zb, o_kl, o_cnt, o_off, o_bsum, o_ord, o_nheavy, o_heavy, bytes;
+  size_t o_part, o_par, o_tw, o_G, o_C, o_R, o_Zb, o_kl, o_cnt, o_where, o_off, o_bsum, o_ord, o_nheavy, o_heavy, bytes;
   int64_t plane, nbox;  // nbox: boxes of the largest grid (B <= max_fft / 4)
 };
 
@@ -795,7 +781,8 @@ FiPlan fi_plan(int64_t n, int max_fft) {
   L.o_part = c.take(sizeof(float) * 2 * FI_GRID);
   L.o_par = c.take(sizeof(FiParams));
   L.o_tw = c.take(sizeof(double2) * size_t(max_fft));
-  L.o_cnt = c.take(sizeof(int) * 2 * size_t(L.nbox));  // counts, then the scatter's cursors
+  L.o_cnt = c.take(sizeof(int) * size_t(L.nbox));
+  L.o_where = c.take(sizeof(int2) * size_t(n));
   L.o_off = c.take(sizeof(int64_t) * size_t(L.nbox + 1));
   L.o_bsum = c.take(sizeof(int64_t) * (size_t(ceil_div(L.nbox + 1, SCAN_CHUNK)) + 1));
   L.o_ord = c.take(sizeof(int32_t) * size_t(n));
@@ -835,15 +822,16 @@ int fi_collect(const float2* Y, int64_t n, const FiParams* par, const double2* C
 
 // The convolution: G to the potentials' planes 0 and 1 of Cg.  The grids
 // cover the largest transform; the kernels stop at the sizes in par.
+template <int T>
 int fi_convolve(const unsigned long long* G, const FiParams* par, int p, const double2* tw, double2* Cg,
                 int64_t plane, int max_fft, hipStream_t s) {
-  auto blocks = [](int64_t b) { return dim3(unsigned(b < 1024 ? b : 1024)); };
-  const int64_t rows = ceil_div(int64_t(max_fft) * (max_fft / 2), FI_PTS);  // groups of rows of a plane
-  hipLaunchKernelGGL(fi_rows_fwd_kernel, blocks(3 * rows), dim3(256), 0, s, G, par, p, tw, Cg, plane);
+  auto blocks = [](int64_t b) { return dim3(unsigned(b < 2048 ? b : 2048)); };
+  const int64_t rows = ceil_div(int64_t(max_fft) * (max_fft / 2), 8 * T);  // groups of rows of a plane
+  hipLaunchKernelGGL(fi_rows_fwd_kernel<T>, blocks(3 * rows), dim3(T), 0, s, G, par, p, tw, Cg, plane);
   TSNE_CHECK_LAUNCH();
-  hipLaunchKernelGGL(fi_cols_kernel, blocks(2 * rows), dim3(256), 0, s, par, tw, Cg, plane);
+  hipLaunchKernelGGL(fi_cols_kernel<T>, blocks(2 * rows), dim3(T), 0, s, par, tw, Cg, plane);
   TSNE_CHECK_LAUNCH();
-  hipLaunchKernelGGL(fi_rows_inv_kernel, blocks(2 * rows), dim3(256), 0, s, par, tw, Cg, plane);
+  hipLaunchKernelGGL(fi_rows_inv_kernel<T>, blocks(2 * rows), dim3(T), 0, s, par, tw, Cg, plane);
   TSNE_CHECK_LAUNCH();
   return TSNE_OK;
 }
@@ -879,7 +867,7 @@ extern "C" int tsne_kl_grad_fft(const float* Y, int64_t n, const int64_t* row_pt
   double* Zb = reinterpret_cast<double*>(ws + L.o_Zb);
   double* klp = reinterpret_cast<double*>(ws + L.o_kl);
   int* cnt = reinterpret_cast<int*>(ws + L.o_cnt);
-  int* cur = cnt + L.nbox;
+  int2* where = reinterpret_cast<int2*>(ws + L.o_where);
   int64_t* off = reinterpret_cast<int64_t*>(ws + L.o_off);
   int64_t* bsum = reinterpret_cast<int64_t*>(ws + L.o_bsum);
   int32_t* order = reinterpret_cast<int32_t*>(ws + L.o_ord);
@@ -893,12 +881,11 @@ extern "C" int tsne_kl_grad_fft(const float* Y, int64_t n, const int64_t* row_pt
                      max_box_width, max_fft, par, tw, nheavy);
   TSNE_CHECK_LAUNCH();
   // counting sort of the points by box, then the per-box node sums
-  if ((rc = launch_fill<int>(cnt, 2 * L.nbox, 0, s))) return rc;
-  const dim3 pgrid(unsigned(ceil_div(n, 256) < FI_CBLOCKS ? ceil_div(n, 256) : FI_CBLOCKS));
-  hipLaunchKernelGGL(fi_count_kernel, pgrid, dim3(256), 0, s, Y2, n, par, cnt);
+  if ((rc = launch_fill<int>(cnt, L.nbox, 0, s))) return rc;
+  hipLaunchKernelGGL(fi_count_kernel, dim3(unsigned(ceil_div(n, FI_CPTS))), dim3(256), 0, s, Y2, n, par, cnt, where);
   TSNE_CHECK_LAUNCH();
   if ((rc = exclusive_scan<int>(cnt, L.nbox, off, bsum, s))) return rc;
-  hipLaunchKernelGGL(fi_scatter_kernel, pgrid, dim3(256), 0, s, Y2, n, par, off, cur, order);
+  hipLaunchKernelGGL(fi_scatter_kernel, dim3(unsigned(ceil_div(n, 256))), dim3(256), 0, s, n, where, off, order);
   TSNE_CHECK_LAUNCH();
   switch (n_interp) {
     case 2: rc = fi_spread<2>(Y2, n, par, off, order, L.nbox, nheavy, heavy, G, s); break;
@@ -907,7 +894,9 @@ extern "C" int tsne_kl_grad_fft(const float* Y, int64_t n, const int64_t* row_pt
     default: rc = fi_spread<5>(Y2, n, par, off, order, L.nbox, nheavy, heavy, G, s);
   }
   if (rc) return rc;
-  if ((rc = fi_convolve(G, par, n_interp, tw, Cg, L.plane, max_fft, s))) return rc;
+  rc = max_fft <= 2048 ? fi_convolve<256>(G, par, n_interp, tw, Cg, L.plane, max_fft, s)
+                       : fi_convolve<512>(G, par, n_interp, tw, Cg, L.plane, max_fft, s);
+  if (rc) return rc;
   switch (n_interp) {
     case 2: rc = fi_collect<2>(Y2, n, par, Cg, L.plane, R, Zb, s); break;
     case 3: rc = fi_collect<3>(Y2, n, par, Cg, L.plane, R, Zb, s); break;

@@ -274,6 +274,167 @@ __global__ __launch_bounds__(256) void finalize_tsne_kernel(
   }
 }
 
+// The CSR attraction of finalize_tsne_kernel for rows taken in a spatial
+// order (rows[64 c .. 64 c + 63], one block), with one repulsion vector R_i
+// per row: g_i = 4 (alpha A_i - R_i / Z), the same bits as the kernel above.
+//
+// What bounds the gather of y_j: a wave's 64 random 8-byte reads are 64 lines
+// of 128 bytes from L2, and at 10^6 points (149 M entries, 126 M lines, 85 %
+// of them in L2) that kernel ran at 17 TB/s of line traffic, 0.95 ms.  But
+// the rows of a block are neighbours, so their ~9,500 entries name only some
+// hundreds of points.  The block therefore reads each of those once, into a
+// direct-mapped table in LDS: every entry writes its column to its slot's
+// tag, the owners of the slots fetch the points that won, and an entry reads
+// its point from LDS, or from memory when another column took its slot.  (A
+// graph without locality loses nothing but the table's passes: every slot's
+// point was needed by some entry.)  16 lanes take a row, lane l its entries
+// l, l + 16, ... in order, FLT_EPT at a time.  A row of more than FLT_LONG
+// entries is taken by the whole block, its terms going through LDS.
+// Measured at 10^6 points, 149 M entries: 0.95 -> 0.655 ms (half the lines
+// from L2; the stream of entries alone, whole rows in a random order, takes
+// about 0.5 ms); 70,001 points 68 -> 48 us.  Blocks of 32 rows with half
+// the table were 2 % slower, of 16 rows 10 %.
+constexpr int FLT_ROWS = 64;
+constexpr int FLT_T = 16 * FLT_ROWS;  // threads
+constexpr int FLT_EPT = 10;  // entries of a lane per pass
+constexpr int FLT_LOG = 12;
+constexpr int FLT_SLOTS = 1 << FLT_LOG;  // points of the table
+constexpr int FLT_LONG = 1024;
+
+__global__ __launch_bounds__(FLT_T, 8) void finalize_local_kernel(
+    const float2* __restrict__ Y, int64_t n, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
+    const float* __restrict__ val, float alpha, const float2* __restrict__ R, const double* __restrict__ Zblock,
+    int64_t nZ, float2* __restrict__ grad, double* __restrict__ Z_out, unsigned long long* __restrict__ nonfinite,
+    const int32_t* __restrict__ rows) {
+#pragma clang fp contract(off)
+  __shared__ int32_t tag[FLT_SLOTS];
+  __shared__ float2 pt[FLT_SLOTS];
+  __shared__ double red[4];
+  __shared__ int maxlen;
+  const int tid = threadIdx.x, g = tid >> 4, sl = tid & 15;
+  const uint32_t n32 = uint32_t(n);  // n <= 2^31
+  const int64_t p = xcd_block() * FLT_ROWS + g;
+  const int64_t row = p < n ? int64_t(rows[p]) : n;
+  int64_t a = 0;
+  int len = 0;
+  float2 yi = make_float2(0.0f, 0.0f), Ri = yi;
+  if (row < n) {
+    a = row_ptr[row];
+    len = int(row_ptr[row + 1] - a);
+    yi = Y[row];
+    Ri = R[row];
+  }
+  if (tid == 0) maxlen = 0;
+  for (int q = tid; q < FLT_SLOTS; q += FLT_T) tag[q] = -1;
+  const double zt = tid < 256 ? zblock_thread_sum(Zblock, nZ) : 0.0;
+  __syncthreads();
+  if (sl == 0) atomicMax(&maxlen, len);
+  // Z as finalize_tsne_kernel sums it: 256 threads, four wave sums in order
+  const double zw = wave_sum_d(zt);
+  if (tid < 256 && lane_id() == 0) red[tid >> 6] = zw;
+  __syncthreads();
+  const double Z = (red[0] + red[1]) + (red[2] + red[3]);
+  if (blockIdx.x == 0 && tid == 0 && Z_out) *Z_out = Z;
+  const bool lng = maxlen > FLT_LONG;  // (the same in every thread)
+  const int top = lng ? FLT_LONG : maxlen;
+  const int own = len <= FLT_LONG ? len : 0;
+  const int32_t* cp = col + a;
+  const float* vp = val + a;
+  float ax = 0.0f, ay = 0.0f;
+  int32_t seen[FLT_SLOTS / FLT_T];  // the tags this thread's slots were last filled for
+#pragma unroll
+  for (int q = 0; q < FLT_SLOTS / FLT_T; ++q) seen[q] = -1;
+  auto slot_of = [](int32_t j) { return int((uint32_t(j) * 2654435761u) >> (32 - FLT_LOG)); };
+  for (int m0 = 0; m0 < top; m0 += 16 * FLT_EPT) {
+    const bool some = m0 + sl < own;
+    int32_t jj[FLT_EPT];
+    float pp[FLT_EPT];
+    if (some) {
+#pragma unroll
+      for (int u = 0; u < FLT_EPT; ++u) {
+        const int e = m0 + sl + 16 * u < own ? m0 + sl + 16 * u : m0 + sl;
+        // (not non-temporal: two loads share a line of 128 bytes)
+        jj[u] = cp[e];
+        pp[u] = vp[e];
+      }
+#pragma unroll
+      for (int u = 0; u < FLT_EPT; ++u) {
+        if (uint32_t(jj[u]) >= n32) {
+          jj[u] = 0;
+          pp[u] = 0.0f;
+        }
+        tag[slot_of(jj[u])] = jj[u];  // some entry of the slot wins
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < FLT_SLOTS / FLT_T; ++q) {
+      const int32_t t = tag[tid + FLT_T * q];
+      if (t != seen[q]) {
+        pt[tid + FLT_T * q] = Y[t];
+        seen[q] = t;
+      }
+    }
+    __syncthreads();
+    if (some) {
+#pragma unroll
+      for (int u = 0; u < FLT_EPT; ++u) {
+        const int sj = slot_of(jj[u]);
+        const float2 yj = tag[sj] == jj[u] ? pt[sj] : Y[jj[u]];
+        const float dx = yi.x - yj.x, dy = yi.y - yj.y;
+        const float q = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, 1.0f));
+        const float pw = pp[u] * __builtin_amdgcn_rcpf(q);
+        if (m0 + sl + 16 * u < own) {
+          ax += pw * dx;
+          ay += pw * dy;
+        }
+      }
+    }
+    __syncthreads();  // the tags are rewritten by the next pass
+  }
+  if (lng) {
+    for (int gg = 0; gg < FLT_ROWS; ++gg) {
+      const int64_t pg = xcd_block() * FLT_ROWS + gg;
+      if (pg >= n) break;
+      const int64_t rg = rows[pg], ag = row_ptr[rg], lg = row_ptr[rg + 1] - ag;
+      if (lg <= FLT_LONG) continue;
+      const float2 yg = Y[rg];
+      for (int64_t c0 = 0; c0 < lg; c0 += FLT_SLOTS) {
+        for (int64_t e = c0 + tid; e < lg && e < c0 + FLT_SLOTS; e += FLT_T) {
+          int32_t j = col[ag + e];
+          float pv = val[ag + e];
+          if (j < 0 || j >= n) {
+            j = 0;
+            pv = 0.0f;
+          }
+          const float2 yj = Y[j];
+          const float dx = yg.x - yj.x, dy = yg.y - yj.y;
+          const float q = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, 1.0f));
+          const float pw = pv * __builtin_amdgcn_rcpf(q);
+          pt[e - c0] = make_float2(pw * dx, pw * dy);
+        }
+        __syncthreads();
+        if (g == gg)
+          for (int64_t e = c0 + sl; e < lg && e < c0 + FLT_SLOTS; e += 16) {
+            ax += pt[e - c0].x;
+            ay += pt[e - c0].y;
+          }
+        __syncthreads();
+      }
+    }
+  }
+  ax = row16_sum(ax);
+  ay = row16_sum(ay);
+  if (sl == 0 && row < n)
+    grad[row] = make_float2(float(4.0 * (double(alpha) * double(ax) - double(Ri.x) / Z)),
+                            float(4.0 * (double(alpha) * double(ay) - double(Ri.y) / Z)));
+  if (nonfinite) {
+    const bool mine = sl == 0;
+    const int bad = __popcll(__ballot(mine && !isfinite(yi.x))) + __popcll(__ballot(mine && !isfinite(yi.y)));
+    if (lane_id() == 0 && bad) atomicAdd(nonfinite, static_cast<unsigned long long>(bad));
+  }
+}
+
 // KL = sum p ln p + sum p ln q + S ln Z  (ln w = -ln q).
 __global__ __launch_bounds__(256) void kl_reduce_kernel(const double* __restrict__ klpart, int64_t nb,
                                                         const double* __restrict__ Zblock, int64_t nZ,
@@ -300,6 +461,14 @@ int finalize_csr_launch(const float* Y, int64_t n, const int64_t* row_ptr, const
                         const int32_t* rows) {
   const int64_t nfin = ceil_div(n, FIN_ROWS);
   double* kp = kl ? klpart : nullptr;
+  if (rows && !kl) {
+    hipLaunchKernelGGL(finalize_local_kernel, dim3(unsigned(ceil_div(n, FLT_ROWS))), dim3(FLT_T), 0, s,
+                       reinterpret_cast<const float2*>(Y), n, row_ptr, col, val, alpha,
+                       reinterpret_cast<const float2*>(R), Zblock, nZ, reinterpret_cast<float2*>(grad), Z, nonfinite,
+                       rows);
+    TSNE_CHECK_LAUNCH();
+    return TSNE_OK;
+  }
   hipLaunchKernelGGL((finalize_tsne_kernel<false, false>), dim3(unsigned(nfin)), dim3(256), 0, s,
                      reinterpret_cast<const float2*>(Y), n, row_ptr, col, val, alpha,
                      reinterpret_cast<const float2*>(R), static_cast<const float*>(nullptr),

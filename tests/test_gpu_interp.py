@@ -199,3 +199,41 @@ def test_fft_grad_box_occupancies(dev, p):
     go, Zo, klo = I.kl_grad(Y, So, 1.0, p=p, **kw)
     assert rel(g, go) <= GRAD_RTOL, rel(g, go)
     assert abs(Z - Zo) <= 1e-9 * Zo
+
+
+def test_fft_grad_long_rows(dev):
+    """The attraction of the box order takes rows in passes of 160 entries and
+    rows of more than 1,024 by the whole block: row lengths around those
+    edges, empty rows and columns outside [0, n) (which contribute nothing),
+    in a last block that is not full.  Against the index order, bit for bit,
+    and against FP64 sums (an FP32 sum of m terms is within m 2^-24 of the
+    terms' absolute sum; the longest row has 7,000)."""
+    say("fft grad long rows")
+    rng = np.random.default_rng(41)
+    n = 8005
+    lens = rng.integers(0, 40, n)
+    lens[[3, 70, 71, 500, 501, 4000, 4001, 8000, 8004]] = [159, 160, 161, 320, 1023, 1024, 1025, 4097, 7000]
+    row_ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    col = np.concatenate([np.sort(rng.choice(n, m, replace=False)) for m in lens]).astype(np.int32)
+    val = rng.uniform(0.5, 1.5, col.size).astype(np.float32) / np.float32(col.size)
+    bad = rng.choice(col.size, 50, replace=False)
+    good = np.ones(col.size, bool)
+    good[bad] = False
+    bcol = col.copy()
+    bcol[bad] = rng.choice([-1, n, n + 5, 2**31 - 1], 50)
+    P = api.SparseP(to_dev(row_ptr, dev), to_dev(bcol, dev), to_dev(val, dev), None, n)
+    Y = synth.random_embedding(n, 8.0, 4200)
+    Yd = to_dev(Y, dev)
+    a, Za, _ = api.kl_grad_fft(Yd, P, 1.0, want_Z=True)
+    b, Zb, _ = api.kl_grad_fft(Yd, P, 1.0, want_Z=True, want_kl=True)
+    assert torch.equal(a, b) and torch.equal(Za, Zb)
+    Ro, Zo = I.repulsion(Y)
+    rows = np.repeat(np.arange(n), lens)[good]
+    d = Y[rows].astype(np.float64) - Y[col[good]].astype(np.float64)
+    t = (val[good] / (1.0 + (d * d).sum(1)))[:, None] * d
+    A, absA = np.zeros((n, 2)), np.zeros((n, 2))
+    np.add.at(A, rows, t)
+    np.add.at(absA, rows, np.abs(t))
+    tol = 4.0 * (lens[:, None] * 2.0**-24 + 1e-6) * absA + 1e-6 * np.abs(4.0 * Ro / Zo) + 1e-12
+    err = np.abs(a.cpu().numpy() - 4.0 * (A - Ro / Zo))
+    assert (err <= tol).all(), (err / tol).max()
