@@ -117,21 +117,22 @@ __device__ __forceinline__ float row16_min(float v) {
 // and a select (M = 4), a DPP row rotation (M = 8), and gfx950's
 // v_permlane16_swap / v_permlane32_swap (M = 16, 32: with both operands v,
 // the first result holds the lower row / half in both places, the second
-// the upper one).
+// the upper one).  bound_ctrl is set: every lane that is used has a source,
+// and the compiler need not clear the destination first.
 template <int M>
 __device__ __forceinline__ uint32_t xor_lane(uint32_t v) {
   static_assert(M == 1 || M == 2 || M == 4 || M == 8 || M == 16 || M == 32, "power of two below 64");
   const int x = int(v);
   if constexpr (M == 1) {
-    return uint32_t(__builtin_amdgcn_update_dpp(0, x, 0xB1, 0xf, 0xf, false));  // quad_perm [1, 0, 3, 2]
+    return uint32_t(__builtin_amdgcn_update_dpp(0, x, 0xB1, 0xf, 0xf, true));  // quad_perm [1, 0, 3, 2]
   } else if constexpr (M == 2) {
-    return uint32_t(__builtin_amdgcn_update_dpp(0, x, 0x4E, 0xf, 0xf, false));  // quad_perm [2, 3, 0, 1]
+    return uint32_t(__builtin_amdgcn_update_dpp(0, x, 0x4E, 0xf, 0xf, true));  // quad_perm [2, 3, 0, 1]
   } else if constexpr (M == 4) {
-    const int up = __builtin_amdgcn_update_dpp(0, x, 0x104, 0xf, 0xf, false);  // row_shl:4, lane i <- i + 4
-    const int dn = __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4, lane i <- i - 4
+    const int up = __builtin_amdgcn_update_dpp(0, x, 0x104, 0xf, 0xf, true);  // row_shl:4, lane i <- i + 4
+    const int dn = __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);  // row_shr:4, lane i <- i - 4
     return uint32_t((lane_id() & 4) ? dn : up);
   } else if constexpr (M == 8) {
-    return uint32_t(__builtin_amdgcn_update_dpp(0, x, 0x128, 0xf, 0xf, false));  // row_ror:8
+    return uint32_t(__builtin_amdgcn_update_dpp(0, x, 0x128, 0xf, 0xf, true));  // row_ror:8
   } else if constexpr (M == 16) {
     const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
     return (lane_id() & 16) ? r[0] : r[1];

@@ -8,35 +8,42 @@
 //   components V = Z U diag(1/s),  scores = Q U diag(s).
 // The two products with X -- Xc W (n x 64) and Xc^T Q (g x 64) -- run on the
 // FP32 matrix cores (v_mfma_f32_16x16x4_f32), X centred on the fly as it is
-// staged in LDS (no cancellation against the mean).  orth() is CholeskyQR2
-// (Gram matrix in FP64, Cholesky + triangular inverse in one FP64 block,
-// the first pass shifted), the 64 x 64 symmetric eigenproblem a cyclic
-// Jacobi method in FP64 (tournament ordering, 32 disjoint rotations per
+// staged in LDS (no cancellation against the mean).  orth() is a CholeskyQR
+// pass, two for the last Q (Gram matrix in FP64, Cholesky + triangular
+// inverse in one FP64 block, the first pass shifted), the 64 x 64 symmetric
+// eigenproblem a one-sided Jacobi method in FP64 (32 disjoint rotations per
 // step).  Sums over rows are per-chunk partials added in a fixed order:
 // the result is bitwise reproducible.
 #include <math.h>
+
+#include <type_traits>
 
 #include "common.hpp"
 
 namespace tsne {
 
 constexpr int PCA_L = 64;       // subspace width = one 64-column MFMA tile row
-constexpr int PCA_RC = 2048;    // rows per partial of the column sums and X^T Q
-constexpr int PCA_GRC = 512;    // rows per partial of a Gram matrix (the least, where m allows)
-constexpr int PCA_GMAX = 1024;  // partials of a Gram matrix (at most)
+constexpr int PCA_RC = 2048;    // rows per partial of the column sums and X^T Q, at most
+constexpr int PCA_RMIN = 64;    // ... and at least
+constexpr int PCA_BM = 128;     // rows of a block of the product with W
+// columns of X staged at a time there (32: four blocks per CU; 64, two blocks,
+// took 590 instead of 525 us at 200,000 x 2,000)
+constexpr int PCA_KC = 32;
+constexpr int PCA_GRC = 64;     // rows per partial of a Gram matrix (the least, where m allows)
+constexpr int PCA_GMAX = 768;   // partials of a Gram matrix (at most: three blocks on each of 256 CUs)
 
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 
 // --- column means ---------------------------------------------------------
 
-// part[r][j] = sum of X[i][j] over the rows i of chunk r = blockIdx.y (FP64,
-// eight independent partial sums per thread, added in a fixed order).
-__global__ __launch_bounds__(256) void pca_colsum_kernel(const float* __restrict__ X, int64_t n, int g,
+// part[r][j] = sum of X[i][j] over the rc rows i of chunk r = blockIdx.y
+// (FP64, eight independent partial sums per thread, added in a fixed order).
+__global__ __launch_bounds__(256) void pca_colsum_kernel(const float* __restrict__ X, int64_t n, int g, int rc,
                                                          double* __restrict__ part) {
   const int j = blockIdx.x * 256 + threadIdx.x;
   if (j >= g) return;
-  const int64_t r0 = int64_t(blockIdx.y) * PCA_RC;
-  const int64_t r1 = r0 + PCA_RC < n ? r0 + PCA_RC : n;
+  const int64_t r0 = int64_t(blockIdx.y) * rc;
+  const int64_t r1 = r0 + rc < n ? r0 + rc : n;
   double s[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   int64_t i = r0;
   for (; i + 8 <= r1; i += 8)
@@ -46,19 +53,34 @@ __global__ __launch_bounds__(256) void pca_colsum_kernel(const float* __restrict
   part[int64_t(blockIdx.y) * g + j] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
 }
 
-__global__ __launch_bounds__(256) void pca_colmean_kernel(const double* __restrict__ part, int64_t nchunk, int g,
-                                                          int64_t n, float* __restrict__ mean) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= g) return;
+// The chunks' sums of 64 columns per block, wave w of 16 a sixteenth of the
+// chunks, the waves' sums added in order.
+__global__ __launch_bounds__(1024) void pca_colmean_kernel(const double* __restrict__ part, int64_t nchunk, int g,
+                                                           int64_t n, float* __restrict__ mean) {
+  __shared__ double sum[16][64];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int j = blockIdx.x * 64 + lane;
+  const int64_t per = (nchunk + 15) / 16;
+  const int64_t r0 = w * per, r1 = r0 + per < nchunk ? r0 + per : nchunk;
   double s = 0.0;
-  for (int64_t r = 0; r < nchunk; ++r) s += part[r * g + j];
-  mean[j] = float(s / double(n));
+  if (j < g)
+    for (int64_t r = r0; r < r1; ++r) s += part[r * g + j];
+  sum[w][lane] = s;
+  __syncthreads();
+  if (w == 0 && j < g) {
+    double t = 0.0;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) t += sum[u][lane];
+    mean[j] = float(t / double(n));
+  }
 }
 
 // --- C = (A - 1 mu^T) W  (M x K times K x 64; the first ncols columns stored) --
 
-// Block: 128 rows of A, 4 waves x 32 rows; K in chunks of 64 staged in LDS,
-// the next chunk loaded into registers while the current one is used (VEC:
+// Block: 128 rows of A, 4 waves x 32 rows; the columns [kper y, kper (y + 1))
+// of A for blockIdx.y = y, whose product goes to C + y M ldc (with more than
+// one y: partials, added by pca_reduce_kernel), in chunks of PCA_KC staged in
+// LDS, the next chunk loaded into registers while the current one is used (VEC:
 // 16-byte loads, K a multiple of 4).  The loads are unconditional, their
 // addresses clamped into the matrices, so that none waits inside a branch:
 // rows past M and columns past K are zeroed, and the mean subtracted, when
@@ -66,21 +88,24 @@ __global__ __launch_bounds__(256) void pca_colmean_kernel(const double* __restri
 // A[l % 16][l / 16] and W[l / 16][l % 16]; the result tile
 // D[4 (l / 16) + r][l % 16] in register r.
 template <bool CENTER, bool VEC>
-__global__ __launch_bounds__(256) void pca_gemm_tall_kernel(const float* __restrict__ A, int64_t M, int K,
+__global__ __launch_bounds__(256, 4) void pca_gemm_tall_kernel(const float* __restrict__ A, int64_t M, int K,
                                                             const float* __restrict__ mu,
                                                             const float* __restrict__ W, float* __restrict__ C,
-                                                            int ldc, int ncols) {
-  constexpr int BM = 128, KC = 64, SA = KC + 4, SW = PCA_L + 16;
+                                                            int ldc, int ncols, int kper) {
+  constexpr int BM = PCA_BM, KC = PCA_KC, SA = KC + 4, SW = PCA_L + 16;
   constexpr int AE = VEC ? (BM * KC) / (4 * 256) : (BM * KC) / 256;  // loads per thread
-  constexpr int RSTEP = VEC ? 16 : 4;                                // rows between a thread's loads
+  constexpr int CT = VEC ? KC / 4 : KC;                              // threads across a row of the chunk
+  constexpr int RSTEP = 256 / CT;                                    // rows between a thread's loads
+  constexpr int WE = KC / 16;
   __shared__ __attribute__((aligned(16))) float As[BM * SA];
   __shared__ __attribute__((aligned(16))) float Ws[KC * SW];
   const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
   const int li = lane & 15, lk = lane >> 4;
   const int64_t m0 = int64_t(blockIdx.x) * BM;
   // this thread's A column offset within a chunk and first row within the block
-  const int ac = VEC ? 4 * (tid & 15) : (tid & 63);
-  const int ar = VEC ? (tid >> 4) : (tid >> 6);
+  const int ac = (VEC ? 4 : 1) * (tid % CT);
+  const int ar = tid / CT;
+  const int kb = int(blockIdx.y) * kper, ke = kb + kper < K ? kb + kper : K;
   floatx4_t acc[2][4];
 #pragma unroll
   for (int a = 0; a < 2; ++a)
@@ -89,9 +114,9 @@ __global__ __launch_bounds__(256) void pca_gemm_tall_kernel(const float* __restr
   float4 ra[VEC ? AE : 1];
   float rs[VEC ? 1 : AE];
   float4 rm = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  float4 rw[4];
+  float4 rw[WE];
   auto load = [&](int k0) {
-    const int c = k0 + ac < K ? k0 + ac : 0;
+    const int c = k0 + ac < ke ? k0 + ac : kb;
 #pragma unroll
     for (int e = 0; e < AE; ++e) {
       const int64_t row = m0 + ar + RSTEP * e;
@@ -104,14 +129,14 @@ __global__ __launch_bounds__(256) void pca_gemm_tall_kernel(const float* __restr
       else rm.x = mu[c];
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < WE; ++e) {
       const int r = k0 + (tid >> 4) + 16 * e;
-      rw[e] = *reinterpret_cast<const float4*>(W + int64_t(r < K ? r : K - 1) * PCA_L + 4 * (tid & 15));
+      rw[e] = *reinterpret_cast<const float4*>(W + int64_t(r < ke ? r : ke - 1) * PCA_L + 4 * (tid & 15));
     }
   };
-  load(0);
-  for (int k0 = 0; k0 < K; k0 += KC) {
-    const bool cok = k0 + ac < K;
+  load(kb);
+  for (int k0 = kb; k0 < ke; k0 += KC) {
+    const bool cok = k0 + ac < ke;
 #pragma unroll
     for (int e = 0; e < AE; ++e) {
       const bool ok = cok && m0 + ar + RSTEP * e < M;
@@ -131,13 +156,13 @@ __global__ __launch_bounds__(256) void pca_gemm_tall_kernel(const float* __restr
       }
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < WE; ++e) {
       const int r = (tid >> 4) + 16 * e;
       *reinterpret_cast<float4*>(Ws + r * SW + 4 * (tid & 15)) =
-          k0 + r < K ? rw[e] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+          k0 + r < ke ? rw[e] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     }
     __syncthreads();
-    if (k0 + KC < K) load(k0 + KC);  // in flight during the products below
+    if (k0 + KC < ke) load(k0 + KC);  // in flight during the products below
 #pragma unroll
     for (int kk = 0; kk < KC; kk += 4) {
       float av[2], bv[4];
@@ -160,14 +185,14 @@ __global__ __launch_bounds__(256) void pca_gemm_tall_kernel(const float* __restr
       for (int r = 0; r < 4; ++r) {
         const int64_t row = m0 + w * 32 + 16 * a + 4 * lk + r;
         const int col = 16 * b + li;
-        if (row < M && col < ncols) C[row * ldc + col] = acc[a][b][r];
+        if (row < M && col < ncols) C[(int64_t(blockIdx.y) * M + row) * ldc + col] = acc[a][b][r];
       }
 }
 
 // --- part[r] = (A - 1 mu^T)^T Bm over the rows of chunk r  (K x 64 each) -----
 
 // Block (256 columns of A from c0 = 256 blockIdx.x, row chunk r = blockIdx.y
-// of PCA_RC rows); wave w owns columns c0 + 64 w .. + 63 (4 tiles of 16)
+// of rc rows); wave w owns columns c0 + 64 w .. + 63 (4 tiles of 16)
 // against all 64 columns of Bm (4 tiles); rows staged 32 at a time, the
 // next stage loaded into registers while the current one is used.  As in
 // the tall product, the loads are unconditional (clamped addresses) and the
@@ -175,7 +200,8 @@ __global__ __launch_bounds__(256) void pca_gemm_tall_kernel(const float* __restr
 template <bool CENTER, bool VEC>
 __global__ __launch_bounds__(256) void pca_gemm_red_kernel(const float* __restrict__ A, int64_t M, int K,
                                                            const float* __restrict__ mu,
-                                                           const float* __restrict__ Bm, float* __restrict__ part) {
+                                                           const float* __restrict__ Bm, int rc,
+                                                           float* __restrict__ part) {
   constexpr int MS = 32, NB = 256, SA = NB + 16, SB = PCA_L + 16;
   constexpr int AE = VEC ? (MS * NB) / (4 * 256) : (MS * NB) / 256;
   constexpr int RSTEP = VEC ? 4 : 1;  // rows between a thread's loads
@@ -184,8 +210,8 @@ __global__ __launch_bounds__(256) void pca_gemm_red_kernel(const float* __restri
   const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
   const int li = lane & 15, lk = lane >> 4;
   const int c0 = blockIdx.x * NB;
-  const int64_t r0 = int64_t(blockIdx.y) * PCA_RC;
-  const int64_t r1 = r0 + PCA_RC < M ? r0 + PCA_RC : M;
+  const int64_t r0 = int64_t(blockIdx.y) * rc;
+  const int64_t r1 = r0 + rc < M ? r0 + rc : M;
   // this thread's column of A (fixed for the block) and first row of a stage
   const int ac = VEC ? 4 * (tid & 63) : tid;
   const int ar = VEC ? (tid >> 6) : 0;
@@ -272,13 +298,20 @@ __global__ __launch_bounds__(256) void pca_gemm_red_kernel(const float* __restri
       }
 }
 
-// out[i][c] = sum over chunks r (in order) of part[r][i][c], as float.
+// out[t] = sum over chunks r (in order) of part[r][t], as float; sixteen
+// chunks' loads in flight.
 __global__ __launch_bounds__(256) void pca_reduce_kernel(const float* __restrict__ part, int64_t nchunk,
                                                          int64_t count, float* __restrict__ out) {
   const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
   if (t >= count) return;
   double s = 0.0;
-  for (int64_t r = 0; r < nchunk; ++r) s += double(part[r * count + t]);
+  for (int64_t r = 0; r < nchunk; r += 16) {
+    float v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = part[(r + u < nchunk ? r + u : nchunk - 1) * count + t];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) s += r + u < nchunk ? double(v[u]) : 0.0;
+  }
   out[t] = float(s);
 }
 
@@ -358,195 +391,249 @@ __global__ __launch_bounds__(256) void pca_gram_kernel(const float* __restrict__
   for (int e = tid; e < PCA_L * PCA_L; e += 256) out[e] = sum[e];
 }
 
-// G[e] = sum over the nchunk partials (eight running sums, added in a fixed
-// order), e < 64 x 64; 64 threads per block.
-__global__ __launch_bounds__(64) void pca_gram_reduce_kernel(const double* __restrict__ part, int64_t nchunk,
-                                                             double* __restrict__ G) {
-  const int e = blockIdx.x * 64 + threadIdx.x;
-  double s[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  int64_t r = 0;
-  for (; r + 8 <= nchunk; r += 8)
+// G[e] = sum over the nchunk partials, e < 64 x 64: block b takes the entries
+// 64 b .., wave w of its 16 a sixteenth of the partials (eight loads in
+// flight), the waves' sums are added in order.
+__global__ __launch_bounds__(1024) void pca_gram_reduce_kernel(const double* __restrict__ part, int64_t nchunk,
+                                                               double* __restrict__ G) {
+  __shared__ double sum[16][64];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int e = blockIdx.x * 64 + lane;
+  const int64_t per = (nchunk + 15) / 16;
+  const int64_t r0 = w * per, r1 = r0 + per < nchunk ? r0 + per : nchunk;
+  double s = 0.0;
+  for (int64_t r = r0; r < r1; r += 8) {
+    double v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) s[u] += part[(r + u) * PCA_L * PCA_L + e];
-  for (; r < nchunk; ++r) s[0] += part[r * PCA_L * PCA_L + e];
-  G[e] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+    for (int u = 0; u < 8; ++u) v[u] = part[(r + u < r1 ? r + u : r1 - 1) * PCA_L * PCA_L + e];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += r + u < r1 ? v[u] : 0.0;
+  }
+  sum[w][lane] = s;
+  __syncthreads();
+  if (w == 0) {
+    double t = 0.0;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) t += sum[u][lane];
+    G[e] = t;
+  }
+}
+
+// 1 / sqrt(x) for x > 0 in FP64: the hardware's estimate and two Newton steps
+// (a third of the dependent operations of 1.0 / sqrt(x)).
+__device__ __forceinline__ double rsqrt_d(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  y = y * (1.5 - 0.5 * x * y * y);
+  return y * (1.5 - 0.5 * x * y * y);
+}
+
+__device__ __forceinline__ double readlane_d(double v, int src) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane(uint32_t(b), src);
+  const uint32_t hi = __builtin_amdgcn_readlane(uint32_t(b >> 32), src);
+  return __builtin_bit_cast(double, (uint64_t(hi) << 32) | lo);
 }
 
 // --- Cholesky G = R^T R (upper R) and R^-1, one block, FP64 ------------------
 
 // shift > 0 adds shift * trace / 64 to the diagonal (the first, shifted pass
-// of CholeskyQR2).  Right-looking: per column j the pivot, row j of R, then
-// the trailing update of the upper triangle.  Thread t owns the entries
-// (t / 64 + 4 u, t % 64), u < 16, of every update; it loads all of them
-// before it stores any, so one LDS round trip serves a whole step.  The
-// inverse comes from the same pass: the row operations that take G to R
-// (row i minus R[j][i] times the scaled row j, row j divided by R[j][j])
-// form the matrix E with E G = R, i.e. E = R^-T; applied to X = I alongside,
-// they leave X = R^-T (lower triangular).  Rinv = X^T (float, 64 x 64
-// row-major) is the W of the next product Q = Y Rinv.
-__global__ __launch_bounds__(256) void pca_cholinv_kernel(const double* __restrict__ Gin, double shift,
+// of CholeskyQR2).  Right-looking, one row of R per step.  The inverse comes
+// from the same pass: the row operations that take G to R (row i minus
+// R[j][i] times the scaled row j, row j divided by R[j][j]) form the matrix E
+// with E G = R, i.e. E = R^-T; applied to X = I alongside, they leave X =
+// R^-T (lower triangular).  Rinv = X^T (float, 64 x 64 row-major) is the W of
+// the next product Q = Y Rinv.
+// What bounds it: a chain of 64 pivots.  Lane c holds column c of A and X in
+// registers, wave w the rows 16 u + 4 w .. + 3 (u < 4).  A step takes the four
+// rows of one wave: its pivots one after another, their effect on the four
+// rows by lane reads, then one LDS write, one barrier, and the update of the
+// rows below from the four rows' broadcast.  With both matrices in LDS and
+// one row per step a launch took 87 us (48 LDS reads, a root and two divisions
+// per step); one row per step in registers 39; now 24.  Entries of A left of
+// the current columns are not kept and reach no result.
+__global__ __launch_bounds__(256, 1) void pca_cholinv_kernel(const double* __restrict__ Gin, double shift,
                                                           float* __restrict__ Rinv) {
-  constexpr int NU = PCA_L * PCA_L / 256;
-  __shared__ double A[PCA_L][PCA_L + 1];
-  __shared__ double X[PCA_L][PCA_L + 1];
-  __shared__ double red[4];
-  const int tid = threadIdx.x, r0 = tid >> 6, c = tid & 63;
-  for (int e = tid; e < PCA_L * PCA_L; e += 256) {
-    A[e / PCA_L][e % PCA_L] = Gin[e];
-    X[e / PCA_L][e % PCA_L] = (e / PCA_L == e % PCA_L) ? 1.0 : 0.0;
-  }
-  __syncthreads();
-  if (shift > 0.0) {
-    const double tr = block_sum_d(tid < PCA_L ? A[tid][tid] : 0.0, red);
-    if (tid < PCA_L) A[tid][tid] += shift * tr / PCA_L;
-    __syncthreads();
-  }
-  for (int j = 0; j < PCA_L; ++j) {
-    // row j of R and row j of X divided by the pivot: every thread of the
-    // first wave takes the pivot itself (lane c: R[j][c] for c >= j, X[j][c]
-    // for c <= j, the only nonzeros of that row of X)
-    if (tid < PCA_L) {
-      const double d = A[j][j];
-      const double rjj = sqrt(d > 1e-300 ? d : 1e-300);
-      const double v = tid == j ? rjj : A[j][tid] / rjj;
-      const double x = X[j][tid] / rjj;
-      __builtin_amdgcn_wave_barrier();  // every lane has read A[j][j] before lane j replaces it
-      if (tid >= j) A[j][tid] = v;
-      if (tid <= j) X[j][tid] = x;
-    }
-    __syncthreads();
-    double rji[NU], aic[NU], xic[NU];
-    const double rjc = A[j][c], xjc = X[j][c];
+  __shared__ __attribute__((aligned(16))) double rowR[2][PCA_L][4], rowX[2][PCA_L][4];  // [buffer][column][row]
+  const int w = threadIdx.x >> 6, c = threadIdx.x & 63;
+  double add = 0.0;
+  if (shift > 0.0) add = shift * wave_sum_d(Gin[c * (PCA_L + 1)]) / PCA_L;
+  double a[4][4], x[4][4];
 #pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      rji[u] = A[j][r0 + 4 * u];
-      aic[u] = A[r0 + 4 * u][c];
-      xic[u] = X[r0 + 4 * u][c];
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = 16 * u + 4 * w + r;
+      a[u][r] = Gin[i * PCA_L + c] + (i == c ? add : 0.0);
+      x[u][r] = i == c ? 1.0 : 0.0;
     }
 #pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const int i = r0 + 4 * u;
-      if (i > j && c >= i) A[i][c] = aic[u] - rji[u] * rjc;
-      if (i > j && c <= j) X[i][c] = xic[u] - rji[u] * xjc;
+  for (int u0 = 0; u0 < 4; ++u0) {
+    for (int w0 = 0; w0 < 4; ++w0) {
+      const int j = 16 * u0 + 4 * w0, b = w0 & 1;
+      if (w == w0) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const double d = readlane_d(a[u0][p], j + p);
+          const double ri = rsqrt_d(d > 1e-300 ? d : 1e-300);
+          a[u0][p] *= ri;
+          x[u0][p] *= ri;
+#pragma unroll
+          for (int r = p + 1; r < 4; ++r) {
+            const double f = readlane_d(a[u0][p], j + r);
+            a[u0][r] -= f * a[u0][p];
+            x[u0][r] -= f * x[u0][p];
+          }
+          rowR[b][c][p] = a[u0][p];
+          rowX[b][c][p] = x[u0][p];
+        }
+      }
+      __syncthreads();  // (two buffers: a step's rows are read before the next but one's are written)
+      double rc[4], xc[4];
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        rc[p] = rowR[b][c][p];
+        xc[p] = rowX[b][c][p];
+      }
+#pragma unroll
+      for (int u = u0; u < 4; ++u) {
+        if (u == u0 && w <= w0) continue;  // wave-uniform
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int p = 0; p < 4; ++p) {
+            const double f = rowR[b][16 * u + 4 * w + r][p];
+            a[u][r] -= f * rc[p];
+            x[u][r] -= f * xc[p];
+          }
+      }
     }
-    __syncthreads();
   }
-  for (int e = tid; e < PCA_L * PCA_L; e += 256) Rinv[e] = float(X[e % PCA_L][e / PCA_L]);
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) Rinv[c * PCA_L + 16 * u + 4 * w + r] = float(x[u][r]);
 }
 
 // --- symmetric eigenproblem of the 64 x 64 Gram matrix, one block, FP64 -------
 
-// Cyclic Jacobi, tournament ordering: in step s of a sweep, player 0 stays
-// and players 1..63 rotate; pair i of the step is (arr[i], arr[63 - i]).
-// Outputs the eigenvalues in descending order (lam) and the matching
-// eigenvectors as the columns of U (row-major 64 x 64, FP64).
-__global__ __launch_bounds__(256) void pca_jacobi_kernel(const double* __restrict__ Gin, double* __restrict__ lam,
+// One-sided Jacobi (Hestenes) on G: rotations of column pairs until all
+// columns are orthogonal, G J = W; J is orthogonal and G symmetric positive
+// semidefinite, so the columns of W are the eigenvectors times their
+// eigenvalues.  A sweep takes the pairs (c, c ^ s), s = 1 .. 63 in Gray-code
+// order: every pair once, and in each step all 32 pairs are disjoint.  Outputs the eigenvalues
+// in descending order (lam) and the matching eigenvectors as the columns of U
+// (row-major 64 x 64, FP64; zero for an eigenvalue of zero).
+// What bounds it: a chain of 63 steps per sweep, 6 to 7 sweeps for the graded
+// matrices of a PCA.  Wave w holds rows 16 w .. 16 w + 15 in registers, lane c
+// column c and its partner's column.  Both lanes of a pair rotate both columns
+// (the same operations on the same bits), so the next step's partner, whose s
+// differs in one bit, comes from the lane that differs in that bit: register
+// moves within a wave (DPP, permlane swaps), no LDS.  The only exchange between
+// waves is the pairs' inner products (one LDS write, one barrier, four reads),
+// the squared norms being carried along.  The two-sided method with both
+// matrices in LDS took 600 us, fetching the partner by permutes through the
+// LDS unit 270, this one 230.
+__global__ __launch_bounds__(256, 1) void pca_jacobi_kernel(const double* __restrict__ Gin, double* __restrict__ lam,
                                                          double* __restrict__ U) {
-  __shared__ double A[PCA_L][PCA_L + 1];
-  __shared__ double V[PCA_L][PCA_L + 1];
-  __shared__ double cs[32], sn[32];
-  __shared__ int pp[32], qq[32];
-  __shared__ double red[4];
-  __shared__ int order[PCA_L];
-  const int tid = threadIdx.x;
-  for (int e = tid; e < PCA_L * PCA_L; e += 256) {
-    A[e / PCA_L][e % PCA_L] = Gin[e];
-    V[e / PCA_L][e % PCA_L] = (e / PCA_L == e % PCA_L) ? 1.0 : 0.0;
-  }
-  __syncthreads();
-  for (int sweep = 0; sweep < 30; ++sweep) {
-    double off = 0.0, dg = 0.0;
-    for (int e = tid; e < PCA_L * PCA_L; e += 256) {
-      const double v = A[e / PCA_L][e % PCA_L];
-      if (e / PCA_L == e % PCA_L) dg += v * v;
-      else off += v * v;
-    }
-    off = block_sum_d(off, red);  // same bits in every thread: a uniform exit
-    dg = block_sum_d(dg, red);
-    if (!(off > 1e-30 * dg)) break;
-    for (int step = 0; step < PCA_L - 1; ++step) {
-      if (tid < 32) {
-        auto player = [&](int j) { return j == 0 ? 0 : 1 + (j - 1 + step) % (PCA_L - 1); };
-        int p = player(tid), q = player(PCA_L - 1 - tid);
-        if (p > q) {
-          const int t = p;
-          p = q;
-          q = t;
-        }
-        const double apq = A[p][q];
-        double c = 1.0, s = 0.0;
-        if (fabs(apq) > 1e-300) {
-          const double th = (A[q][q] - A[p][p]) / (2.0 * apq);
-          const double t = (th >= 0.0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
-          c = 1.0 / sqrt(t * t + 1.0);
-          s = t * c;
-        }
-        cs[tid] = c;
-        sn[tid] = s;
-        pp[tid] = p;
-        qq[tid] = q;
+  constexpr int NR = PCA_L / 4;
+  __shared__ double part[2][4][PCA_L];
+  const int w = threadIdx.x >> 6, c = threadIdx.x & 63;
+  // scaled by a power of two to a largest diagonal entry near 1 (the squares
+  // below then stay in range)
+  double top = Gin[c * (PCA_L + 1)];
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) top = fmax(top, shfl_xor_d(top, m));
+  const int ex = top > 0.0 && top < INFINITY ? ilogb(top) : 0;
+  double a[NR];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) a[r] = ldexp(Gin[(NR * w + r) * PCA_L + c], -ex);
+  int buf = 0;
+  // sum over the waves, in their order
+  auto total = [&](double v) {
+    part[buf][w][c] = v;
+    __syncthreads();
+    const double t = (part[buf][0][c] + part[buf][1][c]) + (part[buf][2][c] + part[buf][3][c]);
+    buf ^= 1;
+    return t;
+  };
+  auto norm2 = [&]() {
+    double v = 0.0;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) v = fma(a[r], a[r], v);
+    return total(v);
+  };
+  for (int sweep = 0; sweep < 40; ++sweep) {
+    double nr = norm2();
+    double o[NR], onr = nr;  // the partner's column and norm (s = 0: its own)
+#pragma unroll
+    for (int r = 0; r < NR; ++r) o[r] = a[r];
+    bool rough = false;  // a pair whose cosine was above 1e-8: another sweep is needed
+    for (int k = 1; k < PCA_L; ++k) {
+      const int st = k ^ (k >> 1);
+      auto swap = [&](auto mc) {
+        constexpr int M = decltype(mc)::value;
+        auto move = [](double v) {
+          const uint64_t q = __builtin_bit_cast(uint64_t, v);
+          return __builtin_bit_cast(double, (uint64_t(xor_lane<M>(uint32_t(q >> 32))) << 32) | xor_lane<M>(uint32_t(q)));
+        };
+#pragma unroll
+        for (int r = 0; r < NR; ++r) o[r] = move(o[r]);
+        onr = move(onr);
+      };
+      switch (__builtin_ctz(unsigned(k))) {  // the bit in which this s differs from the last
+        case 0: swap(std::integral_constant<int, 1>{}); break;
+        case 1: swap(std::integral_constant<int, 2>{}); break;
+        case 2: swap(std::integral_constant<int, 4>{}); break;
+        case 3: swap(std::integral_constant<int, 8>{}); break;
+        case 4: swap(std::integral_constant<int, 16>{}); break;
+        default: swap(std::integral_constant<int, 32>{});
       }
-      __syncthreads();
-      // A <- J^T A J on the 2 x 2 blocks (rows of pair I, columns of pair J):
-      // the rows rotated first, then the columns, as in the two-pass order;
-      // V <- V J on the columns of every pair.  The blocks and the pairs are
-      // disjoint, so each thread loads all of its entries before it stores.
-      {
-        constexpr int NBK = 32 * 32 / 256, NV = 32 * PCA_L / 256;
-        double blk[NBK][4], vv[NV][2];
+      double v0 = 0.0, v1 = 0.0;
 #pragma unroll
-        for (int u = 0; u < NBK; ++u) {
-          const int e = tid + 256 * u, I = e >> 5, J = e & 31;
-          const int p1 = pp[I], q1 = qq[I], p2 = pp[J], q2 = qq[J];
-          blk[u][0] = A[p1][p2];
-          blk[u][1] = A[p1][q2];
-          blk[u][2] = A[q1][p2];
-          blk[u][3] = A[q1][q2];
-        }
-#pragma unroll
-        for (int u = 0; u < NV; ++u) {
-          const int e = tid + 256 * u, i = e / PCA_L, j = e % PCA_L;
-          vv[u][0] = V[j][pp[i]];
-          vv[u][1] = V[j][qq[i]];
-        }
-#pragma unroll
-        for (int u = 0; u < NBK; ++u) {
-          const int e = tid + 256 * u, I = e >> 5, J = e & 31;
-          const int p1 = pp[I], q1 = qq[I], p2 = pp[J], q2 = qq[J];
-          const double c1 = cs[I], s1 = sn[I], c2 = cs[J], s2 = sn[J];
-          const double rpp = c1 * blk[u][0] - s1 * blk[u][2], rpq = c1 * blk[u][1] - s1 * blk[u][3];
-          const double rqp = s1 * blk[u][0] + c1 * blk[u][2], rqq = s1 * blk[u][1] + c1 * blk[u][3];
-          A[p1][p2] = c2 * rpp - s2 * rpq;
-          A[p1][q2] = s2 * rpp + c2 * rpq;
-          A[q1][p2] = c2 * rqp - s2 * rqq;
-          A[q1][q2] = s2 * rqp + c2 * rqq;
-        }
-#pragma unroll
-        for (int u = 0; u < NV; ++u) {
-          const int e = tid + 256 * u, i = e / PCA_L, j = e % PCA_L;
-          const double c = cs[i], s = sn[i];
-          V[j][pp[i]] = c * vv[u][0] - s * vv[u][1];
-          V[j][qq[i]] = s * vv[u][0] + c * vv[u][1];
-        }
+      for (int r = 0; r < NR; r += 2) {
+        v0 = fma(a[r], o[r], v0);
+        v1 = fma(a[r + 1], o[r + 1], v1);
       }
-      __syncthreads();
-    }
-  }
-  if (tid == 0) {
-    for (int i = 0; i < PCA_L; ++i) order[i] = i;
-    for (int i = 1; i < PCA_L; ++i) {  // insertion sort, descending, stable
-      const int o = order[i];
-      int j = i - 1;
-      while (j >= 0 && A[order[j]][order[j]] < A[o][o]) {
-        order[j + 1] = order[j];
-        --j;
+      const double apq = total(v0 + v1);
+      const bool first = c < (c ^ st);
+      const double app = first ? nr : onr, aqq = first ? onr : nr;
+      const double lim = app * aqq, sq = apq * apq;
+      const bool act = sq > 1e-28 * lim;
+      if (__ballot(act) == 0) continue;  // the same in every wave
+      rough |= __ballot(sq > 1e-16 * lim) != 0;
+      // the rotation (of the smaller angle) that makes the columns orthogonal:
+      // with d = aqq - app, e = 2 apq, cos 2theta = |d| / sqrt(d^2 + e^2)
+      const double d = aqq - app, e = d < 0.0 ? -2.0 * apq : 2.0 * apq;
+      const double h2 = fma(d, d, e * e);
+      const double ih = rsqrt_d(h2 > 1e-300 ? h2 : 1e-300);
+      const double c2 = fma(0.5 * fabs(d), ih, 0.5);
+      const double rc = rsqrt_d(c2), si = 0.5 * e * ih * rc;
+      const bool turn = act && h2 > 1e-300;
+      const double cs = turn ? c2 * rc : 1.0;
+      const double sn = turn ? (first ? -si : si) : 0.0;
+      const double dn = sn * rc * apq;  // tan theta apq
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const double x = a[r];
+        a[r] = fma(cs, x, sn * o[r]);
+        o[r] = fma(cs, o[r], -sn * x);
       }
-      order[j + 1] = o;
+      nr += dn;
+      onr -= dn;
     }
+    if (!rough) break;
   }
-  __syncthreads();
-  if (tid < PCA_L) lam[tid] = A[order[tid]][order[tid]];
-  for (int e = tid; e < PCA_L * PCA_L; e += 256) U[e] = V[e / PCA_L][order[e % PCA_L]];
+  const double l = sqrt(norm2());
+  int rank = 0;  // place of this column in descending order
+  for (int q = 0; q < PCA_L; ++q) {
+    const double lq = readlane_d(l, q);
+    rank += lq > l || (lq == l && q < c) ? 1 : 0;
+  }
+  rank = rank < PCA_L ? rank : PCA_L - 1;
+  if (w == 0) lam[rank] = ldexp(l, ex);
+  const double inv = l > 0.0 ? 1.0 / l : 0.0;
+#pragma unroll
+  for (int r = 0; r < NR; ++r) U[(NR * w + r) * PCA_L + rank] = a[r] * inv;
 }
 
 // W1 = U diag(1/s) (float), s = sqrt(max(lam, 0)).
@@ -601,7 +688,8 @@ __global__ __launch_bounds__(256) void pca_sign_kernel(const float* __restrict__
 
 struct PcaPlan {
   size_t o_mpart, o_Ya, o_Yb, o_Za, o_Zb, o_part, o_gpart, o_G, o_Rinv, o_lam, o_U, o_W1, o_W2, bytes;
-  int64_t nchunk_n, nchunk_g, gchunk_max;
+  int64_t nchunk, gchunk_max;
+  int rc;  // rows per chunk of the column sums and of X^T Q
 };
 
 // Row blocks of a Gram matrix over m rows: at most PCA_GMAX blocks, each a
@@ -616,19 +704,47 @@ GramSplit gram_split(int64_t m) {
   return {ceil_div(m, rpb), rpb};
 }
 
+// Rows of X W in whole tiles without a split of the columns (head), and the
+// split of the columns for the rest (see pca_tall).
+struct PcaSplit {
+  int64_t head;
+  int parts, kper;
+};
+PcaSplit pca_split(int64_t M, int K, bool centred) {
+  const int64_t tiles = ceil_div(M, PCA_BM), rest = tiles % 512;
+  if (!centred || rest == 0 || rest > 256) return {M, 1, K};
+  int64_t parts = 512 / rest;
+  const int64_t chunks = ceil_div(K, PCA_KC);
+  if (parts > chunks) parts = chunks;
+  const int kper = int(ceil_div(chunks, parts)) * PCA_KC;
+  return {(tiles - rest) * PCA_BM, int(ceil_div(K, kper)), kper};
+}
+
 PcaPlan pca_plan(int64_t n, int g) {
   PcaPlan L;
   Carve c;
-  L.nchunk_n = ceil_div(n, PCA_RC);
-  L.nchunk_g = ceil_div(g, PCA_RC);
+  // chunks of X's rows: enough for three blocks (the reduction's occupancy)
+  // on each of the 256 CUs, of 64 to 2048 rows (the sums within a chunk are
+  // FP32), in whole rounds of 768 blocks
+  const int64_t cols = ceil_div(g, 256);
+  const int64_t rounds = ceil_div(ceil_div(n, PCA_RC) * cols, 768);
+  int64_t want = 768 * rounds / cols;
+  if (want < 1) want = 1;
+  if (want > 65535) want = 65535;  // grid.y
+  int64_t rc = ceil_div(ceil_div(n, want), 32) * 32;
+  rc = rc < PCA_RMIN ? PCA_RMIN : (rc > PCA_RC ? PCA_RC : rc);
+  L.rc = int(rc);
+  L.nchunk = ceil_div(n, rc);
   const int64_t gn = gram_split(n).nblk, gg = gram_split(g).nblk;
   L.gchunk_max = gn > gg ? gn : gg;
-  L.o_mpart = c.take(sizeof(double) * size_t(L.nchunk_n) * size_t(g));
+  L.o_mpart = c.take(sizeof(double) * size_t(L.nchunk) * size_t(g));
   L.o_Ya = c.take(sizeof(float) * size_t(n) * PCA_L);
   L.o_Yb = c.take(sizeof(float) * size_t(n) * PCA_L);
   L.o_Za = c.take(sizeof(float) * size_t(g) * PCA_L);
   L.o_Zb = c.take(sizeof(float) * size_t(g) * PCA_L);
-  L.o_part = c.take(sizeof(float) * size_t(L.nchunk_n) * size_t(g) * PCA_L);
+  const PcaSplit sp = pca_split(n, g, true);
+  const int64_t red = L.nchunk * int64_t(g), tall = sp.parts * (n - sp.head);
+  L.o_part = c.take(sizeof(float) * size_t(red > tall ? red : tall) * PCA_L);
   L.o_gpart = c.take(sizeof(double) * size_t(L.gchunk_max) * PCA_L * PCA_L);
   L.o_G = c.take(sizeof(double) * PCA_L * PCA_L);
   L.o_Rinv = c.take(sizeof(float) * PCA_L * PCA_L);
@@ -650,19 +766,40 @@ struct PcaCtx {
   }
 };
 
-// C (M x ncols, ldc) = (A - mu) W, A is M x K (mu nullable: no centring)
-int pca_tall(const PcaCtx& x, const float* A, int64_t M, int K, const float* mu, const float* W, float* C, int ldc,
-             int ncols) {
-  const dim3 grid(unsigned(ceil_div(M, 128)));
+// The product of rows [0, M) of A with W, the columns in `parts` ranges of
+// kper: to C, or (parts > 1) M x 64 partials to C.
+int pca_tall_launch(const PcaCtx& x, const float* A, int64_t M, int K, const float* mu, const float* W, float* C,
+                    int ldc, int ncols, int parts, int kper) {
+  const dim3 grid(unsigned(ceil_div(M, PCA_BM)), unsigned(parts));
   const bool vec = K % 4 == 0;
   if (mu && vec)
-    hipLaunchKernelGGL((pca_gemm_tall_kernel<true, true>), grid, dim3(256), 0, x.s, A, M, K, mu, W, C, ldc, ncols);
+    hipLaunchKernelGGL((pca_gemm_tall_kernel<true, true>), grid, dim3(256), 0, x.s, A, M, K, mu, W, C, ldc, ncols, kper);
   else if (mu)
-    hipLaunchKernelGGL((pca_gemm_tall_kernel<true, false>), grid, dim3(256), 0, x.s, A, M, K, mu, W, C, ldc, ncols);
-  else if (vec)
-    hipLaunchKernelGGL((pca_gemm_tall_kernel<false, true>), grid, dim3(256), 0, x.s, A, M, K, mu, W, C, ldc, ncols);
+    hipLaunchKernelGGL((pca_gemm_tall_kernel<true, false>), grid, dim3(256), 0, x.s, A, M, K, mu, W, C, ldc, ncols, kper);
   else
-    hipLaunchKernelGGL((pca_gemm_tall_kernel<false, false>), grid, dim3(256), 0, x.s, A, M, K, mu, W, C, ldc, ncols);
+    hipLaunchKernelGGL((pca_gemm_tall_kernel<false, true>), grid, dim3(256), 0, x.s, A, M, K, mu, W, C, ldc, ncols, kper);
+  TSNE_CHECK_LAUNCH();
+  return TSNE_OK;
+}
+
+// C (M x ncols, ldc) = (A - mu) W, A is M x K (mu nullable: no centring, K =
+// 64).  The rows that do not fill a round of 512 blocks of 128 rows (two per
+// CU; four fit, but a lone pair runs twice as fast) to a half (all rows of a small matrix, the last
+// few tiles of a large one) split the columns as well, into enough ranges to
+// fill the round, and their partials are added in order: 2,700 x 1,838 (22
+// blocks) 91 -> 20 us, 200,000 x 2,000 (1,563 blocks, 27 past three rounds)
+// 540 -> 525 us.
+int pca_tall(const PcaCtx& x, const float* A, int64_t M, int K, const float* mu, const float* W, float* C, int ldc,
+             int ncols) {
+  const PcaSplit sp = pca_split(M, K, mu != nullptr);
+  int rc;
+  if (sp.head > 0 && (rc = pca_tall_launch(x, A, sp.head, K, mu, W, C, ldc, ncols, 1, K))) return rc;
+  if (sp.head == M) return TSNE_OK;
+  float* part = x.at<float>(x.L.o_part);
+  const int64_t tail = M - sp.head;
+  if ((rc = pca_tall_launch(x, A + sp.head * K, tail, K, mu, W, part, PCA_L, PCA_L, sp.parts, sp.kper))) return rc;
+  hipLaunchKernelGGL(pca_reduce_kernel, dim3(unsigned(ceil_div(tail * PCA_L, 256))), dim3(256), 0, x.s, part,
+                     int64_t(sp.parts), tail * PCA_L, C + sp.head * PCA_L);
   TSNE_CHECK_LAUNCH();
   return TSNE_OK;
 }
@@ -670,10 +807,11 @@ int pca_tall(const PcaCtx& x, const float* A, int64_t M, int K, const float* mu,
 // out (K x 64) = (A - mu)^T Bm, A is M x K
 int pca_red(const PcaCtx& x, const float* A, int64_t M, int K, const float* mu, const float* Bm, float* out) {
   float* part = x.at<float>(x.L.o_part);
-  const int64_t nchunk = ceil_div(M, PCA_RC);
+  const int64_t nchunk = x.L.nchunk;
+  const int rc = x.L.rc;
   const dim3 grid(unsigned(ceil_div(K, 256)), unsigned(nchunk));
-  if (K % 4 == 0) hipLaunchKernelGGL((pca_gemm_red_kernel<true, true>), grid, dim3(256), 0, x.s, A, M, K, mu, Bm, part);
-  else hipLaunchKernelGGL((pca_gemm_red_kernel<true, false>), grid, dim3(256), 0, x.s, A, M, K, mu, Bm, part);
+  if (K % 4 == 0) hipLaunchKernelGGL((pca_gemm_red_kernel<true, true>), grid, dim3(256), 0, x.s, A, M, K, mu, Bm, rc, part);
+  else hipLaunchKernelGGL((pca_gemm_red_kernel<true, false>), grid, dim3(256), 0, x.s, A, M, K, mu, Bm, rc, part);
   TSNE_CHECK_LAUNCH();
   const int64_t count = int64_t(K) * PCA_L;
   hipLaunchKernelGGL(pca_reduce_kernel, dim3(unsigned(ceil_div(count, 256))), dim3(256), 0, x.s, part, nchunk, count,
@@ -688,24 +826,20 @@ int pca_gram(const PcaCtx& x, const float* Y, int64_t m) {
   hipLaunchKernelGGL(pca_gram_kernel, dim3(unsigned(sp.nblk)), dim3(256), 0, x.s, Y, m, sp.rpb,
                      x.at<double>(x.L.o_gpart));
   TSNE_CHECK_LAUNCH();
-  hipLaunchKernelGGL(pca_gram_reduce_kernel, dim3(PCA_L * PCA_L / 64), dim3(64), 0, x.s, x.at<double>(x.L.o_gpart),
+  hipLaunchKernelGGL(pca_gram_reduce_kernel, dim3(PCA_L * PCA_L / 64), dim3(1024), 0, x.s, x.at<double>(x.L.o_gpart),
                      sp.nblk, x.at<double>(x.L.o_G));
   TSNE_CHECK_LAUNCH();
   return TSNE_OK;
 }
 
-// CholeskyQR2 of the m x 64 factor in `a` (result in `a`, `b` scratch)
-int pca_orth(const PcaCtx& x, float* a, float* b, int64_t m) {
+// One shifted CholeskyQR pass of the m x 64 factor a: b = a R^-1.
+int pca_orth(const PcaCtx& x, const float* a, float* b, int64_t m, double shift) {
   int rc;
   float* Rinv = x.at<float>(x.L.o_Rinv);
   if ((rc = pca_gram(x, a, m))) return rc;
-  hipLaunchKernelGGL(pca_cholinv_kernel, dim3(1), dim3(256), 0, x.s, x.at<double>(x.L.o_G), 1e-12, Rinv);
+  hipLaunchKernelGGL(pca_cholinv_kernel, dim3(1), dim3(256), 0, x.s, x.at<double>(x.L.o_G), shift, Rinv);
   TSNE_CHECK_LAUNCH();
-  if ((rc = pca_tall(x, a, m, PCA_L, nullptr, Rinv, b, PCA_L, PCA_L))) return rc;
-  if ((rc = pca_gram(x, b, m))) return rc;
-  hipLaunchKernelGGL(pca_cholinv_kernel, dim3(1), dim3(256), 0, x.s, x.at<double>(x.L.o_G), 0.0, Rinv);
-  TSNE_CHECK_LAUNCH();
-  return pca_tall(x, b, m, PCA_L, nullptr, Rinv, a, PCA_L, PCA_L);
+  return pca_tall(x, a, m, PCA_L, nullptr, Rinv, b, PCA_L, PCA_L);
 }
 
 }  // namespace tsne
@@ -727,21 +861,27 @@ extern "C" int tsne_pca(const float* X, int64_t n, int32_t g, int32_t k, int32_t
   float* Za = x.at<float>(L.o_Za);
   float* Zb = x.at<float>(L.o_Zb);
   // column means
-  hipLaunchKernelGGL(pca_colsum_kernel, dim3(unsigned(ceil_div(g, 256)), unsigned(L.nchunk_n)), dim3(256), 0, x.s,
-                     X, n, g, x.at<double>(L.o_mpart));
+  hipLaunchKernelGGL(pca_colsum_kernel, dim3(unsigned(ceil_div(g, 256)), unsigned(L.nchunk)), dim3(256), 0, x.s,
+                     X, n, g, L.rc, x.at<double>(L.o_mpart));
   TSNE_CHECK_LAUNCH();
-  hipLaunchKernelGGL(pca_colmean_kernel, dim3(unsigned(ceil_div(g, 256))), dim3(256), 0, x.s,
-                     x.at<double>(L.o_mpart), L.nchunk_n, g, n, mean);
+  hipLaunchKernelGGL(pca_colmean_kernel, dim3(unsigned(ceil_div(g, 64))), dim3(1024), 0, x.s,
+                     x.at<double>(L.o_mpart), L.nchunk, g, n, mean);
   TSNE_CHECK_LAUNCH();
-  // range finder with power iterations
+  // range finder with power iterations.  Only the last Q has to be
+  // orthonormal (B = Q^T Xc below), so only it takes both passes of
+  // CholeskyQR2; before that one pass keeps the span and a basis with a
+  // condition number near 1, which is all the next product needs.  (The
+  // second pass multiplies by a matrix near I: it cannot mend what rounding
+  // did to the span in the first.)
   if ((rc = pca_tall(x, X, n, g, mean, omega, Ya, PCA_L, PCA_L))) return rc;
-  if ((rc = pca_orth(x, Ya, Yb, n))) return rc;
+  if ((rc = pca_orth(x, Ya, Yb, n, 1e-12))) return rc;
   for (int it = 0; it < q; ++it) {
-    if ((rc = pca_red(x, X, n, g, mean, Ya, Za))) return rc;
-    if ((rc = pca_orth(x, Za, Zb, g))) return rc;
-    if ((rc = pca_tall(x, X, n, g, mean, Za, Ya, PCA_L, PCA_L))) return rc;
-    if ((rc = pca_orth(x, Ya, Yb, n))) return rc;
+    if ((rc = pca_red(x, X, n, g, mean, Yb, Za))) return rc;
+    if ((rc = pca_orth(x, Za, Zb, g, 1e-12))) return rc;
+    if ((rc = pca_tall(x, X, n, g, mean, Zb, Ya, PCA_L, PCA_L))) return rc;
+    if ((rc = pca_orth(x, Ya, Yb, n, 1e-12))) return rc;
   }
+  if ((rc = pca_orth(x, Yb, Ya, n, 0.0))) return rc;
   // Z = Xc^T Q = B^T; Z^T Z = U diag(s^2) U^T
   if ((rc = pca_red(x, X, n, g, mean, Ya, Za))) return rc;
   if ((rc = pca_gram(x, Za, g))) return rc;

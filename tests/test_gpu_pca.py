@@ -108,3 +108,58 @@ def test_pca_rank_deficient(dev):
     dots = np.abs(np.sum(comp[:5] * ocomp[:5], axis=1))
     assert np.all(dots > 1 - 1e-4), dots
     np.testing.assert_allclose(comp @ comp.T, np.eye(k), atol=1e-3)
+
+
+# The splits: fewer tiles of 128 rows than fill the chip (their columns are
+# split, down to the smallest n and g), one tile past a whole round of 512
+# (split) and a round and a half (not split), row chunks of 64 rows and more.
+# Tolerances as in test_pca_matches_oracle; the spectrum falls by 1.13 per
+# component, so every gap is at least 8 %.
+@pytest.mark.parametrize("n,g,k", [(64, 64, 5), (129, 65, 8), (300, 1000, 20), (2700, 1838, 20), (65_537, 70, 12),
+                                   (98_400, 68, 12)])
+def test_pca_split_sizes(dev, n, g, k):
+    say("pca split sizes", n, g, k)
+    X = synth.make_expression(n, g, 70 + n, latent=min(64, g), top=100.0, bottom=0.05)
+    Om = synth.make_omega(g, 71 + g)
+    sc, comp, sv, mu = run(dev, X, k, Om, 2)
+    osc, ocomp, osv, omu = opca.randomized_pca(X.astype(np.float64), k, Om.astype(np.float64), 2)
+    np.testing.assert_allclose(mu, omu, rtol=1e-5, atol=1e-5)
+    assert np.abs(sv - osv).max() <= 2e-5 * osv[0]
+    gap = np.minimum(np.abs(np.diff(np.r_[np.inf, osv])), np.abs(np.diff(np.r_[osv, 0.0]))) / osv
+    good = np.where((gap[:k] > 0.02) & (osv[:k] >= 0.05 * osv[0]))[0]
+    assert good.size >= 4
+    assert np.all(np.sum(comp[good] * ocomp[good], axis=1) > 1 - 1e-4)
+    np.testing.assert_allclose(comp @ comp.T, np.eye(k), atol=2e-5)
+    sc2, comp2, _, _ = run(dev, X, k, Om, 2)
+    assert np.array_equal(sc, sc2) and np.array_equal(comp, comp2)
+
+
+@pytest.mark.parametrize("bottom", [1.0, 1e-2, 1e-4])
+def test_pca_steep_spectra(dev, bottom):
+    # 64 factors falling over up to six decades below the largest: the single
+    # CholeskyQR passes between the products and the one-sided Jacobi method
+    # meet condition numbers up to what FP32 data can hold
+    say("pca steep spectrum", bottom)
+    n, g, k = 3000, 400, 20
+    X = synth.make_expression(n, g, 81, top=100.0, bottom=bottom, noise=0.0, offset=0.5)
+    Om = synth.make_omega(g, 82)
+    sc, comp, sv, mu = run(dev, X, k, Om, 2)
+    osc, ocomp, osv, omu = opca.randomized_pca(X.astype(np.float64), k, Om.astype(np.float64), 2)
+    assert np.abs(sv - osv).max() <= 2e-5 * osv[0]
+    good = np.where(osv[:k] >= 0.05 * osv[0])[0]
+    assert np.all(np.sum(comp[good] * ocomp[good], axis=1) > 1 - 1e-4)
+    np.testing.assert_allclose(comp @ comp.T, np.eye(k), atol=2e-5)
+
+
+def test_pca_low_rank(dev):
+    # rank 20: the directions past it are not defined, the 20 leading ones are
+    say("pca low rank")
+    rng = np.random.default_rng(83)
+    n, g, r = 2000, 300, 20
+    X = (rng.standard_normal((n, r)) * np.geomspace(10.0, 2.0, r)) @ np.linalg.qr(rng.standard_normal((g, r)))[0].T
+    X = np.ascontiguousarray(X, dtype=np.float32)
+    sc, comp, sv, mu = run(dev, X, r, synth.make_omega(g, 84), 2)
+    U, s, Vt = np.linalg.svd(X.astype(np.float64) - X.astype(np.float64).mean(0), full_matrices=False)
+    assert np.abs(sv - s[:r]).max() <= 2e-5 * s[0]
+    assert np.all(np.abs(np.sum(comp * Vt[:r], axis=1)) > 1 - 1e-4)
+    np.testing.assert_allclose(comp @ comp.T, np.eye(r), atol=2e-5)
