@@ -270,6 +270,41 @@ __device__ __forceinline__ void wave_sort(uint64_t (&v)[EPL]) {
   }
 }
 
+// The same for 32-bit keys.
+template <int EPL>
+__device__ __forceinline__ void wave_sort32(uint32_t (&v)[EPL]) {
+  const int lane = lane_id();
+  constexpr int N = EPL * 64;
+#pragma unroll
+  for (int size = 2; size <= N; size <<= 1) {
+#pragma unroll
+    for (int stride = size >> 1; stride > 0; stride >>= 1) {
+      if (stride >= 64) {
+        const int rs = stride >> 6;
+#pragma unroll
+        for (int r = 0; r < EPL; ++r) {
+          const int p = r ^ rs;
+          if (p > r) {
+            const bool asc = (((r << 6) + lane) & size) == 0;
+            const uint32_t mn = v[r] < v[p] ? v[r] : v[p], mx = v[r] < v[p] ? v[p] : v[r];
+            v[r] = asc ? mn : mx;
+            v[p] = asc ? mx : mn;
+          }
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < EPL; ++r) {
+          const uint32_t o = xor_lane(v[r], stride);
+          const bool asc = (((r << 6) + lane) & size) == 0;
+          const bool lower = (lane & stride) == 0;
+          const uint32_t mn = v[r] < o ? v[r] : o, mx = v[r] < o ? o : v[r];
+          v[r] = lower == asc ? mn : mx;
+        }
+      }
+    }
+  }
+}
+
 // Read register r of lane `src` (both wave-uniform) as a uniform value.
 template <int EPL>
 __device__ __forceinline__ uint64_t wave_pick(const uint64_t (&v)[EPL], int e) {
