@@ -147,8 +147,10 @@ int tsne_knn(const float* X, int64_t n, int32_t d, int32_t k, int32_t precision,
  * tsne_calibrate_P -- perplexity calibration [vdMH08 eq. 1 and eq. 3].
  * Per row i, over its k neighbour distances (FP32 arithmetic throughout):
  * s_j = d_ij - min_l d_il, p_{j|i} = exp(-beta_i s_j) / sum_l exp(-beta_i s_l),
- * with beta_i found by bisection (start 1, bracket (0, inf), doubling until
- * bracketed) so that the entropy H = ln sum_l e^{-beta s_l} + beta sum_j p_j s_j
+ * with beta_i found by a bracketed Newton search in ln beta (by bisection
+ * alone -- start 1, bracket (0, inf), doubling until bracketed -- for rows
+ * that it does not settle, for max_iter < 64 and for tol below about 1e-6)
+ * so that the entropy H = ln sum_l e^{-beta s_l} + beta sum_j p_j s_j
  * equals ln(perplexity) nats to within tol.  H is evaluated in FP32 and the
  * search stops once that evaluation is within tol - min(TSNE_CALIB_H_MARGIN,
  * tol / 2): the margin covers the FP32 evaluation error of H (sums of k

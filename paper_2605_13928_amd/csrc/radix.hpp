@@ -82,6 +82,10 @@ __global__ __launch_bounds__(256) void rs_scatter_kernel(In in, int64_t n_max, c
   uint32_t key[RS_ROUNDS];
 #pragma unroll
   for (int r = 0; r < RS_ROUNDS; ++r) key[r] = first + 64 * r < items ? in.get_key(b0 + first + 64 * r) : 0u;
+  uint32_t pa[NPAY > 0 ? RS_ROUNDS : 1];  // in flight while the ranks are formed
+#pragma unroll
+  for (int r = 0; r < RS_ROUNDS; ++r)
+    if (NPAY > 0) pa[NPAY > 0 ? r : 0] = first + 64 * r < items ? in.get_a(b0 + first + 64 * r) : 0u;
 #pragma unroll
   for (int u = 0; u < 4; ++u) wc[u][tid] = 0u;
   const int64_t goff = tid <= int(mask) ? off[int64_t(tid) * nblk + blockIdx.x] : 0;
@@ -96,12 +100,15 @@ __global__ __launch_bounds__(256) void rs_scatter_kernel(In in, int64_t n_max, c
   for (int r = 0; r < RS_ROUNDS; ++r) {
     const bool valid = first + 64 * r < items;
     const uint32_t d = (key[r] >> shift) & mask;
-    uint64_t m = __ballot(valid);
+    const uint64_t act = __ballot(valid);
+    uint32_t mlo = uint32_t(act), mhi = uint32_t(act >> 32);
     for (int b = 0; b < bits; ++b) {
-      const bool bit = (d >> b) & 1u;
-      const uint64_t bb = __ballot(bit);
-      m &= bit ? bb : ~bb;
+      const uint32_t t = 0u - ((d >> b) & 1u);  // all ones where the bit is set
+      const uint64_t bb = __ballot(t != 0u);
+      mlo &= ~(uint32_t(bb) ^ t);
+      mhi &= ~(uint32_t(bb >> 32) ^ t);
     }
+    const uint64_t m = (uint64_t(mhi) << 32) | mlo;
     const uint32_t before = uint32_t(__popcll(m & lt));
     const uint32_t pre = valid ? cw[d] : 0u;
     __builtin_amdgcn_wave_barrier();
@@ -148,18 +155,25 @@ __global__ __launch_bounds__(256) void rs_scatter_kernel(In in, int64_t n_max, c
       if (KEYS) kout[dst[r]] = k;
     }
   }
-  auto payload = [&](auto get, uint32_t* out) {
+  auto payload = [&](const uint32_t (&v)[NPAY > 0 ? RS_ROUNDS : 1], uint32_t* out) {
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < RS_ROUNDS; ++r)
-      if (first + 64 * r < items) stage[pos[r]] = get(b0 + first + 64 * r);
+      if (first + 64 * r < items) stage[pos[r]] = v[NPAY > 0 ? r : 0];
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < RS_ROUNDS; ++r)
       if (tid + 256 * r < items) out[dst[r]] = stage[tid + 256 * r];
   };
-  if (NPAY > 0) payload([&](int64_t i) { return in.get_a(i); }, aout);
-  if (NPAY > 1) payload([&](int64_t i) { return in.get_b(i); }, bout);
+  if (NPAY > 1) {
+    uint32_t pb[NPAY > 0 ? RS_ROUNDS : 1];
+#pragma unroll
+    for (int r = 0; r < RS_ROUNDS; ++r) pb[NPAY > 0 ? r : 0] = first + 64 * r < items ? in.get_b(b0 + first + 64 * r) : 0u;
+    payload(pa, aout);
+    payload(pb, bout);
+  } else if (NPAY > 0) {
+    payload(pa, aout);
+  }
 }
 
 // Workspace of a sort of at most n items (n < 2^32): digit counts, their

@@ -112,3 +112,36 @@ def test_calibrate_unreachable_rows_default_max_iter(dev):
     np.testing.assert_allclose(P[2, :40], 1.0 / 40, rtol=1e-6)
     assert (P[2, 40:] == 0).all()
     np.testing.assert_allclose(P[4, :31], 1.0 / 31, rtol=1e-6)
+
+
+@pytest.mark.parametrize("scale", [1e-12, 1e-3, 1.0, 1e4, 1e15])
+@pytest.mark.parametrize("k,perp", [(3, 2.9), (15, 1.2), (90, 30.0), (150, 149.0)])
+def test_calibrate_newton_agrees_with_bisection(dev, k, perp, scale):
+    """64 evaluations or more allowed: Newton steps in ln beta; fewer: the
+    bisection alone, here with 63.  A bisection from beta = 1 needs about
+    log2 of the scale plus 20 evaluations, so the rows of all but the
+    extreme scales converge in both; wherever both do, each H is within 1e-5
+    of the target.  With v the variance of beta d2 under P and r the range of
+    beta d2, dH / d ln beta = -v and |d ln p / d ln beta| <= r, so the two P
+    differ by at most p r 2e-5 / v to first order (a tenth more is allowed,
+    and 1e-6 p for the rounding of p).  The Newton search converges at every
+    scale."""
+    say("calibrate newton", k, perp, scale)
+    rng = np.random.default_rng(k)
+    d2 = (np.sort(rng.chisquare(50, (300, k)), axis=1) * scale).astype(np.float32)
+    d2[7, : k // 2] = d2[7, 0]  # ties
+    d2[8] = np.float32(scale) * np.arange(1, k + 1, dtype=np.float32) ** 3  # a long tail
+    Pn, bn, cn, nn = (t.cpu().numpy() for t in api.calibrate_P(to_dev(d2, dev), perp, max_iter=200))
+    Pb, bb, cb, nb = (t.cpu().numpy() for t in api.calibrate_P(to_dev(d2, dev), perp, max_iter=63))
+    assert np.isfinite(Pn).all() and np.isfinite(bn).all()
+    assert (cn >= cb).all() and nn[0] == (cn == 0).sum()
+    both = (cn == 1) & (cb == 1)
+    if 1e-5 < scale < 1e6:
+        assert both.sum() >= 298
+    x = bb[both, None].astype(np.float64) * d2[both]
+    p = Pb[both].astype(np.float64)
+    v = (p * x * x).sum(1) - (p * x).sum(1) ** 2
+    tol = p * (1.1 * 2e-5 * (x.max(1) - x.min(1)) / v)[:, None] + 1e-6 * p + 1e-30
+    assert (np.abs(Pn[both] - Pb[both]) <= tol).all()
+    for i in np.flatnonzero(cn == 1)[::37]:
+        assert abs(entropy64(d2[i].astype(np.float64), float(bn[i])) - np.log(perp)) <= 1e-5

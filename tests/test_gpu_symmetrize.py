@@ -87,3 +87,29 @@ def test_symmetrize_rejects_invalid_lists(dev):
     bad[12, 1] = 100  # out of range
     with pytest.raises(ValueError):
         api.symmetrize(to_dev(bad, dev), to_dev(Pc, dev))
+
+
+# The number of sort passes and their digits change with the bits of n (one
+# pass to n = 255, two to 65,535, three above), the blocks hold 4096 items,
+# the out-lists are sorted in 64, 128 or 256 keys, and rows with in-lists of
+# more than 512 sources are searched in memory.
+@pytest.mark.parametrize("n,k", [(128, 32), (255, 3), (256, 16), (257, 64), (1366, 3), (300, 65), (300, 128),
+                                 (300, 129), (300, 256), (65_535, 2), (65_536, 3), (65_537, 1)])
+def test_symmetrize_sort_edges(dev, n, k):
+    say("symmetrize sort edges", n, k)
+    rng = np.random.default_rng(n + k)
+    # in-degrees from none to most of the rows
+    pool = (n * rng.random((n, k + 8)) ** 3).astype(np.int64)
+    idx = np.empty((n, k), np.int32)
+    for i in range(n):
+        row = dict.fromkeys(j for j in pool[i].tolist() if j != i)
+        j = int(rng.integers(n))
+        while len(row) < k:
+            if j != i:
+                row[j] = None
+            j = (j + 1) % n
+        idx[i] = list(row)[:k]
+    Pc = rng.random((n, k))
+    Pc /= Pc.sum(1, keepdims=True)
+    S, G = run_both(dev, idx, Pc)
+    check(S, G, n)
