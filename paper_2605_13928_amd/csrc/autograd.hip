@@ -220,7 +220,7 @@ struct KlLayout32 {
     L.o_kg = c.take(L.kg.bytes);
     L.o_g0 = c.take(sizeof(float) * 2 * size_t(n));
     L.o_Z = c.take(sizeof(double));
-    L.o_Zb = c.take(sizeof(double) * size_t(L.kg.g.nwg));
+    L.o_Zb = c.take(sizeof(double) * size_t(L.kg.g.nwg));  // (the tiles' partials are no more)
     const int64_t nsp = L.nrow_blocks > KL32_SBLOCKS ? L.nrow_blocks : KL32_SBLOCKS;
     L.o_sp = c.take(sizeof(double) * 3 * size_t(nsp));
     L.bytes = c.off;
@@ -234,15 +234,19 @@ int kl_forward_f32(const float* Y, int64_t n, const int64_t* row_ptr, const int3
   double* Zblock = reinterpret_cast<double*>(ws + L.o_Zb);
   double* spart = reinterpret_cast<double*>(ws + L.o_sp);
   const float2* Y2 = reinterpret_cast<const float2*>(Y);
-  const dim3 grid(unsigned(g.nwg)), block(256);
-  if (g.S == 256) hipLaunchKernelGGL(zsum_sym_kernel<1>, grid, block, 0, s, Y2, n, g.ns, Zblock);
+  // few points: one 64 x 64 tile per wave whichever kernel the gradient takes
+  const int64_t nt = ceil_div(n, SYM_TILE);
+  const int64_t nz = n <= SYM_QUAD_N ? ceil_div(nt * (nt + 1) / 2, SYM_WAVES) : g.nwg;
+  const dim3 grid(static_cast<unsigned>(nz)), block(256);
+  if (n <= SYM_QUAD_N) hipLaunchKernelGGL(zsum_tile_kernel, grid, block, 0, s, Y2, n, nt, Zblock);
+  else if (g.S == 256) hipLaunchKernelGGL(zsum_sym_kernel<1>, grid, block, 0, s, Y2, n, g.ns, Zblock);
   else if (g.S == 512) hipLaunchKernelGGL(zsum_sym_kernel<2>, grid, block, 0, s, Y2, n, g.ns, Zblock);
   else hipLaunchKernelGGL(zsum_sym_kernel<4>, grid, block, 0, s, Y2, n, g.ns, Zblock);
   TSNE_CHECK_LAUNCH();
   hipLaunchKernelGGL(sparse_sums_kernel<float>, dim3(unsigned(L.nrow_blocks)), dim3(256), 0, s, Y, n, row_ptr, col,
                      val, spart);
   TSNE_CHECK_LAUNCH();
-  hipLaunchKernelGGL(kl_combine_kernel<float>, dim3(1), dim3(256), 0, s, spart, L.nrow_blocks, Zblock, g.nwg, C, Z);
+  hipLaunchKernelGGL(kl_combine_kernel<float>, dim3(1), dim3(256), 0, s, spart, L.nrow_blocks, Zblock, nz, C, Z);
   TSNE_CHECK_LAUNCH();
   return TSNE_OK;
 }

@@ -651,7 +651,10 @@ int klgrad_launch(const KlGradPlan& L, char* ws, const float* Y, int64_t n, cons
   const dim3 grid(unsigned(g.nwg)), block(256);
 #define TSNE_REP_SYM(Z, PF, A) \
   hipLaunchKernelGGL((rep_sym_kernel<Z, PF, A>), grid, block, lds, s, Y2, n, g.ns, Rpart, Zrowpart, Zblock, al, Apart)
-  if (Zrow) {
+  if (g.S == SYM_QUAD) {
+    auto quad = Zrow ? rep_quad_kernel<true, false> : (fused ? rep_quad_kernel<false, true> : rep_quad_kernel<false, false>);
+    hipLaunchKernelGGL(quad, grid, block, 0, s, Y2, n, g.ns, Rpart, Zrowpart, Zblock, al, Apart);
+  } else if (Zrow) {
     if (g.S == 256) TSNE_REP_SYM(true, 1, false);
     else if (g.S == 512) TSNE_REP_SYM(true, 2, false);
     else TSNE_REP_SYM(true, 4, false);

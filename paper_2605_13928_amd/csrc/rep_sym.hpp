@@ -153,11 +153,28 @@ __host__ __device__ constexpr bool part_grouped(int64_t S) { return S <= 256; }
 // two waves per SIMD) on the 256 CUs of an MI355X.
 constexpr int64_t SYM_GRID = 512;
 constexpr int SYM_MAX_S = 1024;
+// Up to SYM_QUAD_N points superblocks are of 128 and a workgroup takes one
+// pair of them, a tile per wave (rep_quad_kernel): the 21 jobs of 256 x 256
+// that 1,500 points make ran on 21 of the 256 CUs, 24 us of the iteration's
+// 29, against 8.2 us for the 78 of 128 x 128.  Above, a workgroup per job pays
+// its start and its partials (n / 128 slices per point for the finalize pass)
+// more often than the finer split gains.  Whole iterations, quad against 256:
+// 13.6 / 29.3 us at 1,500 points, 13.7 / 21.9 at 3,000, 18.6 / 20.5 at 5,000,
+// 29.3 / 25.0 at 8,000.
+constexpr int SYM_TILE = 64;
+constexpr int SYM_QUAD = 128;
+constexpr int64_t SYM_QUAD_N = 5600;
 
 struct SymGrid {
   int64_t S, ns, njobs, nwg;
   static SymGrid make(int64_t n) {
     SymGrid g;
+    if (n <= SYM_QUAD_N) {
+      g.S = SYM_QUAD;
+      g.ns = ceil_div(n, SYM_QUAD);
+      g.njobs = g.nwg = g.ns * (g.ns + 1) / 2;
+      return g;
+    }
     // largest S in {1024, 512, 256} that still gives each workgroup >= 4 jobs
     int64_t S = SYM_MAX_S;
     while (S > 256) {
@@ -672,6 +689,168 @@ __global__ __launch_bounds__(256, 2) void rep_sym_kernel(const float2* __restric
   if (tid == 0) Zblock[blockIdx.x] = bz;
 }
 
+// Attraction of one entry of a job of S x S points (see rep_sym_kernel), to
+// the fixed-point sums A: i x, i y, j x, j y.
+template <int S>
+__device__ __forceinline__ void att_entry(const float2* ip, const float2* jp, uint32_t pk, float pv,
+                                          unsigned long long* A) {
+  const int il = int(pk & 0xFFFFu), jl = int(pk >> 16);
+  const float2 yi = ip[il], yj = jp[jl];
+  const float dx = yi.x - yj.x, dy = yi.y - yj.y;
+  const float c = pv * __builtin_amdgcn_rcpf(__builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, 1.0f)));
+  const long long fx = __float2ll_rn(c * dx * ATT_SCALE), fy = __float2ll_rn(c * dy * ATT_SCALE);
+  atomicAdd(&A[il], (unsigned long long)fx);
+  atomicAdd(&A[S + il], (unsigned long long)fy);
+  atomicAdd(&A[2 * S + jl], (unsigned long long)(-fx));
+  atomicAdd(&A[3 * S + jl], (unsigned long long)(-fy));
+}
+
+// One 64 x 64 tile by a wave, from LDS: the points of the i and the j
+// subblock; the sums of the i side to di and of the j side to dj (component
+// by component, 64 each, the caller's synchronisation before they are read).
+// diag: the blocks coincide (the i side takes all ordered pairs, dj nothing).
+// Returns the lane's sum of w, over ordered pairs if diag, else unordered.
+template <bool ZROW>
+__device__ __forceinline__ float tile_sums(const float2* ip, const float2* jp, bool diag, float* di, float* dj) {
+  const int lane = lane_id(), a = lane >> 3, b = lane & 7;
+  float xi[8], yi[8];
+  float4 jc[4];
+#pragma unroll
+  for (int r = 0; r < 8; r += 2) {
+    const float4 v = *reinterpret_cast<const float4*>(ip + 8 * a + r);
+    xi[r] = v.x;
+    yi[r] = v.y;
+    xi[r + 1] = v.z;
+    yi[r + 1] = v.w;
+    jc[r / 2] = *reinterpret_cast<const float4*>(jp + 8 * b + r);
+  }
+  float rix[8], riy[8], zi[8], rj[16], zj[8], z = 0.0f;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) rix[r] = riy[r] = zi[r] = 0.0f;
+  if (diag) sym_tile<true, ZROW, true, true>(xi, yi, jc, rix, riy, zi, rj, zj, z, a == b);
+  else sym_tile<false, ZROW, true, true>(xi, yi, jc, rix, riy, zi, rj, zj, z, false);
+  float vi[16], o0, o1;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    vi[r] = rix[r];
+    vi[8 + r] = riy[r];
+  }
+  rs16_lo(vi, o0, o1);
+  float* d = di + ((lane >> 2) & 1) * 64 + 8 * a + 2 * (lane & 1) + 4 * ((lane >> 1) & 1);
+  d[0] = o0;
+  d[1] = o1;
+  if (ZROW) di[2 * 64 + 8 * a + 4 * ((lane >> 2) & 1) + 2 * ((lane >> 1) & 1) + (lane & 1)] = rs8_lo(zi);
+  rs16_hi(rj, o0, o1);
+  d = dj + (lane >> 5) * 64 + 8 * b + 2 * ((lane >> 3) & 1) + 4 * ((lane >> 4) & 1);
+  d[0] = o0;
+  d[1] = o1;
+  if (ZROW) dj[2 * 64 + 8 * b + 4 * ((lane >> 5) & 1) + 2 * ((lane >> 4) & 1) + ((lane >> 3) & 1)] = rs8_hi(zj);
+  return z;
+}
+
+// The gradient's all-pairs pass for few points (SymGrid with S = 128): block q
+// takes job q, its four waves the four 64 x 64 tiles (the diagonal job has
+// three).  Partials, attraction sums and their layout are those of
+// rep_sym_kernel; Z partials one per block.  What bounds it: latency (the
+// points, the attraction list's range and entries, one tile of 64 pairs per
+// lane, two barriers, the partials).  One tile per wave with nothing shared
+// (superblocks of 64) was 2 to 14 % slower per iteration.
+template <bool ZROW, bool ATT>
+__global__ __launch_bounds__(256, 2) void rep_quad_kernel(const float2* __restrict__ Y, int64_t n, int64_t ns,
+                                                          float* __restrict__ part, float* __restrict__ zpart,
+                                                          double* __restrict__ Zblock, AttList att,
+                                                          float2* __restrict__ apart) {
+  static_assert(!(ATT && ZROW), "the fused attraction is for the gradient-only launch");
+  constexpr int S = SYM_QUAD, NC = ZROW ? 3 : 2;
+  __shared__ __attribute__((aligned(16))) float2 pts[2 * S];
+  __shared__ float acc[SYM_WAVES][2][NC * 64];
+  __shared__ unsigned long long aacc[ATT ? 4 * S : 1];
+  __shared__ double red[4];
+  const int tid = threadIdx.x, w = tid >> 6;
+  const int64_t q = blockIdx.x;
+  int64_t s, t;
+  job_pair(q, ns, s, t);
+  const bool diag = s == t;
+  const int64_t pt = (tid < S ? s * S : t * S - S) + tid;  // this thread's point (i side, then j side)
+  constexpr int EB = 2;                                    // attraction entries of a thread in flight
+  int64_t e0 = 0, e1 = 0;
+  uint32_t pk[EB];
+  float pv[EB];
+  auto entries = [&](int64_t e) {
+#pragma unroll
+    for (int u = 0; u < EB; ++u) {
+      const bool ok = e + 256 * u < e1;
+      pk[u] = ok ? att.ij[e + 256 * u] : 0u;
+      pv[u] = ok ? att.p[e + 256 * u] : 0.0f;
+    }
+  };
+  if (ATT) {
+    e0 = min(att.off[q], att.cap) + tid;
+    e1 = min(att.off[q + 1], att.cap);
+  }
+  pts[tid] = load_point(Y, pt, n);
+  if (ATT) {
+    entries(e0);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) aacc[ATT ? c * 256 + tid : 0] = 0ull;
+  }
+  __syncthreads();
+  if (ATT)
+    for (int64_t e = e0; e < e1; e += 256 * EB) {
+#pragma unroll
+      for (int u = 0; u < EB; ++u)
+        if (e + 256 * u < e1) att_entry<S>(pts, pts + S, pk[u], pv[u], aacc);
+      entries(e + 256 * EB);
+    }
+  // wave w: i subblock w & 1, j subblock w >> 1 (on the diagonal the pair
+  // (1, 0) is (0, 1) again)
+  const int us = w & 1, vs = w >> 1;
+  double zsum = 0.0;
+  const bool mine = !(diag && us > vs);
+  if (mine) {
+    const bool dt = diag && us == vs;
+    const float z = tile_sums<ZROW>(pts + 64 * us, pts + S + 64 * vs, dt, acc[w][0], acc[w][1]);
+    zsum = dt ? double(z) : 2.0 * double(z);
+  }
+  __syncthreads();
+  // thread: point tid & 127 of its side, the sums of the two waves that had
+  // its subblock
+  const int u = tid & 127, h = u >> 6, l = u & 63;
+  const int64_t other = tid < S ? t : s;
+  const int64_t idx = part_index(pt, other, ns, n, part_grouped(S));
+  float2* part2 = reinterpret_cast<float2*>(part);
+  if (diag) {
+    // both sides are the same points: the i side of (h, h), and (0, 1)'s i
+    // side for subblock 0, its j side for subblock 1
+    if (tid < S && pt < n) {
+      const float* own = acc[h ? 3 : 0][0];
+      const float* mix = acc[2][h];
+      const float sg = h ? -1.0f : 1.0f;
+      part2[idx] = make_float2(own[l] + sg * mix[l], own[64 + l] + sg * mix[64 + l]);
+      if (ZROW) zpart[idx] = own[128 + l] + mix[128 + l];
+    }
+  } else if (pt < n) {
+    const int side = tid < S ? 0 : 1;
+    const float* x0 = acc[side ? 2 * h : h][side];
+    const float* x1 = acc[side ? 2 * h + 1 : h + 2][side];
+    const float sg = side ? -1.0f : 1.0f;
+    part2[idx] = make_float2(sg * (x0[l] + x1[l]), sg * (x0[64 + l] + x1[64 + l]));
+    if (ZROW) zpart[idx] = x0[128 + l] + x1[128 + l];
+  }
+  if (ATT && pt < n && !(diag && tid >= S)) {
+    const double sc = 1.0 / double(ATT_SCALE);
+    const int c = tid < S ? 0 : 2 * S;
+    double ax = double((long long)aacc[ATT ? c + u : 0]), ay = double((long long)aacc[ATT ? c + S + u : 0]);
+    if (diag) {
+      ax += double((long long)aacc[ATT ? 2 * S + u : 0]);
+      ay += double((long long)aacc[ATT ? 3 * S + u : 0]);
+    }
+    apart[idx] = make_float2(float(ax * sc), float(ay * sc));
+  }
+  const double bz = block_sum_d(zsum, red);
+  if (tid == 0) Zblock[blockIdx.x] = bz;
+}
+
 // Z alone (the KL's forward): the sum of w over all ordered pairs i != j
 // with the decomposition, job dealing and diagonal tiles of rep_sym_kernel
 // but no per-point sums, so a pair costs the two differences, the two FMAs
@@ -771,6 +950,41 @@ __global__ __launch_bounds__(256) void zsum_sym_kernel(const float2* __restrict_
   }
   const double bz = block_sum_d(zsum, red);
   if (tid == 0) Zblock[blockIdx.x] = bz;
+}
+
+// The same for few points: one 64 x 64 tile per wave, ns = n / 64 up.
+static __global__ __launch_bounds__(256) void zsum_tile_kernel(const float2* __restrict__ Y, int64_t n, int64_t ns,
+                                                               double* __restrict__ Zblock) {
+  __shared__ double red[4];
+  const int lane = lane_id(), a = lane >> 3, b = lane & 7;
+  const int64_t q = int64_t(blockIdx.x) * SYM_WAVES + (threadIdx.x >> 6);
+  double zsum = 0.0;
+  if (q < ns * (ns + 1) / 2) {
+    int64_t s, t;
+    job_pair(q, ns, s, t);
+    float xi[8], yi[8];
+    float4 jc[4];
+#pragma unroll
+    for (int r = 0; r < 8; r += 2) {
+      const float2 p0 = load_point(Y, s * SYM_TILE + 8 * a + r, n), p1 = load_point(Y, s * SYM_TILE + 8 * a + r + 1, n);
+      const float2 j0 = load_point(Y, t * SYM_TILE + 8 * b + r, n), j1 = load_point(Y, t * SYM_TILE + 8 * b + r + 1, n);
+      xi[r] = p0.x;
+      yi[r] = p0.y;
+      xi[r + 1] = p1.x;
+      yi[r + 1] = p1.y;
+      jc[r / 2] = make_float4(j0.x, j0.y, j1.x, j1.y);
+    }
+    float z = 0.0f;
+    if (s == t) {
+      sym_tile_z<true>(xi, yi, jc, z, a == b);
+      zsum = double(z);
+    } else {
+      sym_tile_z<false>(xi, yi, jc, z, false);
+      zsum = 2.0 * double(z);
+    }
+  }
+  const double bz = block_sum_d(zsum, red);
+  if (threadIdx.x == 0) Zblock[blockIdx.x] = bz;
 }
 
 inline size_t rep_sym_lds_bytes(int64_t S, bool zrow, bool att) {

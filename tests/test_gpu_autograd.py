@@ -97,3 +97,17 @@ def test_fp32_forward_Z_and_kl_match_the_gradient_pass(dev, n):
     _, Zg, klg, _ = api.kl_grad(Y, P, 1.0, want_Z=True, want_kl=True)
     assert abs(Zf.item() - Zg.item()) <= 1e-6 * Zg.item()
     assert abs(C.item() - klg.item()) <= 1e-5 * max(1.0, abs(klg.item()))
+
+
+@pytest.mark.parametrize("n", [65, 128, 5600, 5601])
+def test_fp32_forward_small_sizes(dev, n):
+    # up to 5,600 points the Z-only pass takes one 64 x 64 tile per wave and
+    # the gradient pass 128-point superblocks (tolerances as above)
+    say("autograd fp32 Z, small sizes", n)
+    _, _, _, S = random_graph_P(n, 30, 10.0, 7 + n % 13)
+    P = sparse_to_dev(S, dev)
+    Y = to_dev(synth.random_embedding(n, 4.0, 11 + n % 7), dev)
+    C, Zf = api.kl_forward(Y, P.val, P)
+    _, Zg, klg, _ = api.kl_grad(Y, P, 1.0, want_Z=True, want_kl=True)
+    assert abs(Zf.item() - Zg.item()) <= 1e-6 * Zg.item()
+    assert abs(C.item() - klg.item()) <= 1e-5 * max(1.0, abs(klg.item()))

@@ -205,3 +205,38 @@ def test_fused_loop_late_schedule_c2(dev, t):
     tol_g = ROW_RTOL * 4.0 * (alpha * Aa + Ra / Zo)
     amb = check_step_rows(Yd.cpu().numpy(), Ud.cpu().numpy(), Gd.cpu().numpy(), Y, U, G, go, tol_g, 200.0, mom)
     assert amb <= 2 * n * 1e-3, amb
+
+
+# Up to 5,600 points a workgroup takes one pair of 128-point superblocks:
+# around the edges of its 64-point subblocks, and around 5,600; above it the
+# 256-point superblocks, with 1, 2 and 3 subblocks in the last one (the order
+# the jobs are dealt in changes between the latter two).
+@pytest.mark.parametrize("n", [5, 63, 64, 65, 127, 128, 129, 191, 193, 257, 5600, 5601, 5633, 5697, 5761])
+@pytest.mark.parametrize("zrow", [True, False])
+def test_klgrad_small_superblock_edges(dev, n, zrow):
+    say("klgrad small superblocks", n, zrow)
+    k = min(30, n - 1)
+    _, _, _, S = random_graph_P(n, k, min(10.0, k - 0.5), n)
+    compare(dev, S, synth.random_embedding(n, 5.0, n + 2), 3.0, zrow)
+
+
+@pytest.mark.parametrize("n", [5, 64, 129, 1500, 5600, 5601])
+def test_fused_attraction_small(dev, n):
+    # the fused launches of the same sizes, every row (see fused_first_iteration)
+    say("fused attraction small", n)
+    k = min(90, n - 1)
+    _, _, _, S = random_graph_P(n, k, min(30.0, k - 0.5), 11)
+    So = widen(S, S.val.astype(np.float32))
+    P = sparse_to_dev(So, dev)
+    Y = synth.random_embedding(n, 3.0, 3100 + n)
+    runs = []
+    for _ in range(2):
+        Yo = to_dev(Y, dev)
+        U, G = torch.zeros_like(Yo), torch.ones_like(Yo)
+        api.optimize(Yo, U, G, P, 0, 1, lr=200.0, exaggeration=12.0)
+        runs.append((Yo, U))
+    assert torch.equal(runs[0][0], runs[1][0]) and torch.equal(runs[0][1], runs[1][1])
+    go, Zo, _ = oracle.kl_grad(Y.astype(np.float64), So, 12.0)
+    g = -runs[0][1].cpu().numpy().astype(np.float64) / (200.0 * 0.8)
+    assert rel(g, go) <= GRAD_RTOL
+    check_grad_rows(g, go, Y.astype(np.float64), np.arange(n), So, 12.0, Zo)
