@@ -217,3 +217,36 @@ def test_umap_smallest_graph_and_most_negatives(dev):
     Yg = api.umap_layout(to_dev(Y0, dev), Gd, 1.5, 0.9, 20, 1.0, 64, seed=7, epochs=(10, 12))
     Yo = U.layout(Y0.astype(np.float64), rp, col, valf, 20, 1.5, 0.9, 1.0, 64, 7, epochs=(10, 12))
     assert np.abs(Yg.cpu().numpy() - Yo).max() <= 2 * step_tol(Y0, Yo)
+
+
+# Blocks of 128 rows take their entries 2048 at a time: complete graphs of
+# equal weights (every entry sampled in every epoch, so each chunk's list is
+# full; 127 to 129 rows and a last block of one), a star whose hub row spans
+# several chunks and all other rows hold one entry, and draws around the batch
+# of five negatives.  Epoch 190 of 200: FP32 steps against FP64, as above.
+@pytest.mark.parametrize("kind,n", [("complete", 127), ("complete", 128), ("complete", 129), ("complete", 257),
+                                    ("star", 5000)])
+@pytest.mark.parametrize("neg", [0, 4, 5, 6, 11])
+def test_umap_epoch_blocks(dev, kind, n, neg):
+    say("umap epoch blocks", kind, n, neg)
+    if kind == "complete":
+        col = np.array([[j for j in range(n) if j != i] for i in range(n)], np.int32).ravel()
+        rp = np.arange(n + 1, dtype=np.int64) * (n - 1)
+    else:
+        col = np.concatenate([np.arange(1, n), np.zeros(n - 1)]).astype(np.int32)
+        rp = np.concatenate([[0], n - 1 + np.arange(n)]).astype(np.int64)
+    val = np.full(col.size, 0.75, np.float32)
+    G = api.SparseP(to_dev(rp, dev), to_dev(col, dev), to_dev(val, dev), None, n)
+    a, b = U.fit_ab(0.5)
+    Y0 = synth.umap_init(n, 91)
+    Ys = api.umap_layout(to_dev(Y0, dev), G, a, b, 200, 1.0, neg, seed=5, epochs=(190, 191))
+    Yg = api.umap_layout(to_dev(Y0, dev), G, a, b, 200, 1.0, neg, seed=5, epochs=(190, 191), symmetric=False)
+    assert torch.equal(Ys, Yg)
+    Yo = U.layout_epoch(Y0.astype(np.float64), rp, col, val, 190, 200, a, b, 1.0, neg, 5)
+    # a row sums up to 5000 (1 + neg) steps of at most 4 alpha each, each off by
+    # FP32 rounding of its own (a few 2^-24 of it): bounded by the sum of the
+    # steps' sizes, which the largest displacement does not show
+    steps = np.diff(rp).max() * (2 + neg)
+    tol = 2e-6 * np.abs(Yo).max() + 2e-5 * np.abs(Yo - Y0).max() + 2e-7 * steps * 0.05 * 4.0
+    e = np.abs(Ys.cpu().numpy() - Yo).max()
+    assert e <= tol, (e, tol)
