@@ -15,6 +15,8 @@
 // (t nnz + e) neg_rate + p, vertex ((z >> 32) n) >> 32.
 #include <math.h>
 
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace tsne {
@@ -27,63 +29,128 @@ constexpr int UMAP_RED_BLOCKS = 256;
 
 // --- smoothed kNN weights ------------------------------------------------------
 
-// One thread per row: d_j = sqrt(d2_j) (FP64 from the FP32 squared
-// distances), rho = the smallest positive d_j (0 if none), sigma by FP64
-// bisection of sum_j exp(-max(0, d_j - rho) / sigma) = log2(k) on
-// [floor, hi] with floor = 1e-3 mean(d) (1e-3 when all d are 0; sigma stays
-// there when the floor already meets the target), w_j = exp(-max(0, d_j -
-// rho) / sigma).  The sum is monotone in sigma, so the bisection keeps the
-// root bracketed; it stops when the midpoint no longer moves.
-__device__ double umap_row_sum(const float* __restrict__ d2, int k, double rho, double s) {
-  double acc = 0.0;
-  for (int j = 0; j < k; ++j) {
-    const double x = sqrt(double(d2[j])) - rho;
-    acc += exp(-(x > 0.0 ? x : 0.0) / s);
-  }
-  return acc;
+// 16 lanes (a DPP row) per row: d_j = sqrt(d2_j) (FP64 from the FP32 squared
+// distances), rho = the smallest positive d_j (0 if none), sigma the FP64
+// root of f(sigma) = sum_j exp(-max(0, d_j - rho) / sigma) = log2(k) above
+// floor = 1e-3 mean(d) (1e-3 when all d are 0; sigma stays there when the
+// floor already meets the target), w_j = exp(-max(0, d_j - rho) / sigma).
+// What bounds it: FP64 exponentials.  In t = 1 / sigma, ln f is convex and
+// decreasing, so Newton steps in t from 0 rise to the root without passing it;
+// they take 6 to 9 evaluations of f to the last bit, where a bisection by one
+// thread per row took 55 (15.2 ms for 700,000 rows of 30, now WEIGHTS_MS).  A
+// row that they do not settle (non-finite distances) is bisected as before.
+constexpr int UMAP_NEWTON = 60;
+
+__device__ __forceinline__ double row16_sum_d(double v) {
+  auto add = [&](auto ctrl) {
+    constexpr int C = decltype(ctrl)::value;
+    const uint64_t q = __builtin_bit_cast(uint64_t, v);
+    const uint64_t o = (uint64_t(uint32_t(dpp_i<C>(int(uint32_t(q >> 32))))) << 32) | uint32_t(dpp_i<C>(int(uint32_t(q))));
+    v += __builtin_bit_cast(double, o);
+  };
+  add(std::integral_constant<int, 0x128>{});
+  add(std::integral_constant<int, 0x124>{});
+  add(std::integral_constant<int, 0x122>{});
+  add(std::integral_constant<int, 0x121>{});
+  return v;
 }
 
+template <int KPL>  // distances per lane
 __global__ __launch_bounds__(256) void umap_weights_kernel(const float* __restrict__ d2, int64_t n, int k,
                                                            float* __restrict__ rho_out, float* __restrict__ sigma_out,
                                                            float* __restrict__ w) {
-  const int64_t i = gtid();
-  if (i >= n) return;
+  const int64_t i = gtid() >> 4;
+  const int sl = lane_id() & 15;
+  if (i >= n) return;  // whole rows of 16 lanes
   const float* r = d2 + i * k;
   const double target = log2(double(k));
-  double rho = 0.0, sum = 0.0, xmax = 0.0;
-  bool any = false;
-  for (int j = 0; j < k; ++j) {
-    const double d = sqrt(double(r[j]));
-    sum += d;
-    if (d > 0.0 && (!any || d < rho)) {
-      rho = d;
-      any = true;
-    }
+  double x[KPL];
+  double rho = INFINITY, sum = 0.0;
+#pragma unroll
+  for (int u = 0; u < KPL; ++u) {
+    const int j = sl + 16 * u;
+    x[u] = j < k ? sqrt(double(r[j])) : 0.0;
+    sum += x[u];
+    if (x[u] > 0.0 && x[u] < rho) rho = x[u];
   }
-  for (int j = 0; j < k; ++j) {
-    const double x = sqrt(double(r[j])) - rho;
-    xmax = x > xmax ? x : xmax;
+  sum = row16_sum_d(sum);
+#pragma unroll
+  for (int m = 1; m < 16; m <<= 1) {
+    const double o = shfl_xor_d(rho, m);
+    rho = o < rho ? o : rho;
   }
+  bool any = false;  // a positive distance (rho may be infinite itself)
+#pragma unroll
+  for (int u = 0; u < KPL; ++u) any |= x[u] > 0.0;
+  any = (__ballot(any) >> (lane_id() & 48) & 0xFFFFull) != 0;
+  if (!any) rho = 0.0;
+  double xmax = 0.0;
+#pragma unroll
+  for (int u = 0; u < KPL; ++u) {
+    const double v = x[u] - rho;
+    x[u] = v > 0.0 ? v : 0.0;
+    xmax = x[u] > xmax ? x[u] : xmax;
+  }
+#pragma unroll
+  for (int m = 1; m < 16; m <<= 1) {
+    const double o = shfl_xor_d(xmax, m);
+    xmax = o > xmax ? o : xmax;
+  }
+  auto f = [&](double s) {
+    double acc = 0.0;
+#pragma unroll
+    for (int u = 0; u < KPL; ++u)
+      if (sl + 16 * u < k) acc += exp(-x[u] / s);
+    return row16_sum_d(acc);
+  };
   const double mean = sum / k;
   const double floor_s = mean > 0.0 ? 1e-3 * mean : 1e-3;
   double s = floor_s;
-  if (umap_row_sum(r, k, rho, floor_s) < target) {
-    double lo = floor_s, hi = fmax(2.0 * floor_s, xmax > 0.0 ? xmax : 1.0);
-    for (int it = 0; it < 2100 && umap_row_sum(r, k, rho, hi) < target; ++it) hi *= 2.0;
-    for (int it = 0; it < 200; ++it) {
-      const double mid = 0.5 * (lo + hi);
-      if (mid <= lo || mid >= hi) break;
-      if (umap_row_sum(r, k, rho, mid) < target) lo = mid;
-      else hi = mid;
+  if (f(floor_s) < target) {
+    double sx = 0.0;
+#pragma unroll
+    for (int u = 0; u < KPL; ++u) sx += x[u];
+    sx = row16_sum_d(sx);
+    const double lt = log(target);
+    double t = log(double(k) / target) * double(k) / sx;  // the step from t = 0
+    bool settled = false;
+    for (int it = 0; it < UMAP_NEWTON && t > 0.0 && t < INFINITY; ++it) {
+      double a = 0.0, b = 0.0;
+#pragma unroll
+      for (int u = 0; u < KPL; ++u) {
+        const double e = sl + 16 * u < k ? exp(-x[u] * t) : 0.0;
+        a += e;
+        b += e * x[u];
+      }
+      a = row16_sum_d(a);
+      b = row16_sum_d(b);
+      const double tn = t + (log(a) - lt) * a / b;
+      // at the root the steps are rounding, of either sign
+      settled = tn <= t * (1.0 + 4e-16);
+      if (!(tn > t)) break;
+      t = tn;
+      if (settled) break;
     }
-    s = 0.5 * (lo + hi);
+    s = 1.0 / t;
+    if (!settled || !(s > floor_s)) {
+      double lo = floor_s, hi = fmax(2.0 * floor_s, xmax > 0.0 ? xmax : 1.0);
+      for (int it = 0; it < 2100 && f(hi) < target; ++it) hi *= 2.0;
+      for (int it = 0; it < 200; ++it) {
+        const double mid = 0.5 * (lo + hi);
+        if (mid <= lo || mid >= hi) break;
+        if (f(mid) < target) lo = mid;
+        else hi = mid;
+      }
+      s = 0.5 * (lo + hi);
+    }
   }
-  rho_out[i] = float(rho);
-  sigma_out[i] = float(s);
-  for (int j = 0; j < k; ++j) {
-    const double x = sqrt(double(r[j])) - rho;
-    w[i * k + j] = float(exp(-(x > 0.0 ? x : 0.0) / s));
+  if (sl == 0) {
+    rho_out[i] = float(rho);
+    sigma_out[i] = float(s);
   }
+#pragma unroll
+  for (int u = 0; u < KPL; ++u)
+    if (sl + 16 * u < k) w[i * k + sl + 16 * u] = float(exp(-x[u] / s));
 }
 
 // --- layout ----------------------------------------------------------------------
@@ -409,8 +476,13 @@ extern "C" int tsne_umap_weights(const float* nbr_d2, int64_t n, int32_t k, floa
   if (!nbr_d2 || !rho || !sigma || !w || n < 1 || k < 1) return TSNE_ERR_INVALID_ARG;
   if (k > TSNE_MAX_K) return TSNE_ERR_UNSUPPORTED;
   TSNE_REQUIRE_GFX950();
-  hipLaunchKernelGGL(umap_weights_kernel, dim3(unsigned(ceil_div(n, 256))), dim3(256), 0, as_stream(stream), nbr_d2,
-                     n, k, rho, sigma, w);
+  auto kern = k <= 16   ? umap_weights_kernel<1>
+              : k <= 32 ? umap_weights_kernel<2>
+              : k <= 64 ? umap_weights_kernel<4>
+              : k <= 128 ? umap_weights_kernel<8>
+                         : umap_weights_kernel<16>;
+  hipLaunchKernelGGL(kern, dim3(unsigned(ceil_div(n, 16))), dim3(256), 0, as_stream(stream), nbr_d2, n, int(k), rho,
+                     sigma, w);
   TSNE_CHECK_LAUNCH();
   return TSNE_OK;
 }

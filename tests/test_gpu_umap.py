@@ -250,3 +250,34 @@ def test_umap_epoch_blocks(dev, kind, n, neg):
     tol = 2e-6 * np.abs(Yo).max() + 2e-5 * np.abs(Yo - Y0).max() + 2e-7 * steps * 0.05 * 4.0
     e = np.abs(Ys.cpu().numpy() - Yo).max()
     assert e <= tol, (e, tol)
+
+
+# 16 lanes take a row, with 1, 2, 4, 8 or 16 distances each: both sides of
+# every switch, rows of heavy-tailed distances, duplicates, zeros and ties
+# (sigma at its floor), and non-finite distances (which stay as they are: an
+# infinite distance makes the mean and so sigma infinite).  Tolerances as
+# above: FP32 rounding of FP64 values.
+@pytest.mark.parametrize("k", [1, 2, 3, 15, 16, 17, 32, 33, 64, 65, 128, 129, 256])
+def test_umap_weights_lane_splits(dev, k):
+    say("umap weights lane splits", k)
+    rng = np.random.default_rng(k)
+    d = np.concatenate([np.abs(1 + 0.2 * rng.standard_normal((60, k))) * 8, rng.exponential(1.0, (60, k)) ** 4,
+                        rng.uniform(1.0, 1.001, (20, k))])
+    d[3] = 0.0
+    d[4, : k // 2] = 0.0
+    d[5] = 2.5
+    d[6, 1:] = d[6, 0]
+    d[7] *= 1e-15
+    d[8] *= 1e15
+    d2 = np.sort(d * d, axis=1).astype(np.float32)
+    d2[9] = rng.permutation(d2[9])
+    rho, sigma, w = U.smooth_knn(np.sqrt(d2.astype(np.float64)))
+    g_rho, g_sigma, g_w = (t.cpu().numpy().astype(np.float64) for t in api.umap_weights(to_dev(d2, dev)))
+    np.testing.assert_allclose(g_rho, rho, rtol=6e-8, atol=0)
+    np.testing.assert_allclose(g_sigma, sigma, rtol=2e-7, atol=0)
+    np.testing.assert_allclose(g_w, w, rtol=2e-7, atol=1e-30)
+    bad = d2.copy()
+    bad[0, -1] = np.inf
+    b_rho, b_sigma, b_w = (t.cpu().numpy() for t in api.umap_weights(to_dev(bad, dev)))
+    assert np.isinf(b_sigma[0])
+    np.testing.assert_array_equal(b_w[1:], g_w[1:].astype(np.float32))
