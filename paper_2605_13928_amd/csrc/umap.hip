@@ -37,7 +37,7 @@ constexpr int UMAP_RED_BLOCKS = 256;
 // What bounds it: FP64 exponentials.  In t = 1 / sigma, ln f is convex and
 // decreasing, so Newton steps in t from 0 rise to the root without passing it;
 // they take 6 to 9 evaluations of f to the last bit, where a bisection by one
-// thread per row took 55 (15.2 ms for 700,000 rows of 30, now WEIGHTS_MS).  A
+// thread per row took 55 (15.2 ms for 700,000 rows of 30, now 0.64).  A
 // row that they do not settle (non-finite distances) is bisected as before.
 constexpr int UMAP_NEWTON = 60;
 
