@@ -238,7 +238,7 @@ int kl_forward_f32(const float* Y, int64_t n, const int64_t* row_ptr, const int3
   const int64_t nt = ceil_div(n, SYM_TILE);
   const int64_t nz = n <= SYM_QUAD_N ? ceil_div(nt * (nt + 1) / 2, SYM_WAVES) : g.nwg;
   const dim3 grid(static_cast<unsigned>(nz)), block(256);
-  if (n <= SYM_QUAD_N) hipLaunchKernelGGL(zsum_tile_kernel, grid, block, 0, s, Y2, n, nt, Zblock);
+  if (n <= SYM_QUAD_N) hipLaunchKernelGGL(zsum_tile_kernel<>, grid, block, 0, s, Y2, n, nt, Zblock);
   else if (g.S == 256) hipLaunchKernelGGL(zsum_sym_kernel<1>, grid, block, 0, s, Y2, n, g.ns, Zblock);
   else if (g.S == 512) hipLaunchKernelGGL(zsum_sym_kernel<2>, grid, block, 0, s, Y2, n, g.ns, Zblock);
   else hipLaunchKernelGGL(zsum_sym_kernel<4>, grid, block, 0, s, Y2, n, g.ns, Zblock);

@@ -953,8 +953,9 @@ __global__ __launch_bounds__(256) void zsum_sym_kernel(const float2* __restrict_
 }
 
 // The same for few points: one 64 x 64 tile per wave, ns = n / 64 up.
-static __global__ __launch_bounds__(256) void zsum_tile_kernel(const float2* __restrict__ Y, int64_t n, int64_t ns,
-                                                               double* __restrict__ Zblock) {
+template <int = 0>
+__global__ __launch_bounds__(256) void zsum_tile_kernel(const float2* __restrict__ Y, int64_t n, int64_t ns,
+                                                        double* __restrict__ Zblock) {
   __shared__ double red[4];
   const int lane = lane_id(), a = lane >> 3, b = lane & 7;
   const int64_t q = int64_t(blockIdx.x) * SYM_WAVES + (threadIdx.x >> 6);
