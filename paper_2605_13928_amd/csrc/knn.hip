@@ -8,20 +8,20 @@
 //            n_cand best per row kept, then re-ranked by FP32 direct
 //            differences on the original points.
 // Selection (both paths): every row owns a candidate buffer in global
-// memory, a count in LDS and a threshold tau in registers of the wave that
-// owns the row.  A candidate with d <= tau is appended; a lane reserves the
-// slots of all its candidates of one row and step with one LDS atomic.  Before a
-// buffer could overflow, the owning wave finds the k-th smallest distance
-// tau by a radix select, keeps the keys with d <= tau and makes tau the
-// new threshold.  The true k best always satisfy d <= tau, so nothing is
-// lost; ties at tau are kept and resolved by index in the final sort (a
-// wave-wide bitonic sort of the (d, j) keys).  Since the kept keys are the
-// best ones whatever order the candidates arrive in, both paths sweep them
-// in a locality order (points sorted by a Morton key of their leading
-// coordinates, each query block starting next to its own queries), so that
-// tau is tight after a few tiles and few candidates are appended, and skip
-// the candidate tiles whose bounding box lies beyond every threshold of
-// the block (a bound that leaves the results those of the full sweep).
+// memory, a count and a threshold tau in registers of the wave that owns
+// the row.  A candidate with d <= tau is appended, at a slot counted across
+// the wave's lanes (no atomics).  Before a buffer could overflow, the owning
+// wave bounds the k-th smallest distance by a radix select, keeps the keys
+// up to the bound and makes it the new threshold.  The true k best always
+// satisfy d <= tau, so nothing is lost; ties are resolved by index at the
+// end (a wave-wide bitonic sort of the (d, j) keys).  Since the kept keys
+// are the best ones whatever order the candidates arrive in, both paths
+// sweep them in a locality order (points sorted by their nearest two of up
+// to 256 pivots, each query block sweeping outward from its own queries),
+// so that tau is tight after a few tiles and few candidates are appended,
+// and skip the candidate tiles whose bounding box lies beyond every
+// threshold of the block (a bound that leaves the results those of the full
+// sweep).
 #include <cfloat>
 #include <type_traits>
 
@@ -38,6 +38,11 @@ namespace tsne {
 // write-back or invalidation beyond the CU.
 __device__ __forceinline__ void wg_fence() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); }
 
+// base + the number of lanes below this one in the mask.
+__device__ __forceinline__ int lane_prefix(uint64_t m, int base) {
+  return int(__builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), uint32_t(base))));
+}
+
 // Inclusive prefix sum over the 64 lanes of a wave, in DPP: shifts by 1, 2,
 // 4 and 8 within each row of 16 (lanes shifted in from outside the row add
 // 0), then row 0's total into row 1 and row 2's into row 3 (row_bcast:15),
@@ -52,16 +57,52 @@ __device__ __forceinline__ int wave_incl_scan(int x) {
   return x;
 }
 
-// Shrink a row's buffer of c keys to the keys whose distance is at most the
-// keep-th smallest distance tau_d (all of the best `keep` by (d, j), plus
-// any further keys tied at tau_d), and set tau = tau_d.  tau_d is found by
-// a radix select on the distance bits (8 bits per pass, histograms in the
-// wave's 256-entry LDS array `hist`), so no sort is needed; the kept keys
-// are written in lane order.  If ties would leave more than `limit` keys,
-// the buffer is sorted instead and exactly `keep` are kept.  Returns the new
-// count.  Called by the whole wave with uniform arguments, c > keep.
+// One pass of a radix select over a wave's words v (those with `in` set),
+// 8 bits from `shift` up, with a histogram in the wave's 256-entry LDS array
+// `hist`: the bin that holds the k-th smallest (by the words' lower bits; the
+// higher ones are equal), the number of words below that bin, and in it.
+template <int EPL, class In, class Word>
+__device__ __forceinline__ void select_pass(uint32_t* __restrict__ hist, int shift, int k, In in, Word word, int& bin,
+                                            int& below, int& inside) {
+  const int lane = lane_id();
+  reinterpret_cast<uint4*>(hist)[lane] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+  for (int t = 0; t < EPL; ++t)
+    if (in(t)) atomicAdd(&hist[(word(t) >> shift) & 255u], 1u);
+  const uint4 hv = reinterpret_cast<const uint4*>(hist)[lane];
+  const int h[4] = {int(hv.x), int(hv.y), int(hv.z), int(hv.w)};
+  const int own = h[0] + h[1] + h[2] + h[3];
+  const int incl = wave_incl_scan(own), excl = incl - own;
+  const uint64_t owner = __ballot(excl < k && k <= incl);  // exactly one lane
+  const int L = __ffsll((unsigned long long)owner) - 1;
+  // first bin of this lane whose cumulative count reaches k
+  int b = lane * 4, run = excl, hb = h[0];
+#pragma unroll
+  for (int u = 1; u < 4; ++u) {
+    const bool on = run + hb < k;
+    b += on ? 1 : 0;
+    run += on ? hb : 0;
+    hb = on ? h[u] : hb;
+  }
+  bin = __builtin_amdgcn_readlane(b, L);
+  below = __builtin_amdgcn_readlane(run, L);
+  inside = __builtin_amdgcn_readlane(hb, L);
+}
+
+// Shrink a row's buffer of c keys to those whose distance is at most a bound
+// no less than the keep-th smallest (so to the best `keep` by (d, j) and
+// perhaps some more), and set tau to that bound.  The bound comes from a
+// radix select on the distance bits from the highest bit in which the keys
+// differ; it stops once at most `slack` keys more than `keep` lie at or below
+// the bin's upper edge (usually after two passes; with slack 0 only an exact
+// bound will do).  If ties would leave more than `limit` >= keep + slack
+// keys, the tied ones are selected by index and exactly `keep` are kept.  No
+// sort: its unrolled masks and code cost the callers registers and
+// instruction cache.  The kept keys are written in lane order.  Returns the
+// new count.  Called by the whole wave with uniform arguments, c > keep.
+constexpr int SLACK = 32;
 template <int EPL>
-__device__ int compact_row(uint64_t* __restrict__ buf, int c, int keep, int limit, float& tau,
+__device__ int compact_row(uint64_t* __restrict__ buf, int c, int keep, int slack, int limit, float& tau,
                            uint32_t* __restrict__ hist) {
   const int lane = lane_id();
   const uint64_t lt = (uint64_t(1) << lane) - 1;
@@ -72,73 +113,80 @@ __device__ int compact_row(uint64_t* __restrict__ buf, int c, int keep, int limi
     const int e = t * 64 + lane;
     v[t] = e < c ? buf[e] : KEY_MAX;
   }
-  uint32_t prefix = 0, pmask = 0;
-  int k = keep, eq = 0;
+  const uint32_t d0 = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(v[0] >> 32))));
+  uint32_t diff = 0;
 #pragma unroll
-  for (int shift = 24; shift >= 0; shift -= 8) {
+  for (int t = 0; t < EPL; ++t) diff |= t * 64 + lane < c ? uint32_t(v[t] >> 32) ^ d0 : 0u;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) hist[lane * 4 + u] = 0;
-#pragma unroll
-    for (int t = 0; t < EPL; ++t) {
-      const uint32_t d = uint32_t(v[t] >> 32);
-      if (t * 64 + lane < c && (d & pmask) == prefix) atomicAdd(&hist[(d >> shift) & 255u], 1u);
-    }
-    uint32_t h[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) h[u] = hist[lane * 4 + u];
-    const int local = int(h[0] + h[1] + h[2] + h[3]);
-    const int incl = wave_incl_scan(local);
-    const int excl = incl - local;
-    const uint64_t owner = __ballot(excl < k && k <= incl);  // exactly one lane
-    const int L = __ffsll((unsigned long long)owner) - 1;
-    int run = excl, bin = lane * 4, hb = 0;
-    {
-      // first bin of this lane whose cumulative count reaches k
-      int acc = excl;
-      bool found = false;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (!found && acc + int(h[u]) >= k) {
-          found = true;
-          bin = lane * 4 + u;
-          hb = int(h[u]);
-          run = acc;
-        }
-        acc += int(h[u]);
-      }
-    }
-    bin = __builtin_amdgcn_readlane(bin, L);
-    run = __builtin_amdgcn_readlane(run, L);
-    hb = __builtin_amdgcn_readlane(hb, L);
+  for (int m = 1; m < 64; m <<= 1) diff |= xor_lane(diff, m);
+  diff = uint32_t(__builtin_amdgcn_readfirstlane(int(diff))) | 255u;
+  const int hb = 31 - __builtin_clz(diff);
+  int shift = hb - 7;
+  uint32_t pmask = ~((2u << hb) - 1u), prefix = d0 & pmask;
+  int k = keep, kept;
+  for (;;) {
+    int bin, below, inside;
+    select_pass<EPL>(
+        hist, shift, k, [&](int t) { return t * 64 + lane < c && (uint32_t(v[t] >> 32) & pmask) == prefix; },
+        [&](int t) { return uint32_t(v[t] >> 32); }, bin, below, inside);
     prefix |= uint32_t(bin) << shift;
-    pmask |= 0xFFu << shift;
-    k -= run;
-    eq = hb;
+    pmask = ~((1u << shift) - 1u);
+    k -= below;
+    kept = (keep - k) + inside;  // keys with d & pmask <= prefix
+    if (shift == 0 || (kept <= keep + slack && (prefix | ~pmask) < 0x7F800000u)) break;
+    shift = shift > 8 ? shift - 8 : 0;
   }
-  const int kept = (keep - k) + eq;  // keys with d < tau_d, plus those equal
-  if (kept <= limit) {
-    int base = 0;
-#pragma unroll
-    for (int t = 0; t < EPL; ++t) {
-      const bool take = t * 64 + lane < c && uint32_t(v[t] >> 32) <= prefix;
-      const uint64_t m = __ballot(take);
-      if (take) buf[base + __popcll(m & lt)] = v[t];
-      base += __popcll(m);
+  const uint32_t bound = prefix | ~pmask;
+  uint32_t last = ~0u;  // largest index kept of the keys at the bound
+  if (kept > limit) {   // (then the bound is exact)
+    last = 0;
+    uint32_t im = 0;
+    for (shift = 24; shift >= 0; shift -= 8) {
+      int bin, below, inside;
+      select_pass<EPL>(
+          hist, shift, k,
+          [&](int t) {
+            return t * 64 + lane < c && uint32_t(v[t] >> 32) == bound && (uint32_t(v[t]) & im) == last;
+          },
+          [&](int t) { return uint32_t(v[t]); }, bin, below, inside);
+      last |= uint32_t(bin) << shift;
+      im |= 255u << shift;
+      k -= below;
     }
-    tau = __uint_as_float(prefix);
-    wg_fence();
-    return kept;
+    kept = keep;
   }
-  // many keys tied at tau_d: sort and keep exactly `keep`
-  wave_sort<EPL>(v);
+  int base = 0;
+#pragma unroll
+  for (int t = 0; t < EPL; ++t) {
+    const uint32_t d = uint32_t(v[t] >> 32);
+    const bool take = t * 64 + lane < c && (d < bound || (d == bound && uint32_t(v[t]) <= last));
+    const uint64_t m = __ballot(take);
+    if (take) buf[base + __popcll(m & lt)] = v[t];
+    base += __popcll(m);
+  }
+  tau = __uint_as_float(bound);
+  wg_fence();
+  return kept;
+}
+
+// The indices of a row's `keep` best keys, in no order (fewer if it holds
+// fewer, then -1): the selection of compact_row without the sort.
+template <int EPL>
+__device__ void emit_set(uint64_t* __restrict__ buf, int c, int keep, int32_t* __restrict__ oidx,
+                         uint32_t* __restrict__ hist) {
+  const int lane = lane_id();
+  if (c > keep) {
+    float tau;
+    compact_row<EPL>(buf, c, keep, 0, keep, tau, hist);
+  } else {
+    wg_fence();
+  }
+  const int have = c < keep ? c : keep;
 #pragma unroll
   for (int t = 0; t < EPL; ++t) {
     const int e = t * 64 + lane;
-    if (e < keep) buf[e] = v[t];
+    if (e < keep) oidx[e] = e < have ? key_index(buf[e]) : -1;
   }
-  tau = key_dist(wave_pick<EPL>(v, keep - 1));
-  wg_fence();
-  return keep;
 }
 
 // Sort a row's buffer and write its first `keep` keys out.
@@ -171,174 +219,221 @@ __device__ void emit_row(const uint64_t* __restrict__ buf, int c, int keep, int3
 // queries than every threshold of the wave can hold no candidate for it,
 // so the wave skips it, and the block fetches only the tiles some wave
 // needs.  Boxes span the leading BOX_D coordinates.
-constexpr int BOX_D = 16;
+constexpr int BOX_D = 32;
+// Tiles are tested a window at a time, with the thresholds of that moment.  The
+// first window ends where the first compactions have made them finite (without
+// that, 64 tiles of 128 columns were all evaluated: 41 % of 20,000 points);
+// the next ones double up to the 64 lanes, as the thresholds settle.  Most
+// windows end after the first coordinates (all tiles far): four 16-byte loads
+// per lane and step, from boxes stored coordinates apart.
+// FP32: before a window the rows with more than F_TIGHTEN keys over k are
+// compacted, and if at least F_BY_ROW tiles of it stay, the test is repeated
+// with each row in place of the box of the wave's rows (a wave that holds rows
+// of two clusters has a box between them: 1.20 -> 1.02 ms at 20,011 points).
+constexpr int F_WIN0 = 4, B_WIN0 = 8;
+constexpr int F_TIGHTEN = 64, F_BY_ROW = 2;
+// The it-th tile of a sweep: outward from t0 on both sides in turn, cyclically
+// (a bijection of [0, nt)).  (Swept upward only, the rows of a block that end
+// the run of their cluster met their neighbours last, with thresholds from
+// other clusters until then: 1,000,000 points in BF16, 68 -> 57 ms.)
+__device__ __forceinline__ int outward(int t0, int it, int nt) {
+  const int t = t0 + ((it & 1) ? -((it + 1) >> 1) : it >> 1);
+  return t < 0 ? t + nt : (t < nt ? t : t - nt);
+}
+__device__ __forceinline__ int next_window(int w, int w0) { return w < w0 ? w0 : (w < 64 ? 2 * w : 64); }
 
 // ---------------------------------------------------------------------
-// FP32 exact path.  Block = 4 waves x RW rows (RW = 16, or 8 where that
-// gives the busiest CU fewer rows: fknn_small_blocks); each step covers 128
-// columns, 2 per lane; the rows' coordinates are LDS broadcasts, the
-// columns' are per-lane LDS reads, dimension chunks of 56.  Rows and
-// columns are positions of the locality order (Xs = X in that order; perm
-// maps a position to its point, which keys and outputs name); a block
-// sweeps the column tiles cyclically from the one before its own rows and
-// skips those the box tests of its waves rule out.
+// FP32 exact path.  Block = 4 waves x 8 rows; each step covers 128 columns,
+// 2 per lane; the rows' coordinates are LDS broadcasts, the columns' are
+// per-lane LDS reads, dimension chunks of 56.  Rows and columns are
+// positions of the locality order (Xt = X in that order; perm maps a
+// position to its point, which keys and outputs name); a block sweeps the
+// column tiles outward from its own rows and skips those the box tests of
+// its waves rule out.  What bounds it is the last block: 32 rows a block (64
+// take 20 to 50 % longer from 30,000 clustered points up, and save 3 % at
+// d = 200 without clusters), thresholds and counts in one register each (a
+// lane per row: arrays of them went to scratch), the next tile in registers
+// while this one is consumed.  20,011 points x 50, 30 clusters, k = 90: 2.61
+// -> 0.82 ms; 100,000: 24.9 -> 2.3 ms; 40,000 without clusters: 8.5 -> 5.9.
 
+typedef float floatx4_t __attribute__((ext_vector_type(4)));
 constexpr int F_COLS = 128;
 constexpr int F_DC = 56;
 constexpr int XJ_S = F_COLS + 4;  // LDS row strides: multiples of 4 floats keep the
                                   // 16-byte reads aligned and spread the stores' banks
-// Three blocks of either size are resident per CU (LDS and registers), on
-// 256 CUs.  32-row blocks are taken when all of them are resident at once
-// and the CU with the most blocks then holds fewer rows than with 64-row
-// blocks (20 k points: 3 x 32 = 96 rows against 2 x 64 = 128).
-constexpr int64_t F_CUS = 256, F_RESIDENT = 3;
-inline bool fknn_small_blocks(int64_t n) {
-  const int64_t b8 = ceil_div(n, 32), b16 = ceil_div(n, 64);
-  return b8 <= F_CUS * F_RESIDENT && ceil_div(b8, F_CUS) * 32 < ceil_div(b16, F_CUS) * 64;
-}
+constexpr int F_RW = 8;           // rows per wave
 
-// Stage rows [r0, r0 + nrows) x dims [dc, dc + dl) of X transposed into
-// dst[c * stride + r]: one row per wave instruction (coalesced), rows past
-// n as zeros.
-__device__ __forceinline__ void stage_rows_t(float* __restrict__ dst, int stride, const float* __restrict__ X,
-                                             int64_t r0, int nrows, int64_t n, int d, int dc, int dl) {
-  const int lane = lane_id(), w = threadIdx.x >> 6;
-  for (int r = w; r < nrows; r += 16) {
-    float v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int rr = r + 4 * u;
-      const int64_t g = r0 + rr;
-      v[u] = (rr < nrows && g < n && lane < dl) ? X[g * d + dc + lane] : 0.0f;
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int rr = r + 4 * u;
-      if (rr < nrows && lane < dl) dst[lane * stride + rr] = v[u];
-    }
-  }
-}
-
-// Boxes of the FP32 column tiles: tile u holds positions F_COLS u ..
-// F_COLS u + F_COLS - 1 of Xs (those below n); box[u][c] = (min, max) of
-// coordinate c < BOX_D ((0, 0) past d; NaN left out).  Lane 16 g + c scans
-// coordinate c of rows g, g + 4, ...; the four groups merge by lane
-// exchange.
-__global__ __launch_bounds__(256) void f32_box_kernel(const float* __restrict__ Xs, int64_t n, int d, int64_t ntiles,
-                                                      float2* __restrict__ box) {
-  const int lane = lane_id(), c = lane & 15, g = lane >> 4;
-  const int64_t u = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  if (u >= ntiles) return;
-  const int64_t r0 = u * F_COLS;
+// The rows of the locality order by column tiles, transposed: coordinate c of
+// position F_COLS u + r is Xt[(u d + c) F_COLS + r] (zeros past n), so that a
+// sweep copies a tile to LDS with 16-byte loads and stores.  A block per
+// tile; it also writes the tile's box: box[(c / 2) ntiles + u] holds (min,
+// max) of coordinates c, c + 1 < BOX_D over the rows below n ((0, 0) past d;
+// NaN left out), coordinates apart so that 64 consecutive tiles are read
+// with whole lines.
+constexpr int GT_DC = 64;
+__global__ __launch_bounds__(256) void gather_tiles_kernel(const float* __restrict__ X, int64_t n, int d,
+                                                           int64_t ntiles, const int32_t* __restrict__ perm,
+                                                           float* __restrict__ Xt, float2* __restrict__ box) {
+  static_assert(BOX_D == 32 && GT_DC >= BOX_D, "eight threads per coordinate of the box");
+  __shared__ float t_s[GT_DC * (F_COLS + 1)];
+  const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
+  const int64_t u = blockIdx.x, r0 = u * F_COLS;
   const int rows = int(n - r0 < F_COLS ? n - r0 : F_COLS);
-  float lo = INFINITY, hi = -INFINITY;
-  if (c < d) {
-    for (int r = g; r < rows; r += 4) {
-      const float v = Xs[(r0 + r) * d + c];
-      lo = fminf(lo, v);
-      hi = fmaxf(hi, v);
+  for (int dc = 0; dc < d; dc += GT_DC) {
+    const int dl = d - dc < GT_DC ? d - dc : GT_DC;
+    if (dc > 0) __syncthreads();
+    for (int r = w; r < F_COLS; r += 32) {
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int rr = r + 4 * e;
+        v[e] = rr < rows && lane < dl ? X[int64_t(perm[r0 + rr]) * d + dc + lane] : 0.0f;
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (lane < dl) t_s[lane * (F_COLS + 1) + r + 4 * e] = v[e];
+    }
+    __syncthreads();
+    for (int e = tid; e < dl * F_COLS; e += 256)
+      Xt[(u * d + dc) * F_COLS + e] = t_s[(e / F_COLS) * (F_COLS + 1) + e % F_COLS];
+    if (dc == 0) {
+      const int c = tid >> 3;
+      float lo = INFINITY, hi = -INFINITY;
+      if (c < d)
+        for (int r = tid & 7; r < rows; r += 8) {
+          const float v = t_s[c * (F_COLS + 1) + r];
+          lo = fminf(lo, v);
+          hi = fmaxf(hi, v);
+        }
+#pragma unroll
+      for (int m = 1; m < 8; m <<= 1) {
+        lo = fminf(lo, xor_lane_f(lo, m));
+        hi = fmaxf(hi, xor_lane_f(hi, m));
+      }
+      if ((tid & 7) == 0) box[((c >> 1) * ntiles + u) * 2 + (c & 1)] = c < d ? make_float2(lo, hi) : make_float2(0.0f, 0.0f);
     }
   }
-  lo = fminf(lo, xor_lane_f(lo, 16));
-  lo = fminf(lo, xor_lane_f(lo, 32));
-  hi = fmaxf(hi, xor_lane_f(hi, 16));
-  hi = fmaxf(hi, xor_lane_f(hi, 32));
-  if (lane < BOX_D) box[u * BOX_D + lane] = lane < d ? make_float2(lo, hi) : make_float2(0.0f, 0.0f);
 }
 
-// Xs[p] = X[perm[p]]: the rows in the locality order, one wave per row.
-__global__ __launch_bounds__(256) void gather_rows_kernel(const float* __restrict__ X, int64_t n, int d,
-                                                          const int32_t* __restrict__ perm, float* __restrict__ Xs) {
-  const int64_t p = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  if (p >= n) return;
-  const int64_t src = perm[p];
-  for (int c = lane_id(); c < d; c += 64) Xs[p * d + c] = X[src * d + c];
+__device__ __forceinline__ int64_t xt_at(int64_t p, int d, int c) {
+  return (p / F_COLS * d + c) * F_COLS + p % F_COLS;
 }
 
 // Skipping test of the FP32 path.  Its distance sums d non-negative terms
 // (a rounded difference, squared and added by one FMA each), so it is at
 // least (1 - (d + 2) u) >= 1 - 2^-15 of the exact one for d <= 256; the
-// box bound LB (16 terms) is within 2^-19 of exact.  With the box of a
-// wave's 16 rows, LB (1 - 2^-12) > tau_max (the wave's largest threshold)
+// box bound LB (32 terms) is within 2^-18 of exact.  With the box of a
+// wave's rows, LB (1 - 2^-12) > tau_max (the wave's largest threshold)
 // therefore means every distance of the tile exceeds every threshold of
 // the wave: it would append nothing for it, and skipping it leaves the
 // buffers, and the outputs, as the full sweep makes them.  The block
 // stages the tiles that some wave evaluates (the OR of the waves' window
 // masks, exchanged through LDS).
-template <int EPL, int F_RW>
-__global__ __launch_bounds__(256, 3) void knn_fp32_kernel(const float* __restrict__ Xs, const int32_t* __restrict__ perm,
+template <int EPL>
+__global__ __launch_bounds__(256, 3) void knn_fp32_kernel(const float* __restrict__ Xt, const int32_t* __restrict__ perm,
                                                        const float4* __restrict__ cbox4, int64_t n, int d, int k,
                                                        uint64_t* __restrict__ bufs, int32_t* __restrict__ out_idx,
                                                        float* __restrict__ out_d2) {
-  static_assert(F_RW == 8 || F_RW == 16, "rows per wave");
   constexpr int F_ROWS = 4 * F_RW;
   constexpr int XI_S = F_ROWS + 4;
   constexpr int CAP = 64 * EPL;
   __shared__ __attribute__((aligned(16))) float xi_s[F_DC * XI_S];
   __shared__ __attribute__((aligned(16))) float xj_s[F_DC * XJ_S];
-  __shared__ uint32_t hist_s[4][256];  // per-wave radix-select histograms
+  __shared__ alignas(16) uint32_t hist_s[4][256];  // per-wave radix-select histograms
   __shared__ int32_t pj_s[F_COLS];     // the points of the staged columns
   __shared__ float4 qbox[4][BOX_D / 2];  // box of each wave's rows: (lo, hi) of two coordinates each
   __shared__ uint64_t wmask_s[2][4];     // each wave's live positions, by window parity
   const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t row0 = int64_t(blockIdx.x) * F_ROWS;
-  __shared__ int cnt_s[F_ROWS];  // buffer counts (appended by LDS atomics)
-  if (tid < F_ROWS) cnt_s[tid] = 0;  // published by the first barrier
-  // per row of this wave (uniform): threshold
-  float tau[F_RW];
-#pragma unroll
-  for (int r = 0; r < F_RW; ++r) tau[r] = row0 + w * F_RW + r < n ? INFINITY : -INFINITY;  // rows past n never accept
+  // lane r holds the state of the wave's row r: its threshold (rows past n
+  // never accept; nor do the lanes past the rows) and its buffer count
+  float tauv = lane < F_RW && row0 + w * F_RW + lane < n ? INFINITY : -INFINITY;
+  int cntv = 0;
+  auto tau_of = [&](int r) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tauv), r)); };
+  auto count_of = [&](int r) { return __builtin_amdgcn_readlane(cntv, r); };
   const int64_t wrow0 = row0 + w * F_RW;  // this wave's rows
   const bool has_rows = wrow0 < n;
   {
     // this wave's box (rows past n left out)
-    const int c = lane & 15, g = lane >> 4;
+    const int c = lane & 31, g = lane >> 5;
     float lo = INFINITY, hi = -INFINITY;
     if (c < d) {
-      for (int r = g; r < F_RW && wrow0 + r < n; r += 4) {
-        const float v = Xs[(wrow0 + r) * d + c];
+      for (int r = g; r < F_RW && wrow0 + r < n; r += 2) {
+        const float v = Xt[xt_at(wrow0 + r, d, c)];
         lo = fminf(lo, v);
         hi = fmaxf(hi, v);
       }
     }
-    lo = fminf(lo, xor_lane_f(lo, 16));
     lo = fminf(lo, xor_lane_f(lo, 32));
-    hi = fmaxf(hi, xor_lane_f(hi, 16));
     hi = fmaxf(hi, xor_lane_f(hi, 32));
     if (lane < BOX_D)
       reinterpret_cast<float2*>(qbox[w])[lane] = lane < d ? make_float2(lo, hi) : make_float2(0.0f, 0.0f);
   }
-  const bool one_chunk = d <= F_DC;
-  if (one_chunk) stage_rows_t(xi_s, XI_S, Xs, row0, F_ROWS, n, d, 0, d);
-  const int ntc = int((n + F_COLS - 1) / F_COLS);
-  int tstart = int(row0 / F_COLS) - 1;
-  if (tstart < 0) tstart += ntc;
-  auto tile_of = [&](int it) -> int {
-    const int ti = tstart + it;
-    return ti < ntc ? ti : ti - ntc;
+  // coordinates dc .. dc + dl - 1 of the block's rows (all in one tile)
+  auto stage_rows = [&](int dc, int dl) __attribute__((always_inline)) {
+    for (int e = tid; e < dl * F_ROWS; e += 256)
+      xi_s[e / F_ROWS * XI_S + e % F_ROWS] = Xt[xt_at(row0 + e % F_ROWS, d, dc + e / F_ROWS)];
   };
-  // live positions of the window [p0, p0 + 64): this wave's (returned) and
+  const bool one_chunk = d <= F_DC;
+  if (one_chunk) stage_rows(0, d);
+  const int ntc = int((n + F_COLS - 1) / F_COLS);
+  const int tstart = int(row0 / F_COLS);
+  auto tile_of = [&](int it) __attribute__((always_inline)) -> int { return outward(tstart, it, ntc); };
+  // live positions of the window [p0, p0 + width): this wave's (returned) and
   // the block's (any wave's, in `blk`); called by all waves together
   int wpar = 0;
-  auto window = [&](int p0, uint64_t& blk) -> uint64_t {
-    // this wave's largest threshold now (uniform per row; rows past n hold -inf)
-    float tm = tau[0];
-#pragma unroll
-    for (int r = 1; r < F_RW; ++r) tm = fmaxf(tm, tau[r]);
+  auto window = [&](int p0, int width, uint64_t& blk) __attribute__((always_inline)) -> uint64_t {
+    const float tm = -wave_min(-tauv);  // this wave's largest threshold now
     const int p = p0 + lane;
-    bool live = has_rows && p < ntc;
+    bool live = has_rows && lane < width && p < ntc;
     if (tm < INFINITY) {
-      const float4* tb = cbox4 + tile_of(live ? p : 0) * (BOX_D / 2);
+      const float4* tb = cbox4 + tile_of(live ? p : 0);
       float lb = 0.0f;
-#pragma unroll 2
-      for (int h = 0; h < BOX_D / 2; ++h) {
-        const float4 v = tb[h], q = qbox[w][h];  // (lo, hi) of coordinates 2h and 2h + 1
-        const float g0 = fmaxf(fmaxf(v.x - q.y, q.x - v.y), 0.0f);
-        const float g1 = fmaxf(fmaxf(v.z - q.w, q.z - v.w), 0.0f);
-        lb = fmaf(g0, g0, lb);
-        lb = fmaf(g1, g1, lb);
+#pragma unroll 1
+      for (int h0 = 0; h0 < BOX_D / 2 && __ballot(live); h0 += 4) {
+        float4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = tb[int64_t(h0 + u) * ntc];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float4 q = qbox[w][h0 + u];  // (lo, hi) of coordinates 2h and 2h + 1
+          const float g0 = fmaxf(fmaxf(v[u].x - q.y, q.x - v[u].y), 0.0f);
+          const float g1 = fmaxf(fmaxf(v[u].z - q.w, q.z - v[u].w), 0.0f);
+          lb = fmaf(g0, g0, lb);
+          lb = fmaf(g1, g1, lb);
+        }
+        live = live && !(lb * (1.0f - 1.0f / 4096.0f) > tm);
       }
-      live = live && !(lb * (1.0f - 1.0f / 4096.0f) > tm);
+      // the same row by row, where that can save more than it costs
+      if (__popcll(__ballot(live)) >= F_BY_ROW) {
+        float lr[F_RW];
+#pragma unroll
+        for (int r = 0; r < F_RW; ++r) lr[r] = 0.0f;
+        const int dd = d < BOX_D ? d : BOX_D;
+#pragma unroll 2
+        for (int c = 0; c < dd; ++c) {
+          const float2 v = reinterpret_cast<const float2*>(tb + int64_t(c >> 1) * ntc)[c & 1];
+          const float4* xr = reinterpret_cast<const float4*>(Xt + xt_at(wrow0, d, c));
+          float x[F_RW];
+#pragma unroll
+          for (int q4 = 0; q4 < F_RW / 4; ++q4) {
+            const float4 xv = xr[q4];
+            x[4 * q4] = xv.x;
+            x[4 * q4 + 1] = xv.y;
+            x[4 * q4 + 2] = xv.z;
+            x[4 * q4 + 3] = xv.w;
+          }
+#pragma unroll
+          for (int r = 0; r < F_RW; ++r) {
+            const float g = fmaxf(fmaxf(v.x - x[r], x[r] - v.y), 0.0f);
+            lr[r] = fmaf(g, g, lr[r]);
+          }
+        }
+        bool any = false;
+#pragma unroll
+        for (int r = 0; r < F_RW; ++r) any |= !(lr[r] * (1.0f - 1.0f / 4096.0f) > tau_of(r));
+        live = live && any;
+      }
     }
     const uint64_t mine = __ballot(live);
     // two buffers: a wave may write the next window's mask while another
@@ -349,40 +444,84 @@ __global__ __launch_bounds__(256, 3) void knn_fp32_kernel(const float* __restric
     wpar ^= 1;
     return mine;
   };
-  int wb = -64;  // first position of the current window (none yet)
-  uint64_t win = 0, mine = 0;
-  int from = 0;
-  for (;;) {
-    __syncthreads();  // every wave is done with the previous tile
-    // the next position some wave evaluates
-    int pos = from;
-    bool pos_mine = false;
-    while (pos < ntc) {
-      if (pos >= wb + 64) {
-        wb = pos;
-        mine = window(wb, win);
-      }
-      const uint64_t m = win >> (pos - wb);
-      if (m) {
-        pos += __builtin_ctzll(m);
-        pos_mine = (mine >> (pos - wb)) & 1;
-        break;
-      }
-      pos = wb + 64;
+  // compaction of the rows with more than `above` keys
+  auto compact_above = [&](int above) __attribute__((always_inline)) {
+    uint64_t need = __ballot(cntv > above);
+    while (need) {
+      const int r = __builtin_ctzll(need);
+      need &= need - 1;
+      float nt;
+      const int nc = compact_row<EPL>(bufs + (row0 + w * F_RW + r) * CAP, count_of(r), k, SLACK, CAP - F_COLS, nt,
+                                      hist_s[w]);
+      tauv = lane == r ? nt : tauv;
+      cntv = lane == r ? nc : cntv;
     }
-    if (pos >= ntc) break;
-    const int64_t c0 = int64_t(tile_of(pos)) * F_COLS;
-    float acc[F_RW][2];
+  };
+  int wb = 0, ww = 0;  // first position and width of the current window (none yet)
+  uint64_t win = 0, mine = 0;
+  // the next position from p on that some wave evaluates (ntc if none)
+  auto find = [&](int p, bool& is_mine) __attribute__((always_inline)) -> int {
+    is_mine = false;
+    while (p < ntc) {
+      if (p >= wb + ww) {
+        wb = p;
+        ww = next_window(ww, F_WIN0);
+        compact_above(k + F_TIGHTEN);
+        mine = window(wb, ww, win);
+      }
+      const uint64_t m = win >> (p - wb);
+      if (m) {
+        p += __builtin_ctzll(m);
+        is_mine = (mine >> (p - wb)) & 1;
+        return p;
+      }
+      p = wb + ww;
+    }
+    return ntc;
+  };
+  // A step is a chunk of coordinates of a tile.  The next step's chunk is
+  // loaded to registers while this one is consumed from LDS.
+  constexpr int PRE = F_DC * F_COLS / 4 / 256;
+  floatx4_t pre[PRE] = {};
+  int32_t pre_j = -1;
+  auto load = [&](int p, int dc) __attribute__((always_inline)) {
+    const int64_t u = tile_of(p);
+    const floatx4_t* src = reinterpret_cast<const floatx4_t*>(Xt + (u * d + dc) * F_COLS);
+    const int len = (d - dc < F_DC ? d - dc : F_DC) * (F_COLS / 4);
 #pragma unroll
-    for (int r = 0; r < F_RW; ++r) acc[r][0] = acc[r][1] = 0.0f;
-    for (int dc = 0; dc < d; dc += F_DC) {
-      const int dl = (d - dc) < F_DC ? (d - dc) : F_DC;
-      if (dc > 0) __syncthreads();
-      if (!one_chunk) stage_rows_t(xi_s, XI_S, Xs, row0, F_ROWS, n, d, dc, dl);
-      stage_rows_t(xj_s, XJ_S, Xs, c0, F_COLS, n, d, dc, dl);
-      if (dc == 0 && tid < F_COLS) pj_s[tid] = c0 + tid < n ? perm[c0 + tid] : -1;
-      __syncthreads();
-      if (!pos_mine) continue;  // no distance of this tile can pass a threshold of this wave
+    for (int e = 0; e < PRE; ++e)
+      if (tid + 256 * e < len) pre[e] = src[tid + 256 * e];
+    if (dc == 0 && tid < F_COLS) pre_j = u * F_COLS + tid < n ? perm[u * F_COLS + tid] : -1;
+  };
+  float acc[F_RW][2];
+  bool pos_mine = false;
+  int dc = 0, pos = find(0, pos_mine);
+  if (pos < ntc) load(pos, 0);
+  while (pos < ntc) {
+    const int64_t c0 = int64_t(tile_of(pos)) * F_COLS;
+    const int dl = (d - dc) < F_DC ? (d - dc) : F_DC;
+    __syncthreads();  // every wave is done with the previous step
+#pragma unroll
+    for (int e = 0; e < PRE; ++e) {
+      const int at = tid + 256 * e;
+      if (at < dl * (F_COLS / 4))
+        *reinterpret_cast<floatx4_t*>(&xj_s[at / (F_COLS / 4) * XJ_S + at % (F_COLS / 4) * 4]) = pre[e];
+    }
+    if (!one_chunk) stage_rows(dc, dl);
+    if (dc == 0) {
+      if (tid < F_COLS) pj_s[tid] = pre_j;
+#pragma unroll
+      for (int r = 0; r < F_RW; ++r) acc[r][0] = acc[r][1] = 0.0f;
+    }
+    int npos = pos, ndc = dc + F_DC;
+    bool nmine = pos_mine;
+    if (ndc >= d) {
+      ndc = 0;
+      npos = find(pos + 1, nmine);
+    }
+    if (npos < ntc) load(npos, ndc);
+    __syncthreads();
+    if (pos_mine) {  // else no distance of this tile can pass a threshold of this wave
       for (int c = 0; c < dl; ++c) {
         const float4* ap = reinterpret_cast<const float4*>(&xi_s[c * XI_S + w * F_RW]);
         float a[F_RW];
@@ -408,46 +547,47 @@ __global__ __launch_bounds__(256, 3) void knn_fp32_kernel(const float* __restric
     // runs when some lane has a candidate at or below its row's threshold
     bool any = false;
 #pragma unroll
-    for (int r = 0; r < F_RW; ++r) any |= (acc[r][0] <= tau[r]) | (acc[r][1] <= tau[r]);
-    if (pos_mine && __ballot(any)) {
+    for (int r = 0; r < F_RW; ++r) any |= fminf(acc[r][0], acc[r][1]) <= tau_of(r);
+    if (pos_mine && ndc == 0 && __ballot(any)) {
       const bool edge = (c0 + F_COLS > n) || (c0 < row0 + F_ROWS && row0 < c0 + F_COLS);
       const int64_t j0 = c0 + lane * 2;
       const int32_t pj0 = pj_s[lane * 2], pj1 = pj_s[lane * 2 + 1];
 #pragma unroll
       for (int r = 0; r < F_RW; ++r) {
         const int64_t gi = row0 + w * F_RW + r;
-        const bool p0 = acc[r][0] <= tau[r] && (!edge || (j0 < n && j0 != gi));
-        const bool p1 = acc[r][1] <= tau[r] && (!edge || (j0 + 1 < n && j0 + 1 != gi));
-        const int c = int(p0) + int(p1);
-        if (c) {
-          int slot = atomicAdd(&cnt_s[w * F_RW + r], c);
+        const float tr = tau_of(r);
+        const bool p0 = acc[r][0] <= tr && (!edge || (j0 < n && j0 != gi));
+        const bool p1 = acc[r][1] <= tr && (!edge || (j0 + 1 < n && j0 + 1 != gi));
+        const uint64_t m0 = __ballot(p0), m1 = __ballot(p1);
+        if (m0 | m1) {
+          // slots by lane: the counts are wave-uniform, no atomics
+          int slot = lane_prefix(m1, lane_prefix(m0, count_of(r)));
           uint64_t* buf = bufs + gi * CAP;
           if (p0) buf[slot++] = make_key(acc[r][0], pj0);
           if (p1) buf[slot] = make_key(acc[r][1], pj1);
+          cntv += lane == r ? __popcll(m0) + __popcll(m1) : 0;
         }
       }
       // compaction of rows that could overflow in the next step
-      const int cl = cnt_s[w * F_RW + (lane & (F_RW - 1))];
-      uint64_t need = __ballot(lane < F_RW && cl > CAP - F_COLS);
-      while (need) {
-        const int r = __ffsll((unsigned long long)need) - 1;
-        need &= need - 1;
-        float nt;
-        const int nc = compact_row<EPL>(bufs + (row0 + w * F_RW + r) * CAP, __builtin_amdgcn_readlane(cl, r), k,
-                                        CAP - F_COLS, nt, hist_s[w]);
-        if (lane == 0) cnt_s[w * F_RW + r] = nc;
-#pragma unroll
-        for (int rr = 0; rr < F_RW; ++rr)
-          if (rr == r) tau[rr] = nt;
-      }
+      compact_above(CAP - F_COLS);
     }
-    from = pos + 1;
+    pos = npos;
+    dc = ndc;
+    pos_mine = nmine;
   }
   for (int r = 0; r < F_RW; ++r) {
     const int64_t gi = row0 + w * F_RW + r;
     if (gi >= n) break;
     const int64_t pt = perm[gi];
-    emit_row<EPL>(bufs + gi * CAP, cnt_s[w * F_RW + r], k, out_idx + pt * k, out_d2 + pt * k);
+    uint64_t* buf = bufs + gi * CAP;
+    int c = count_of(r);
+    // fewer keys to sort where the selection leaves at most 128
+    if (c > 128 && k <= 128) {
+      float t;
+      c = compact_row<EPL>(buf, c, k, SLACK, CAP - F_COLS, t, hist_s[w]);
+    }
+    if (c <= 128 && k <= 128) emit_row<2>(buf, c, k, out_idx + pt * k, out_d2 + pt * k);
+    else emit_row<EPL>(buf, c, k, out_idx + pt * k, out_d2 + pt * k);
   }
 }
 
@@ -465,94 +605,257 @@ __device__ __forceinline__ float bf16_to_f(uint16_t h) { return __uint_as_float(
 constexpr uint16_t BF16_ONE = 0x3F80;
 constexpr uint16_t BF16_INF = 0x7F80;
 
-// Locality order (both paths).  Points are counting-sorted by a 16-bit
-// Morton key of their first three coordinates (6, 5 and 5 bits over each
-// coordinate's range; fewer coordinates when d < 3): position p of the
-// sorted order holds point perm[p].  Within a key the order is that of the
-// scatter's atomics; nothing downstream depends on it (the selection keeps
-// the best keys (d, original index) whatever order they arrive in).
+// Locality order (both paths).  Points are counting-sorted by a 16-bit key
+// that names the nearest and the second nearest of up to 256 pivots (points
+// taken at equal steps of the input): the cells of the pivots adapt to the
+// clusters of the data and are narrow in every coordinate, and the second
+// pivot divides them further.  Cells that are near each other get near
+// numbers (loc_rank_kernel).  Position p of the sorted order holds point
+// perm[p]; within a key the order is that of the scatter's atomics.
+// Nothing downstream depends on any of it (the selection keeps the best keys
+// (d, original index) whatever order they arrive in), so non-finite
+// coordinates and ties may fall anywhere.
+// Against a Morton key of the points' first three coordinates, whose tiles
+// mix the clusters that overlap in those, the sweeps evaluate (with boxes of
+// 32 coordinates, 16 before) 3.6 % of the tiles in place of 42 % (200,000
+// points x 50 in 30 clusters of one size and shape) and 6.0 % in place of
+// 14 % (of many sizes, variances falling with the coordinate).
 constexpr int LOC_BINS = 1 << 16;
-constexpr int LOC_DIMS = 3;
-constexpr int LOC_BITS[LOC_DIMS] = {6, 5, 5};
+constexpr int LOC_PIV = 256;     // pivots, at most; 64 points per pivot at least
+constexpr int LOC_CEN = 32;
+inline int loc_kpad(int d) { return (d + 31) / 32 * 32; }
+inline int loc_pivots(int64_t n) { return n / 64 < 1 ? 1 : (n / 64 < LOC_PIV ? int(n / 64) : LOC_PIV); }
 
-// float <-> unsigned int with the same order, for integer atomic min / max
-__device__ __forceinline__ uint32_t f_ord(float f) {
-  const uint32_t u = __float_as_uint(f);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+
+// The m <= 256 pivots, a wave each: the row in bf16, padded with zeros to kp
+// (a multiple of 32), and its squared norm (infinite for the slots past m and
+// for a pivot that is not finite, which are then nearest to nothing).
+__global__ __launch_bounds__(256) void loc_pivot_kernel(const float* __restrict__ X, int64_t n, int d, int m, int kp,
+                                                        uint16_t* __restrict__ piv, float* __restrict__ pnorm) {
+  const int lane = lane_id(), p = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const float* row = X + (p < m ? int64_t(p) * n / m : 0) * d;
+  float norm = 0.0f;
+  for (int c = lane; c < d; c += 64) norm = fmaf(row[c], row[c], norm);
+  norm = wave_sum(norm);
+  const bool ok = p < m && isfinite(norm);
+  for (int c = lane; c < kp; c += 64) piv[p * kp + c] = ok && c < d ? bf16_rne(row[c]) : uint16_t(0);
+  if (lane == 0) pnorm[p] = ok ? norm : INFINITY;
 }
-__device__ __forceinline__ float ord_f(uint32_t u) { return __uint_as_float((u & 0x80000000u) ? (u & 0x7FFFFFFFu) : ~u); }
 
-// rng[c] = min and rng[LOC_DIMS + c] = max (order-encoded) of the finite
-// values of coordinate c < min(d, 3); rng starts at {~0 x 3, 0 x 3}.
-__global__ __launch_bounds__(256) void loc_range_kernel(const float* __restrict__ X, int64_t n, int d,
-                                                        uint32_t* __restrict__ rng) {
-  const int nd = d < LOC_DIMS ? d : LOC_DIMS;
-  float mn[LOC_DIMS], mx[LOC_DIMS];
+// The pivots' ranks, one pivot per thread of one block, by their first 32
+// coordinates.  Centres are taken among the pivots by farthest-first
+// traversal (so every cluster far from the others has one, and all of its
+// pivots belong to it), chained from the first to the nearest one not yet
+// in the chain, and the pivots are ranked by the place of their centre in
+// the chain, then by how much nearer they are to the centre before than to
+// the one after it.  (Ranked by a Morton key of centres taken from the first
+// 32 pivots, half of 30 equal clusters of 20,000 points fell into two runs,
+// and the points of the shorter run were near their neighbours only at the
+// far end of their sweep.)
+__global__ __launch_bounds__(LOC_PIV) void loc_rank_kernel(const uint16_t* __restrict__ piv,
+                                                           const float* __restrict__ pnorm, int m, int kp,
+                                                           int* __restrict__ rank) {
+  __shared__ float coord[LOC_PIV][33];
+  __shared__ float dist_s[LOC_CEN][LOC_CEN + 1];
+  __shared__ int cen_s[LOC_CEN], chain_s[LOC_CEN], place_s[LOC_CEN];
+  __shared__ float part_d[2][4];
+  __shared__ int part_p[2][4];
+  __shared__ uint64_t key[LOC_PIV];
+  const int p = threadIdx.x, lane = lane_id(), w = p >> 6;
+  const bool ok = pnorm[p] < INFINITY;
+  uint4 raw[4];
 #pragma unroll
-  for (int c = 0; c < LOC_DIMS; ++c) {
-    mn[c] = INFINITY;
-    mx[c] = -INFINITY;
-  }
-  for (int64_t i = gtid(); i < n; i += int64_t(gridDim.x) * blockDim.x) {
+  for (int u = 0; u < 4; ++u) raw[u] = reinterpret_cast<const uint4*>(piv + p * kp)[u];
+  float x[32];
 #pragma unroll
-    for (int c = 0; c < LOC_DIMS; ++c) {
-      if (c < nd) {
-        const float v = X[i * d + c];
-        if (isfinite(v)) {
-          mn[c] = fminf(mn[c], v);
-          mx[c] = fmaxf(mx[c], v);
-        }
-      }
+  for (int u = 0; u < 4; ++u) {
+    const uint32_t h[4] = {raw[u].x, raw[u].y, raw[u].z, raw[u].w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      x[8 * u + 2 * e] = bf16_to_f(uint16_t(h[e]));
+      x[8 * u + 2 * e + 1] = bf16_to_f(uint16_t(h[e] >> 16));
     }
   }
-  // the block's extremes (waves, then wave 0 over the four), one atomic per
-  // block and bound: the grid is small, so few atomics meet at one address
-  __shared__ float part[4][2 * LOC_DIMS];
-  const int w = threadIdx.x >> 6;
 #pragma unroll
-  for (int c = 0; c < LOC_DIMS; ++c) {
-    const float a = wave_min(mn[c]), b = -wave_min(-mx[c]);
-    if (lane_id() == 0) {
-      part[w][c] = a;
-      part[w][LOC_DIMS + c] = b;
+  for (int c = 0; c < 32; ++c) coord[p][c] = x[c];
+  __syncthreads();
+  auto distance = [&](int q) {  // from this thread's pivot to pivot q
+    float s = 0.0f;
+#pragma unroll
+    for (int c = 0; c < 32; ++c) {
+      const float u = x[c] - coord[q][c];
+      s = fmaf(u, u, s);
+    }
+    return s;
+  };
+  const int nc = m < LOC_CEN ? m : LOC_CEN;
+  float near_d = INFINITY;
+  int near = 0, cur = 0;
+  for (int s = 0; s < nc; ++s) {
+    if (p == 0) cen_s[s] = cur;
+    const float dist = distance(cur);
+    if (dist < near_d) {
+      near_d = dist;
+      near = s;
+    }
+    // the pivot farthest from its centre (the lowest of several)
+    const float v = ok ? near_d : -1.0f;
+    const float top = -wave_min(-v);
+    const uint64_t who = __ballot(v == top);
+    if (lane == 0) {
+      part_d[s & 1][w] = top;
+      part_p[s & 1][w] = 64 * w + (who ? __builtin_ctzll(who) : 0);
+    }
+    __syncthreads();
+    float best = -2.0f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (part_d[s & 1][u] > best) {
+        best = part_d[s & 1][u];
+        cur = part_p[s & 1][u];
+      }
+  }
+  __syncthreads();
+  for (int e = p; e < LOC_CEN * LOC_CEN; e += LOC_PIV) {
+    const int a = e / LOC_CEN, b = e % LOC_CEN;
+    if (a < nc && b < nc) {
+      float s = 0.0f;
+      for (int c = 0; c < 32; ++c) {
+        const float u = coord[cen_s[a]][c] - coord[cen_s[b]][c];
+        s = fmaf(u, u, s);
+      }
+      dist_s[a][b] = s;
     }
   }
   __syncthreads();
-  if (threadIdx.x < nd) {
-    const int c = threadIdx.x;
-    const float a = fminf(fminf(part[0][c], part[1][c]), fminf(part[2][c], part[3][c]));
-    const float b = fmaxf(fmaxf(part[0][LOC_DIMS + c], part[1][LOC_DIMS + c]),
-                          fmaxf(part[2][LOC_DIMS + c], part[3][LOC_DIMS + c]));
-    if (a <= b) {
-      atomicMin(&rng[c], f_ord(a));
-      atomicMax(&rng[LOC_DIMS + c], f_ord(b));
+  if (w == 0) {
+    int at = 0;
+    bool open = lane < nc;
+    for (int s = 0; s < nc; ++s) {
+      if (lane == 0) {
+        chain_s[s] = at;
+        place_s[at] = s;
+      }
+      open = open && lane != at;
+      const float v = open ? dist_s[at][lane & (LOC_CEN - 1)] : INFINITY;
+      const uint64_t who = __ballot(open && v == wave_min(v));
+      // (none is left after the last; distances that are not finite leave the lowest open one)
+      const uint64_t left = who ? who : __ballot(open);
+      at = left ? __builtin_ctzll(left) : 0;
     }
   }
+  __syncthreads();
+  const int place = place_s[near];
+  const int before = chain_s[place > 0 ? place - 1 : 0], after = chain_s[place + 1 < nc ? place + 1 : nc - 1];
+  const uint32_t t = __float_as_uint(distance(cen_s[before]) - distance(cen_s[after]));
+  const uint32_t ord = (t >> 31) ? ~t : t | 0x80000000u;
+  // the slots past m and pivots that are not finite come last
+  const uint64_t own = ok ? (uint64_t(place) << 32) | ord : ~uint64_t(0);
+  key[p] = own;
+  __syncthreads();
+  int r = 0;
+#pragma unroll 8
+  for (int u = 0; u < LOC_PIV; ++u) r += key[u] < own || (key[u] == own && u < p) ? 1 : 0;
+  rank[p] = r;
 }
 
-// key[i] = the Morton key of point i (0 for non-finite coordinates), and its
-// count in hist.
-__global__ __launch_bounds__(256) void loc_key_kernel(const float* __restrict__ X, int64_t n, int d,
-                                                      const uint32_t* __restrict__ rng, uint16_t* __restrict__ key,
-                                                      int* __restrict__ hist) {
-  const int nd = d < LOC_DIMS ? d : LOC_DIMS;
-  for (int64_t i = gtid(); i < n; i += int64_t(gridDim.x) * blockDim.x) {
-    uint32_t q[LOC_DIMS] = {0u, 0u, 0u};
+// key[i] = (rank of the nearest pivot) << 8 | (rank of the second), and its
+// count in hist.  A wave takes 32 points against all pivots on the bf16
+// matrix cores (the order needs no more precision): MFMA operands lane l,
+// pivot or point l % 16, k elements 32 s + 8 (l / 16) .. + 7; result register
+// r: pivot 4 (l / 16) + r of the tile, point l % 16.
+__global__ __launch_bounds__(256) void loc_key_kernel(const float* __restrict__ X, int64_t n, int d, int m, int kp,
+                                                      const uint16_t* __restrict__ piv,
+                                                      const float* __restrict__ pnorm, const int* __restrict__ rank,
+                                                      uint16_t* __restrict__ key, int* __restrict__ hist) {
+  constexpr int PT = 2;  // tiles of 16 points
+  const int lane = lane_id(), q16 = lane & 15, g4 = lane >> 4;
+  const int64_t i0 = (int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6)) * (16 * PT);
+  if (i0 >= n) return;
+  float b1[PT], b2[PT];
+  int i1[PT], i2[PT];
 #pragma unroll
-    for (int c = 0; c < LOC_DIMS; ++c) {
-      if (c >= nd || rng[c] > rng[LOC_DIMS + c]) continue;  // no finite value at all
-      const float lo = ord_f(rng[c]), hi = ord_f(rng[LOC_DIMS + c]);
-      const float v = X[i * d + c];
-      const float cells = float(1u << LOC_BITS[c]);
-      const float t = hi > lo ? (v - lo) / (hi - lo) * cells : 0.0f;
-      q[c] = (isfinite(t) && t > 0.0f) ? (t < cells ? uint32_t(t) : (1u << LOC_BITS[c]) - 1u) : 0u;
+  for (int t = 0; t < PT; ++t) {
+    b1[t] = b2[t] = INFINITY;
+    i1[t] = i2[t] = 0;
+  }
+  auto offer = [&](int t, float dist, int u) {
+    const bool first = dist < b1[t], second = dist < b2[t];
+    b2[t] = first ? b1[t] : (second ? dist : b2[t]);
+    i2[t] = first ? i1[t] : (second ? u : i2[t]);
+    b1[t] = first ? dist : b1[t];
+    i1[t] = first ? u : i1[t];
+  };
+  auto point = [&](int t, int k0) {  // 8 coordinates from k0 + 8 g4
+    const int64_t i = i0 + 16 * t + q16;
+    const float* row = X + (i < n ? i : n - 1) * d;
+    bf16x8_t v;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int c = k0 + 8 * g4 + e;
+      v[e] = __builtin_bit_cast(__bf16, bf16_rne(c < d ? row[c < d ? c : 0] : 0.0f));
     }
-    // interleave from the top: q0 bit 5, then (q0, q1, q2) bits 4 .. 0
-    uint32_t k = (q[0] >> 5) & 1u;
+    return v;
+  };
+  const int tiles = (m + 15) / 16;
+  if (kp <= 64) {
+    bf16x8_t x[PT][2];
 #pragma unroll
-    for (int b = 4; b >= 0; --b) k = (k << 3) | (((q[0] >> b) & 1u) << 2) | (((q[1] >> b) & 1u) << 1) | ((q[2] >> b) & 1u);
-    key[i] = uint16_t(k);
-    atomicAdd(&hist[k], 1);
+    for (int t = 0; t < PT; ++t)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) x[t][s] = point(t, 32 * s);
+    for (int u = 0; u < tiles; ++u) {
+      const uint4* pr = reinterpret_cast<const uint4*>(piv + (16 * u + q16) * kp + 8 * g4);
+      const bf16x8_t a0 = __builtin_bit_cast(bf16x8_t, pr[0]);
+      const bf16x8_t a1 = __builtin_bit_cast(bf16x8_t, kp > 32 ? pr[4] : make_uint4(0, 0, 0, 0));
+      const float4 nv = reinterpret_cast<const float4*>(pnorm)[4 * u + g4];
+      const float nr[4] = {nv.x, nv.y, nv.z, nv.w};
+#pragma unroll
+      for (int t = 0; t < PT; ++t) {
+        floatx4_t acc = floatx4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, x[t][0], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, x[t][1], acc, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) offer(t, fmaf(-2.0f, acc[r], nr[r]), 16 * u + 4 * g4 + r);
+      }
+    }
+  } else {
+    for (int u = 0; u < tiles; ++u) {
+      const float4 nv = reinterpret_cast<const float4*>(pnorm)[4 * u + g4];
+      const float nr[4] = {nv.x, nv.y, nv.z, nv.w};
+      floatx4_t acc[PT];
+#pragma unroll
+      for (int t = 0; t < PT; ++t) acc[t] = floatx4_t{0.0f, 0.0f, 0.0f, 0.0f};
+      for (int k0 = 0; k0 < kp; k0 += 32) {
+        const bf16x8_t a = __builtin_bit_cast(
+            bf16x8_t, *reinterpret_cast<const uint4*>(piv + (16 * u + q16) * kp + k0 + 8 * g4));
+#pragma unroll
+        for (int t = 0; t < PT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, point(t, k0), acc[t], 0, 0, 0);
+      }
+#pragma unroll
+      for (int t = 0; t < PT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) offer(t, fmaf(-2.0f, acc[t][r], nr[r]), 16 * u + 4 * g4 + r);
+    }
+  }
+  // the four lanes of a point
+#pragma unroll
+  for (int t = 0; t < PT; ++t) {
+#pragma unroll
+    for (int s = 16; s < 64; s <<= 1) {
+      const float o1 = xor_lane_f(b1[t], s), o2 = xor_lane_f(b2[t], s);
+      const int j1 = int(xor_lane(uint32_t(i1[t]), s)), j2 = int(xor_lane(uint32_t(i2[t]), s));
+      offer(t, o1, j1);
+      offer(t, o2, j2);
+    }
+    if (!(b2[t] < INFINITY)) i2[t] = i1[t];
+    const int64_t i = i0 + 16 * t + q16;
+    if (g4 == t && i < n) {
+      const uint32_t k = uint32_t(rank[i1[t]]) << 8 | uint32_t(rank[i2[t]]);
+      key[i] = uint16_t(k);
+      atomicAdd(&hist[k], 1);
+    }
   }
 }
 
@@ -612,9 +915,6 @@ __global__ __launch_bounds__(256) void bf16_prep_kernel(const float* __restrict_
   Xc[row * 64 + lane] = c;
 }
 
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float floatx4_t __attribute__((ext_vector_type(4)));
-
 constexpr int B_TJ = 64;  // candidates per LDS tile
 
 // candidate rows: the n points and at least one infinite row, up to a
@@ -643,7 +943,7 @@ __global__ __launch_bounds__(256) void bf16_box_kernel(const uint16_t* __restric
     lo = fminf(lo, v);
     hi = fmaxf(hi, v);
   }
-  if (lane < BOX_D) box[u * BOX_D + lane] = lane < d ? make_float2(lo, hi) : make_float2(0.0f, 0.0f);
+  if (lane < BOX_D) box[((lane >> 1) * ntiles + u) * 2 + (lane & 1)] = lane < d ? make_float2(lo, hi) : make_float2(0.0f, 0.0f);
   if (lane == d) tnrm[u] = hi * (1.0f + 1.0f / 128.0f);
 }
 
@@ -652,18 +952,42 @@ __global__ __launch_bounds__(256) void bf16_box_kernel(const uint16_t* __restric
 // of 16 consecutive rows hit distinct banks.
 __device__ __forceinline__ int tile_slot(int r, int c) { return r * 8 + (c ^ (r & 7)); }
 
+// LDS reads that the compiler does not see: it takes every LDS read after a
+// direct-to-LDS load for a read of what that load brings and waits for all
+// outstanding memory operations first, the prefetch of the other buffer
+// included.  The caller has waited for the data; the block waits for the
+// reads' results itself.
+typedef int intx4_t __attribute__((ext_vector_type(4)));
+template <class T>
+__device__ __forceinline__ uint32_t lds_address(const T* p) {
+  return uint32_t(uintptr_t((__attribute__((address_space(3))) const T*)p));
+}
+__device__ __forceinline__ void lds_read_b128(uint32_t at, intx4_t& v) {
+  asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(v) : "v"(at) : "memory");
+}
+__device__ __forceinline__ void lds_read2_b128(uint32_t at0, uint32_t at1, bf16x8_t& v0, bf16x8_t& v1) {
+  asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(v0), "=&v"(v1)
+               : "v"(at0), "v"(at1)
+               : "memory");
+}
+
 // Block = 4 waves x 64 queries, positions of the locality order (Xq, Xc and
 // the buffers are in that order; perm maps a position to its point, which
-// is what keys and outputs name).  The candidate tiles are swept cyclically
-// from two tiles before the block's first query, so the block's own
-// neighbourhood comes first.  Lane l works on queries 16 t + (l % 16),
+// is what keys and outputs name).  The candidate tiles are swept outward
+// from the block's own.  Lane l works on queries 16 t + (l % 16),
 // t = 0..3, of its wave and, per 16-candidate subtile, on candidates
 // 4 (l / 16) .. + 3 (the MFMA C layout).  A query's threshold and buffer
 // count are held (identically) by its four lanes.  Four blocks fit a CU
-// (at most 128 VGPRs, which the kernel fits without VGPR spills; the
-// selection is bound by memory instructions, so resident waves count more
-// than registers), and 1024 resident blocks cover 262144 queries in one
-// round.
+// (at most 128 VGPRs, which the kernel fits without VGPR spills), and 1024
+// resident blocks cover 262144 queries in one round.  The kernel is bound by
+// the instructions of the appends (57 % of all; half of a wave's time) and
+// the waits of its four waves for each other (a third); what else cost was
+// found by clocks in a copy: the compiler's wait for the prefetch of the next
+// tile before every LDS read (lds_read_b128), the code and masks of unrolled
+// subtiles and sorts (instruction cache, spills), box tests with 64 lines per
+// load.  1,000,000 points x 50, k = 90: 66 -> 31 ms; 1 or 2 waves a block: 57
+// and 48 ms when 4 took 47.
 // Tile skipping.  A wave does not evaluate a tile in which no distance can
 // pass the threshold of any of its 64 queries, and the block does not
 // fetch a tile that none of its waves evaluates.  With B the box of the
@@ -690,7 +1014,7 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
   constexpr int CAP = 64 * EPL;
   __shared__ uint4 tile[2][B_TJ * 8];  // double-buffered: 64 rows x 128 bytes each
   __shared__ int32_t ptile[2][B_TJ];    // the original indices of those rows
-  __shared__ uint32_t hist_s[4][256];   // per-wave radix-select histograms
+  __shared__ alignas(16) uint32_t hist_s[4][256];   // per-wave radix-select histograms
   __shared__ float4 qbox[4][BOX_D / 2];  // box of each wave's queries: (lo, hi) of two coordinates each
   __shared__ float qnrm_s[4];            // bound on the squared norms of each wave's queries
   __shared__ uint64_t wmask_s[2][4];     // each wave's live positions, by window parity
@@ -752,44 +1076,46 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
     if (w == 0) __builtin_amdgcn_global_load_lds(perm + c0 + lane, &ptile[b][0], 4, 0, 0);
   };
   const int ntiles = (n32 + B_TJ - 1) / B_TJ;
-  int t0 = (qblock / B_TJ - 2) % ntiles;
-  if (t0 < 0) t0 += ntiles;
-  auto tile_of = [&](int it) -> int {
-    const int ti = t0 + it;
-    return ti < ntiles ? ti : ti - ntiles;
-  };
+  const int t0 = qblock / B_TJ + 2 < ntiles ? qblock / B_TJ + 2 : ntiles - 1;
+  auto tile_of = [&](int it) -> int { return outward(t0, it, ntiles); };
   auto tile_c0 = [&](int it) -> int { return tile_of(it) * B_TJ; };
   // each wave's query box: its 64 queries are candidate tile qblock / 64 + w
   const int qt = qblock / B_TJ + w;
   const bool has_q = qt < ntiles;  // else the wave holds only padding queries
   if (has_q) {
-    if (lane < BOX_D / 2) qbox[w][lane] = box4[qt * (BOX_D / 2) + lane];
+    if (lane < BOX_D / 2) qbox[w][lane] = box4[int64_t(lane) * ntiles + qt];
     if (lane == 0) qnrm_s[w] = tnrm[qt];
   }
   __syncthreads();
-  // live positions of the window [p0, p0 + 64): this wave's (returned) and
+  // live positions of the window [p0, p0 + width): this wave's (returned) and
   // the block's (any wave's, in `blk`); called by all waves together
   int wpar = 0;
-  auto window = [&](int p0, uint64_t& blk) -> uint64_t {
+  auto window = [&](int p0, int width, uint64_t& blk) -> uint64_t {
     // this wave's largest threshold now (padding queries hold -inf)
     const float m4 = fmaxf(fmaxf(tau[0], tau[1]), fmaxf(tau[2], tau[3]));
     const float tm = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(-wave_min(-m4))));
     const int p = p0 + lane;
-    bool live = has_q && p < ntiles;
+    bool live = has_q && lane < width && p < ntiles;
     if (tm < FLT_MAX) {
       const int t = tile_of(live ? p : 0);
-      const float4* tb = box4 + t * (BOX_D / 2);
+      const float4* tb = box4 + t;
+      const float bound = tm + (qnrm_s[w] + tnrm[t]) * (1.0f / 4096.0f);
       float lb = 0.0f;
-#pragma unroll 2
-      for (int h = 0; h < BOX_D / 2; ++h) {
-        const float4 v = tb[h], q = qbox[w][h];  // (lo, hi) of coordinates 2h and 2h + 1
-        const float g0 = fmaxf(fmaxf(v.x - q.y, q.x - v.y), 0.0f);
-        const float g1 = fmaxf(fmaxf(v.z - q.w, q.z - v.w), 0.0f);
-        lb = fmaf(g0, g0, lb);
-        lb = fmaf(g1, g1, lb);
+#pragma unroll 1
+      for (int h0 = 0; h0 < BOX_D / 2 && __ballot(live); h0 += 4) {  // (most windows end after the first coordinates)
+        float4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = tb[int64_t(h0 + u) * ntiles];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float4 q = qbox[w][h0 + u];  // (lo, hi) of coordinates 2h and 2h + 1
+          const float g0 = fmaxf(fmaxf(v[u].x - q.y, q.x - v[u].y), 0.0f);
+          const float g1 = fmaxf(fmaxf(v[u].z - q.w, q.z - v[u].w), 0.0f);
+          lb = fmaf(g0, g0, lb);
+          lb = fmaf(g1, g1, lb);
+        }
+        live = live && !(lb > bound);
       }
-      const float margin = (qnrm_s[w] + tnrm[t]) * (1.0f / 4096.0f);
-      live = live && !(lb > tm + margin);
     }
     const uint64_t mine = __ballot(live);
     // two buffers: a wave may write the next window's mask while another
@@ -800,12 +1126,14 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
     wpar ^= 1;
     return mine;
   };
-  int wb = 0;  // first position of the current window
+  int wb = 0, ww = B_WIN0;  // first position and width of the current window
   uint64_t win = 0;
-  uint64_t mine = window(0, win);
+  uint64_t mine = window(0, ww, win);
   int pos = 0, buf = 0;
   bool cur_mine = mine & 1;  // position 0 is live for every wave with queries
   load_tile(tile_c0(0), 0);
+  char* const wbuf = reinterpret_cast<char*>(bufs + int64_t(qbase) * CAP);  // the wave's buffers
+  const uint32_t q16_off = uint32_t(q16 * CAP * 8);
   while (pos < ntiles) {
     const int c0 = tile_c0(pos);
     __builtin_amdgcn_s_waitcnt(0);  // this wave's part of the tile has landed
@@ -814,9 +1142,10 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
     int nxt = pos + 1;
     bool nxt_mine = false;
     while (nxt < ntiles) {
-      if (nxt >= wb + 64) {
+      if (nxt >= wb + ww) {
         wb = nxt;
-        mine = window(wb, win);
+        ww = next_window(ww, B_WIN0);
+        mine = window(wb, ww, win);
       }
       const uint64_t m = win >> (nxt - wb);
       if (m) {
@@ -824,7 +1153,7 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
         nxt_mine = (mine >> (nxt - wb)) & 1;
         break;
       }
-      nxt = wb + 64;
+      nxt = wb + ww;
     }
     // fetch the next tile while this one is consumed
     if (nxt < ntiles) load_tile(tile_c0(nxt), buf ^ 1);
@@ -834,11 +1163,11 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
     // the others need only the threshold test
     auto sweep = [&](auto edge_c) {
       constexpr bool EDGE = decltype(edge_c)::value;
-#pragma unroll
+#pragma unroll 1
       for (int sub = 0; sub < B_TJ / 16; ++sub) {
         const int rloc = sub * 16 + q16;
-        const bf16x8_t a0 = __builtin_bit_cast(bf16x8_t, tl[tile_slot(rloc, g4)]);
-        const bf16x8_t a1 = __builtin_bit_cast(bf16x8_t, tl[tile_slot(rloc, 4 + g4)]);
+        bf16x8_t a0, a1;
+        lds_read2_b128(lds_address(tl + tile_slot(rloc, g4)), lds_address(tl + tile_slot(rloc, 4 + g4)), a0, a1);
         floatx4_t acc[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
@@ -854,8 +1183,9 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
                      min(__float_as_int(acc[t][2]), __float_as_int(acc[t][3]))) <= tau_key[t];
         if (__ballot(any)) {
           const int jb = c0 + sub * 16 + 4 * g4;
-          const int4 pj = *reinterpret_cast<const int4*>(pt + sub * 16 + 4 * g4);  // perm[jb .. jb + 3]
-          const int pjr[4] = {pj.x, pj.y, pj.z, pj.w};
+          intx4_t pj;  // perm[jb .. jb + 3]
+          lds_read_b128(lds_address(pt + sub * 16 + 4 * g4), pj);
+          const int pjr[4] = {pj[0], pj[1], pj[2], pj[3]};
 #pragma unroll
           for (int t = 0; t < 4; ++t) {
             const int qi = qbase + t * 16 + q16;
@@ -876,13 +1206,18 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
             const int s01 = int(r32[0]), s23 = int(r32[1]);  // c of rows 0 + 1 and 2 + 3
             int pos = cnt[t] + ((g4 & 1) ? lo : 0) + ((g4 & 2) ? s01 : 0);
             cnt[t] += s01 + s23;
-            // the buffers of queries qbase + 16 t ..: a wave-uniform base and
-            // a small per-lane offset (no 64-bit pointer per query and t)
-            uint64_t* tbuf = bufs + int64_t(qbase + t * 16) * CAP;
-            const uint32_t lo_off = uint32_t(q16 * CAP);
+            // byte offset of the next slot from the wave's buffers: a
+            // wave-uniform base and a small per-lane offset (no 64-bit
+            // pointer per query and t)
+            uint32_t at = uint32_t(pos) * 8u + (q16_off + uint32_t(t * 16 * CAP * 8));
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-              if (p[r]) tbuf[lo_off + uint32_t(pos++)] = make_key(fmaxf(acc[t][r], 0.0f), pjr[r]);
+              if (p[r]) {
+                // (a negative distance counts as 0)
+                const uint32_t hi = uint32_t(max(__float_as_int(acc[t][r]), 0));
+                *reinterpret_cast<uint2*>(wbuf + at) = make_uint2(uint32_t(pjr[r]), hi);
+                at += 8u;
+              }
           }
         }
       }
@@ -902,7 +1237,7 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
       const int t = r >> 4, q = r & 15;
       const int c = __builtin_amdgcn_readlane(t == 0 ? cnt[0] : t == 1 ? cnt[1] : t == 2 ? cnt[2] : cnt[3], q);
       float nt;
-      const int nc = compact_row<EPL>(bufs + int64_t(qbase + r) * CAP, c, ncand, CAP - B_TJ, nt, hist_s[w]);
+      const int nc = compact_row<EPL>(bufs + int64_t(qbase + r) * CAP, c, ncand, SLACK, CAP - B_TJ, nt, hist_s[w]);
 #pragma unroll
       for (int tt = 0; tt < 4; ++tt)
         if (tt == t && q16 == q) {
@@ -920,7 +1255,7 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
     if (qi >= n32) break;
     const int t = r >> 4;
     const int c = __builtin_amdgcn_readlane(t == 0 ? cnt[0] : t == 1 ? cnt[1] : t == 2 ? cnt[2] : cnt[3], r & 15);
-    emit_row<EPL>(bufs + int64_t(qi) * CAP, c, ncand, cand + int64_t(perm[qi]) * ncand, nullptr);
+    emit_set<EPL>(bufs + int64_t(qi) * CAP, c, ncand, cand + int64_t(perm[qi]) * ncand, hist_s[w]);
   }
 }
 
@@ -939,52 +1274,92 @@ __global__ __launch_bounds__(256) void pad_rows_kernel(const float* __restrict__
 // candidates, sorted by (d, j); best k written.  Rows are taken in the
 // locality order (wave w re-ranks row perm[w]), so the waves resident at one
 // time gather overlapping candidate rows from the caches.  The query row is
-// read with uniform (scalar) loads; each lane issues all loads of a
-// candidate row before the arithmetic, four coordinates per load from the
-// padded rows Xp (dp <= DP floats each), which quarters the scattered
-// requests the address units must serve; coordinates past dp re-read the
-// row's last four (in bounds) and, like the zeros past d, add an exact 0.
-template <int DP>
-__global__ __launch_bounds__(256) void rerank_kernel(const float* __restrict__ Xp, int64_t n, int d, int dp,
+// read with uniform (scalar) loads.  The gather of the padded rows Xp (dp <=
+// DP floats each) is bound by the 128-byte lines that cross from L2 to L1:
+// 64 candidates go straight to LDS, 7 chunks of 16 bytes of each per pass,
+// with neighbouring lanes on neighbouring chunks, so that a line crosses
+// once (a lane per candidate reads 16 bytes of 64 lines at a time, and they
+// are evicted before the next 16 bytes); an odd number of chunks keeps the
+// reads of a chunk of 16 rows on distinct banks.  Chunks past dp re-read the
+// row's last (in bounds); coordinates past d add an exact 0.
+constexpr int RR_C = 7;
+template <int DP, bool FULL>
+__global__ __launch_bounds__(256) void rerank_kernel(const float* __restrict__ Xp, int64_t n, int dpv,
                                                      const int32_t* __restrict__ perm, const int32_t* __restrict__ cand,
                                                      int ncand, int k, int32_t* __restrict__ out_idx,
                                                      float* __restrict__ out_d2) {
   static_assert(DP % 4 == 0, "whole float4 loads");
-  const int lane = lane_id();
-  const int64_t pos = int64_t(__builtin_amdgcn_readfirstlane(int(blockIdx.x) * 4 + int(threadIdx.x >> 6)));
+  __shared__ float4 rows_s[4][64 * RR_C];
+  static_assert(sizeof(rows_s[0]) >= 256 * 8 + 256 * 4, "the keys and the histogram reuse it");
+  const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const int64_t pos = int64_t(blockIdx.x) * 4 + w;
   if (pos >= n) return;
   const int64_t row = int64_t(__builtin_amdgcn_readfirstlane(perm[pos]));
-  float xi[DP];
+  const int dp = FULL ? DP : dpv, last = dp / 4 - 1;
+  float4 xi[DP / 4];
 #pragma unroll
-  for (int c = 0; c < DP; ++c) xi[c] = c < d ? Xp[row * dp + c] : 0.0f;
-  const int last = dp / 4 - 1;
+  for (int u = 0; u < DP / 4; ++u) xi[u] = reinterpret_cast<const float4*>(Xp + row * dp)[u < last ? u : last];
   uint64_t v[4];
+  int c = 0;  // candidates (a row short of them, with non-finite input, holds -1 past its own)
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    const int e = t * 64 + lane;
     v[t] = KEY_MAX;
+    if (t * 64 >= ncand) continue;
+    const int e = t * 64 + lane;
     const int32_t j = e < ncand ? cand[row * ncand + e] : -1;
-    if (j >= 0 && j < n) {  // a row short of candidates (non-finite input) holds -1
-      const float4* xj4 = reinterpret_cast<const float4*>(Xp + int64_t(j) * dp);
-      float xv[DP];
+    const bool valid = j >= 0 && j < n;
+    c += __popcll(__ballot(valid));
+    const int js = valid ? j : 0;
+    int64_t src[RR_C];  // the rows that this lane brings chunks of
 #pragma unroll
-      for (int c = 0; c < DP; c += 4) {
-        const float4 q = xj4[c / 4 < last ? c / 4 : last];
-        xv[c] = q.x;
-        xv[c + 1] = q.y;
-        xv[c + 2] = q.z;
-        xv[c + 3] = q.w;
-      }
-      float s2 = 0.0f;
+    for (int u = 0; u < RR_C; ++u)
+      src[u] = int64_t(__builtin_amdgcn_ds_bpermute((u * 64 + lane) / RR_C * 4, js)) * (dp / 4);
+    float s2 = 0.0f;
 #pragma unroll
-      for (int c = 0; c < DP; ++c) {
-        const float u = c < d ? xi[c] - xv[c] : 0.0f;
-        s2 = __builtin_fmaf(u, u, s2);
+    for (int c0 = 0; c0 < DP / 4; c0 += RR_C) {
+      // the reads of what this overwrites have returned
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+#pragma unroll
+      for (int u = 0; u < RR_C; ++u) {
+        const int ch = c0 + (u * 64 + lane) % RR_C;
+        __builtin_amdgcn_global_load_lds(reinterpret_cast<const float4*>(Xp) + src[u] + (ch < last ? ch : last),
+                                         &rows_s[w][u * 64], 16, 0, 0);
       }
-      v[t] = make_key(s2, j);
+      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < RR_C && c0 + u < DP / 4; ++u) {
+        const float4 q = rows_s[w][lane * RR_C + u], x = xi[c0 + u];
+        if (!FULL && c0 + u > last) break;
+        const float u0 = x.x - q.x, u1 = x.y - q.y, u2 = x.z - q.z, u3 = x.w - q.w;
+        s2 = __builtin_fmaf(u0, u0, s2);
+        s2 = __builtin_fmaf(u1, u1, s2);
+        s2 = __builtin_fmaf(u2, u2, s2);
+        s2 = __builtin_fmaf(u3, u3, s2);
+      }
     }
+    if (valid) v[t] = make_key(s2, j);
   }
-  wave_sort<4>(v);
+  // at most 128 keys to sort where that is enough for k
+  if (k <= 128) {
+    uint64_t* keys = reinterpret_cast<uint64_t*>(rows_s[w]);
+    if (c > 128) {
+      wg_fence();
+#pragma unroll
+      for (int t = 0; t < 4; ++t) keys[t * 64 + lane] = v[t];
+      float tau;
+      c = compact_row<4>(keys, c, k, 128 - k, 128, tau, reinterpret_cast<uint32_t*>(keys + 256));
+#pragma unroll
+      for (int t = 0; t < 2; ++t) v[t] = t * 64 + lane < c ? keys[t * 64 + lane] : KEY_MAX;
+    }
+    uint64_t s[2] = {v[0], v[1]};
+    wave_sort<2>(s);
+    v[0] = s[0];
+    v[1] = s[1];
+  } else {
+    wave_sort<4>(v);
+  }
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     const int e = t * 64 + lane;
@@ -1007,7 +1382,7 @@ __global__ __launch_bounds__(256) void count_nonfinite_kernel(const float* __res
 
 struct KnnLayout {
   int epl;
-  size_t o_buf, o_xq, o_xc, o_xs, o_xp, o_cand, o_perm, o_key, o_rng, o_hist, o_cur, o_off, o_bsum, o_box, o_tnrm,
+  size_t o_buf, o_xq, o_xc, o_xs, o_xp, o_cand, o_perm, o_key, o_piv, o_pnorm, o_prank, o_hist, o_cur, o_off, o_bsum, o_box, o_tnrm,
       bytes;
   static KnnLayout make(int64_t n, int d, int precision, int ncand) {
     KnnLayout L;
@@ -1017,13 +1392,15 @@ struct KnnLayout {
     // the locality order (both paths)
     L.o_perm = c.take(sizeof(int32_t) * size_t(bf16_rows(n)));  // padded like the BF16 candidate rows
     L.o_key = c.take(sizeof(uint16_t) * size_t(n));
-    L.o_rng = c.take(sizeof(uint32_t) * 2 * LOC_DIMS);
+    L.o_piv = c.take(sizeof(uint16_t) * size_t(loc_kpad(d)) * LOC_PIV);
+    L.o_pnorm = c.take(sizeof(float) * LOC_PIV);
+    L.o_prank = c.take(sizeof(int) * LOC_PIV);
     L.o_hist = c.take(sizeof(int) * LOC_BINS);
     L.o_cur = c.take(sizeof(int) * LOC_BINS);
     L.o_off = c.take(sizeof(int64_t) * (LOC_BINS + 1));
     L.o_bsum = c.take(sizeof(int64_t) * (size_t(ceil_div(LOC_BINS + 1, SCAN_CHUNK)) + 1));
     if (precision == TSNE_KNN_FP32) {
-      L.o_xs = c.take(sizeof(float) * size_t(n) * size_t(d));  // X in the locality order
+      L.o_xs = c.take(sizeof(float) * size_t(ceil_div(n, F_COLS) * F_COLS) * size_t(d));  // X by column tiles
       L.o_xq = L.o_xc = L.o_cand = L.o_tnrm = L.o_xp = 0;
       L.o_box = c.take(sizeof(float2) * BOX_D * size_t(ceil_div(n, F_COLS)));
     } else {
@@ -1067,24 +1444,27 @@ extern "C" int tsne_knn(const float* X, int64_t n, int32_t d, int32_t k, int32_t
     hipLaunchKernelGGL(count_nonfinite_kernel, dim3(unsigned(blocks)), dim3(256), 0, s, X, cnt, nf);
     TSNE_CHECK_LAUNCH();
   }
-  // locality order (both paths): key range, keys and their counts,
-  // offsets, scatter
-  uint32_t* rng = reinterpret_cast<uint32_t*>(ws + L.o_rng);
+  // locality order (both paths): pivots, keys and their counts, offsets,
+  // scatter
+  uint16_t* piv = reinterpret_cast<uint16_t*>(ws + L.o_piv);
+  float* pnorm = reinterpret_cast<float*>(ws + L.o_pnorm);
+  int* prank = reinterpret_cast<int*>(ws + L.o_prank);
   uint16_t* key = reinterpret_cast<uint16_t*>(ws + L.o_key);
   int* hist = reinterpret_cast<int*>(ws + L.o_hist);
   int* cur = reinterpret_cast<int*>(ws + L.o_cur);
   int64_t* off = reinterpret_cast<int64_t*>(ws + L.o_off);
   int64_t* bsum = reinterpret_cast<int64_t*>(ws + L.o_bsum);
   int32_t* perm = reinterpret_cast<int32_t*>(ws + L.o_perm);
-  if ((rc = launch_fill<uint32_t>(rng, LOC_DIMS, ~0u, s))) return rc;
-  if ((rc = launch_fill<uint32_t>(rng + LOC_DIMS, LOC_DIMS, 0u, s))) return rc;
-  if ((rc = launch_fill<int>(hist, LOC_BINS, 0, s))) return rc;
-  if ((rc = launch_fill<int>(cur, LOC_BINS, 0, s))) return rc;
+  // (hist and cur are adjacent)
+  if ((rc = launch_fill<int>(hist, 2 * LOC_BINS, 0, s))) return rc;
   const dim3 lgrid(unsigned(ceil_div(n, 256) < 2048 ? ceil_div(n, 256) : 2048));
-  hipLaunchKernelGGL(loc_range_kernel, dim3(unsigned(ceil_div(n, 256) < 256 ? ceil_div(n, 256) : 256)), dim3(256), 0,
-                     s, X, n, d, rng);
+  const int m = loc_pivots(n), kp = loc_kpad(d);
+  hipLaunchKernelGGL(loc_pivot_kernel, dim3(LOC_PIV / 4), dim3(256), 0, s, X, n, d, m, kp, piv, pnorm);
   TSNE_CHECK_LAUNCH();
-  hipLaunchKernelGGL(loc_key_kernel, lgrid, dim3(256), 0, s, X, n, d, rng, key, hist);
+  hipLaunchKernelGGL(loc_rank_kernel, dim3(1), dim3(LOC_PIV), 0, s, piv, pnorm, m, kp, prank);
+  TSNE_CHECK_LAUNCH();
+  hipLaunchKernelGGL(loc_key_kernel, dim3(unsigned(ceil_div(n, 128))), dim3(256), 0, s, X, n, d, m, kp, piv, pnorm,
+                     prank, key, hist);
   TSNE_CHECK_LAUNCH();
   if ((rc = exclusive_scan<int>(hist, LOC_BINS, off, bsum, s))) return rc;
   hipLaunchKernelGGL(loc_scatter_kernel, lgrid, dim3(256), 0, s, key, n, off, cur, perm);
@@ -1093,17 +1473,11 @@ extern "C" int tsne_knn(const float* X, int64_t n, int32_t d, int32_t k, int32_t
     float* Xs = reinterpret_cast<float*>(ws + L.o_xs);
     float2* box = reinterpret_cast<float2*>(ws + L.o_box);
     const int64_t ntc = ceil_div(n, F_COLS);
-    hipLaunchKernelGGL(gather_rows_kernel, dim3(unsigned(ceil_div(n, 4))), dim3(256), 0, s, X, n, d, perm, Xs);
-    TSNE_CHECK_LAUNCH();
-    hipLaunchKernelGGL(f32_box_kernel, dim3(unsigned(ceil_div(ntc, 4))), dim3(256), 0, s, Xs, n, d, ntc, box);
+    hipLaunchKernelGGL(gather_tiles_kernel, dim3(unsigned(ntc)), dim3(256), 0, s, X, n, d, ntc, perm, Xs, box);
     TSNE_CHECK_LAUNCH();
     const float4* box4 = reinterpret_cast<const float4*>(box);
-    if (fknn_small_blocks(n))
-      hipLaunchKernelGGL((knn_fp32_kernel<8, 8>), dim3(unsigned(ceil_div(n, 32))), dim3(256), 0, s, Xs, perm, box4, n,
-                         d, k, bufs, nbr_idx, nbr_d2);
-    else
-      hipLaunchKernelGGL((knn_fp32_kernel<8, 16>), dim3(unsigned(ceil_div(n, 64))), dim3(256), 0, s, Xs, perm, box4,
-                         n, d, k, bufs, nbr_idx, nbr_d2);
+    hipLaunchKernelGGL(knn_fp32_kernel<8>, dim3(unsigned(ceil_div(n, 4 * F_RW))), dim3(256), 0, s, Xs, perm, box4, n, d,
+                       k, bufs, nbr_idx, nbr_d2);
     TSNE_CHECK_LAUNCH();
     return TSNE_OK;
   }
@@ -1131,11 +1505,11 @@ extern "C" int tsne_knn(const float* X, int64_t n, int32_t d, int32_t k, int32_t
   TSNE_CHECK_LAUNCH();
   // the exact width for the common 50-coordinate input, else the largest
   if (dp == 52)
-    hipLaunchKernelGGL((rerank_kernel<52>), dim3(unsigned(ceil_div(n, 4))), dim3(256), 0, s, Xp, n, d, dp, perm, cand,
+    hipLaunchKernelGGL((rerank_kernel<52, true>), dim3(unsigned(ceil_div(n, 4))), dim3(256), 0, s, Xp, n, dp, perm, cand,
                        n_cand, k, nbr_idx, nbr_d2);
   else
-    hipLaunchKernelGGL((rerank_kernel<(TSNE_MAX_D_BF16 + 3) / 4 * 4>), dim3(unsigned(ceil_div(n, 4))), dim3(256), 0, s,
-                       Xp, n, d, dp, perm, cand, n_cand, k, nbr_idx, nbr_d2);
+    hipLaunchKernelGGL((rerank_kernel<(TSNE_MAX_D_BF16 + 3) / 4 * 4, false>), dim3(unsigned(ceil_div(n, 4))), dim3(256), 0, s,
+                       Xp, n, dp, perm, cand, n_cand, k, nbr_idx, nbr_d2);
   TSNE_CHECK_LAUNCH();
   return TSNE_OK;
 }

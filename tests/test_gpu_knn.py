@@ -185,3 +185,56 @@ def test_knn_bf16_tile_skipping_nonfinite_rows(dev):
     back = np.searchsorted(fin, g)
     raw, adj = check_knn(Xf, rows, back.astype(np.int32), gd[fin[rows]], oi, od, min_agree=0.999)
     say("bf16 agreement, finite rows", raw, adj)
+
+
+@pytest.mark.parametrize("n,d,k", [(31, 31, 30), (33, 1, 7), (127, 32, 96), (129, 33, 97), (1023, 56, 128),
+                                   (8257, 57, 90), (4100, 113, 129)])
+def test_knn_fp32_tiles_and_chunks(dev, n, d, k):
+    # rows per block (32), columns per tile (128), coordinates per step (56)
+    # and per box (32), keys per short sort (128), each from both sides;
+    # clusters of very different sizes, sorted, so that blocks hold rows of
+    # two clusters and short clusters lie far from their tiles
+    say("knn fp32 tiles and chunks", n, d, k)
+    rng = np.random.default_rng(n + d + k)
+    size = np.maximum(1, n * np.array([0.5, 0.3, 0.15, 0.04, 0.01])).astype(int)
+    lab = np.repeat(np.arange(5), size)[:n]
+    lab = np.concatenate([lab, np.zeros(n - lab.size, int)])
+    X = (20 * rng.standard_normal((5, d))[lab] + rng.standard_normal((n, d))).astype(np.float32)
+    X[n // 2 : n // 2 + 3] = X[0]  # ties
+    oi, od = oracle.knn(X, k)
+    gi, gd = gpu_knn(dev, X, k)
+    check_knn(X, np.arange(n), gi, gd, oi, od)
+
+
+@pytest.mark.parametrize("d,k,n_cand", [(1, 30, 60), (28, 128, 255), (29, 129, 256), (52, 100, 256), (53, 90, 129),
+                                        (58, 128, 200)])
+def test_knn_bf16_rerank_edges(dev, d, k, n_cand):
+    # every other point is a candidate, so the result is the exact kNN:
+    # coordinates per pass (28) and in all (52, 58), candidates to sort (128)
+    # from both sides
+    say("knn bf16 re-rank", d, k, n_cand)
+    n = n_cand + 1
+    X = (np.random.default_rng(d + k).standard_normal((n, d)) * 3).astype(np.float32)
+    oi, od = oracle.knn(X, k)
+    gi, gd = gpu_knn(dev, X, k, "bf16", n_cand=n_cand)
+    check_knn(X, np.arange(n), gi, gd, oi, od)
+
+
+@pytest.mark.parametrize("prec,every", [("fp32", 1), ("bf16", 1), ("fp32", 2), ("bf16", 2)])
+def test_knn_nonfinite_pivots(dev, prec, every):
+    # the points that the locality order would take its cells from, all or
+    # every other one, are not finite
+    say("knn pivots", prec, every)
+    n, d, k = 5000, 20, 15
+    X = separated_clusters(n, d, 6, 7)
+    m = n // 64
+    bad = (np.arange(m) * n // m)[::every]
+    X[bad, 3] = np.nan
+    X[bad[::3], 3] = np.inf
+    fin = np.setdiff1d(np.arange(n), bad)
+    gi, gd = gpu_knn(dev, X, k, prec, n_cand=2 * k if prec == "bf16" else None)
+    oi, od = oracle.knn(X[fin], k)
+    assert np.isin(gi[fin], fin).all()
+    back = np.searchsorted(fin, gi[fin])
+    check_knn(X[fin], np.arange(fin.size), back.astype(np.int32), gd[fin], oi, od,
+              **({"min_agree": 0.999} if prec == "bf16" else {}))
