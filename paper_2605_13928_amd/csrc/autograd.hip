@@ -143,6 +143,10 @@ __global__ __launch_bounds__(256) void kl_backward_rows_kernel(
   }
 }
 
+// Entries per lane in flight.  Bound by the two gathers (val at tpos, y_j): a
+// 128-byte line each; 50,000 rows of 144 entries 147 -> 117 us (4: 127).
+constexpr int KL32_EPT = 8;
+
 // FP32 backward from g0 = -4 R / Z (the gradient pass with attraction
 // weight 0) and Z: dY_i = gC (2 sum_{e in row i} (p_e + p_tpos(e)) w_e
 // (y_i - y_j) + S g0_i), dP_e = gC (1 + ln p_e + ln q_e + ln Z).
@@ -163,17 +167,36 @@ __global__ __launch_bounds__(256) void kl_backward_g0_kernel(
   float ax = 0.0f, ay = 0.0f;
   if (row < n) {
     const float xi = Y[2 * row], yi = Y[2 * row + 1];
-    for (int64_t e = row_ptr[row] + sl; e < row_ptr[row + 1]; e += 16) {
-      const int32_t j = col[e];
-      const float p = val[e];
-      const float pt = val[tpos[e]];
-      const float dx = xi - Y[2 * j], dy = yi - Y[2 * j + 1];
-      const float q = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, 1.0f));
-      const float pw = (p + pt) * __builtin_amdgcn_rcpf(q);
-      ax = __builtin_fmaf(pw, dx, ax);
-      ay = __builtin_fmaf(pw, dy, ay);
-      // ln p + ln q as one logarithm (p q stays within [p, p q_max])
-      if (dP) dP[e] = g * (1.0f + logf(p * q) + lnZ);
+    const int64_t e1 = row_ptr[row + 1];
+    for (int64_t e0 = row_ptr[row] + sl; e0 < e1; e0 += 16 * KL32_EPT) {
+      // all loads of a level before the next one (entries past the row re-read its last)
+      int32_t j[KL32_EPT], tp[KL32_EPT];
+      float p[KL32_EPT], pt[KL32_EPT];
+      float2 y[KL32_EPT];
+#pragma unroll
+      for (int u = 0; u < KL32_EPT; ++u) {
+        const int64_t e = e0 + 16 * u < e1 ? e0 + 16 * u : e1 - 1;
+        j[u] = col[e];
+        p[u] = val[e];
+        tp[u] = tpos[e];
+      }
+#pragma unroll
+      for (int u = 0; u < KL32_EPT; ++u) {
+        pt[u] = val[tp[u]];
+        y[u] = reinterpret_cast<const float2*>(Y)[j[u]];
+      }
+#pragma unroll
+      for (int u = 0; u < KL32_EPT; ++u) {
+        const int64_t e = e0 + 16 * u;
+        if (e >= e1) break;
+        const float dx = xi - y[u].x, dy = yi - y[u].y;
+        const float q = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, 1.0f));
+        const float pw = (p[u] + pt[u]) * __builtin_amdgcn_rcpf(q);
+        ax = __builtin_fmaf(pw, dx, ax);
+        ay = __builtin_fmaf(pw, dy, ay);
+        // ln p + ln q as one logarithm (p q stays within [p, p q_max])
+        if (dP) dP[e] = g * (1.0f + logf(p[u] * q) + lnZ);
+      }
     }
   }
   ax = row16_sum(ax);
@@ -188,15 +211,24 @@ __global__ __launch_bounds__(256) void kl_backward_g0_kernel(
 // order of the sums is fixed), in the layout the backward kernel reads (the
 // third of three doubles per block).  The values are row_ptr[0] = 0 ..
 // row_ptr[n] - 1.
-constexpr int KL32_SBLOCKS = 256;
+constexpr int KL32_SBLOCKS = 1024;
 __global__ __launch_bounds__(256) void val_sums_kernel(const float* __restrict__ val,
                                                        const int64_t* __restrict__ row_ptr, int64_t n,
                                                        double* __restrict__ part) {
   __shared__ double red[256];
   const int64_t nnz = row_ptr[n];
-  double a = 0.0;
-  for (int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x; e < nnz; e += int64_t(gridDim.x) * 256)
-    a += double(val[e]);
+  // eight loads in flight per thread and 1024 blocks (256 blocks of one load
+  // at a time paid the latency of each: 45 us for 7.2 M values, now 11)
+  double s[8] = {};
+  const int64_t step = int64_t(gridDim.x) * 256;
+  for (int64_t e0 = int64_t(blockIdx.x) * 256 + threadIdx.x; e0 < nnz; e0 += 8 * step) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = e0 + u * step < nnz ? val[e0 + u * step] : 0.0f;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s[u] += double(v[u]);
+  }
+  double a = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
   a = block_sum_d(a, red);
   if (threadIdx.x == 0) {
     part[3 * blockIdx.x] = 0.0;
@@ -257,9 +289,11 @@ int kl_backward_f32(const float* Y, int64_t n, const int64_t* row_ptr, const int
   float* g0 = reinterpret_cast<float*>(ws + L.o_g0);
   double* Zs = reinterpret_cast<double*>(ws + L.o_Z);
   double* spart = reinterpret_cast<double*>(ws + L.o_sp);
-  int rc = klgrad_launch(L.kg, ws + L.o_kg, Y, n, row_ptr, col, val, 0.0f, g0, Zs, nullptr, nullptr, s);
+  // no entries: the attraction is kl_backward_g0_kernel's (gathered at weight 0
+  // by the finalize pass it took 40 of 955 us at 50,000 points)
+  int rc = klgrad_launch(L.kg, ws + L.o_kg, Y, n, nullptr, nullptr, nullptr, 0.0f, g0, Zs, nullptr, nullptr, s);
   if (rc) return rc;
-  // S in 256 block partials (the stored values are contiguous: row_ptr[0] = 0)
+  // S in block partials (the stored values are contiguous: row_ptr[0] = 0)
   hipLaunchKernelGGL(val_sums_kernel, dim3(unsigned(KL32_SBLOCKS)), dim3(256), 0, s, val, row_ptr, n, spart);
   TSNE_CHECK_LAUNCH();
   hipLaunchKernelGGL(kl_backward_g0_kernel, dim3(unsigned(L.nrow_blocks)), dim3(256), 0, s, Y, n, row_ptr, col, val,

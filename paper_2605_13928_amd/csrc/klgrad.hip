@@ -36,7 +36,8 @@ namespace tsne {
 // optimiser step to the row (FusedStep).  Column indices outside [0, n)
 // contribute nothing.  ATTP: the attraction was summed per job by the
 // all-pairs kernel (AttList); it is read from its partial slices, exactly
-// like the repulsion, and the CSR is not touched.  nonfinite (nullable):
+// like the repulsion, and the CSR is not touched; nor with row_ptr null (no
+// attraction).  nonfinite (nullable):
 // the block adds the number of non-finite coordinates of its rows of Y (with
 // STEP: of its stepped rows, the positions the pass writes).
 constexpr int FIN_ROWS = 16;
@@ -76,7 +77,8 @@ __global__ __launch_bounds__(256) void finalize_tsne_kernel(
   // --- loads with no dependences -----------------------------------------
   int64_t len = 0;
   if (tid < FIN_ROWS) {
-    const int64_t a = myrow < n ? row_ptr[myrow] : 0, b = myrow < n ? row_ptr[myrow + 1] : 0;
+    const bool has = row_ptr && myrow < n;
+    const int64_t a = has ? row_ptr[myrow] : 0, b = has ? row_ptr[myrow + 1] : 0;
     rp0[tid] = a;
     len = b - a;
     yrow[tid] = myrow < n ? Y[myrow] : make_float2(0.0f, 0.0f);

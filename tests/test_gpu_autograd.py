@@ -111,3 +111,21 @@ def test_fp32_forward_small_sizes(dev, n):
     _, Zg, klg, _ = api.kl_grad(Y, P, 1.0, want_Z=True, want_kl=True)
     assert abs(Zf.item() - Zg.item()) <= 1e-6 * Zg.item()
     assert abs(C.item() - klg.item()) <= 1e-5 * max(1.0, abs(klg.item()))
+
+
+@pytest.mark.parametrize("m", [1, 15, 16, 127, 128, 129, 700])
+def test_fp32_backward_row_lengths(dev, m):
+    # a star: the hub's row holds m entries (16 lanes of 8 entries in flight
+    # per trip, so one entry, partial, whole and several trips), the others
+    # one, and three rows none.  Same tolerances as the other FP32 cases.
+    say("autograd rows", m)
+    n = m + 4
+    row_ptr = np.concatenate([[0], m + np.arange(m + 1), [2 * m] * 3])
+    col = np.concatenate([np.arange(1, m + 1), np.zeros(m, int)])
+    tpos = np.concatenate([m + np.arange(m), np.arange(m)])
+    S = oracle.CSR(row_ptr, col, np.random.default_rng(m).uniform(0.5, 1.5, 2 * m) / (2 * m), tpos)
+    Y = synth.random_embedding(n, 3.0, m)
+    C, Co, dY, dYo, dP, dPo = forward_backward(dev, S, Y, gC=0.7, perturb_seed=2)
+    assert abs(C - Co) <= 1e-5 * max(1.0, abs(Co))
+    assert rel(dY, dYo) <= 1e-4
+    assert rel(dP, dPo) <= 1e-5
