@@ -231,6 +231,7 @@ constexpr int BOX_D = 32;
 // with each row in place of the box of the wave's rows (a wave that holds rows
 // of two clusters has a box between them: 1.20 -> 1.02 ms at 20,011 points).
 constexpr int F_WIN0 = 4, B_WIN0 = 8;
+constexpr int64_t B_SMALL_N = 1 << 19;  // BF16: 16 queries a wave up to here, 32 above (knn_bf16_kernel)
 constexpr int F_TIGHTEN = 64, F_BY_ROW = 2;
 // The it-th tile of a sweep: outward from t0 on both sides in turn, cyclically
 // (a bijection of [0, nt)).  (Swept upward only, the rows of a block that end
@@ -656,12 +657,12 @@ __global__ __launch_bounds__(256) void loc_pivot_kernel(const float* __restrict_
 __global__ __launch_bounds__(LOC_PIV) void loc_rank_kernel(const uint16_t* __restrict__ piv,
                                                            const float* __restrict__ pnorm, int m, int kp,
                                                            int* __restrict__ rank) {
-  __shared__ float coord[LOC_PIV][33];
+  __shared__ float4 coord[LOC_PIV][9];  // 8 used: rows of an odd number of 16 bytes
   __shared__ float dist_s[LOC_CEN][LOC_CEN + 1];
   __shared__ int cen_s[LOC_CEN], chain_s[LOC_CEN], place_s[LOC_CEN];
   __shared__ float part_d[2][4];
   __shared__ int part_p[2][4];
-  __shared__ uint64_t key[LOC_PIV];
+  __shared__ ulonglong2 key[LOC_PIV / 2];
   const int p = threadIdx.x, lane = lane_id(), w = p >> 6;
   const bool ok = pnorm[p] < INFINITY;
   uint4 raw[4];
@@ -678,14 +679,15 @@ __global__ __launch_bounds__(LOC_PIV) void loc_rank_kernel(const uint16_t* __res
     }
   }
 #pragma unroll
-  for (int c = 0; c < 32; ++c) coord[p][c] = x[c];
+  for (int c = 0; c < 8; ++c) coord[p][c] = make_float4(x[4 * c], x[4 * c + 1], x[4 * c + 2], x[4 * c + 3]);
   __syncthreads();
   auto distance = [&](int q) {  // from this thread's pivot to pivot q
     float s = 0.0f;
 #pragma unroll
-    for (int c = 0; c < 32; ++c) {
-      const float u = x[c] - coord[q][c];
-      s = fmaf(u, u, s);
+    for (int c = 0; c < 8; ++c) {
+      const float4 v = coord[q][c];
+      const float u0 = x[4 * c] - v.x, u1 = x[4 * c + 1] - v.y, u2 = x[4 * c + 2] - v.z, u3 = x[4 * c + 3] - v.w;
+      s = fmaf(u0, u0, fmaf(u1, u1, fmaf(u2, u2, fmaf(u3, u3, s))));
     }
     return s;
   };
@@ -721,9 +723,11 @@ __global__ __launch_bounds__(LOC_PIV) void loc_rank_kernel(const uint16_t* __res
     const int a = e / LOC_CEN, b = e % LOC_CEN;
     if (a < nc && b < nc) {
       float s = 0.0f;
-      for (int c = 0; c < 32; ++c) {
-        const float u = coord[cen_s[a]][c] - coord[cen_s[b]][c];
-        s = fmaf(u, u, s);
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const float4 v = coord[cen_s[a]][c], y = coord[cen_s[b]][c];
+        const float u0 = v.x - y.x, u1 = v.y - y.y, u2 = v.z - y.z, u3 = v.w - y.w;
+        s = fmaf(u0, u0, fmaf(u1, u1, fmaf(u2, u2, fmaf(u3, u3, s))));
       }
       dist_s[a][b] = s;
     }
@@ -750,13 +754,16 @@ __global__ __launch_bounds__(LOC_PIV) void loc_rank_kernel(const uint16_t* __res
   const int before = chain_s[place > 0 ? place - 1 : 0], after = chain_s[place + 1 < nc ? place + 1 : nc - 1];
   const uint32_t t = __float_as_uint(distance(cen_s[before]) - distance(cen_s[after]));
   const uint32_t ord = (t >> 31) ? ~t : t | 0x80000000u;
-  // the slots past m and pivots that are not finite come last
-  const uint64_t own = ok ? (uint64_t(place) << 32) | ord : ~uint64_t(0);
-  key[p] = own;
+  // (distinct; the slots past m and pivots that are not finite come last)
+  const uint64_t own = (ok ? (uint64_t(place) << 40) | (uint64_t(ord) << 8) : ~uint64_t(255)) | uint64_t(p);
+  reinterpret_cast<uint64_t*>(key)[p] = own;
   __syncthreads();
   int r = 0;
-#pragma unroll 8
-  for (int u = 0; u < LOC_PIV; ++u) r += key[u] < own || (key[u] == own && u < p) ? 1 : 0;
+#pragma unroll 16
+  for (int u = 0; u < LOC_PIV / 2; ++u) {
+    const ulonglong2 v = key[u];
+    r += (v.x < own ? 1 : 0) + (v.y < own ? 1 : 0);
+  }
   rank[p] = r;
 }
 
@@ -972,26 +979,30 @@ __device__ __forceinline__ void lds_read2_b128(uint32_t at0, uint32_t at1, bf16x
                : "memory");
 }
 
-// Block = 4 waves x 64 queries, positions of the locality order (Xq, Xc and
-// the buffers are in that order; perm maps a position to its point, which
+// Block = 4 waves x 16 QT queries, positions of the locality order (Xq, Xc
+// and the buffers are in that order; perm maps a position to its point, which
 // is what keys and outputs name).  The candidate tiles are swept outward
-// from the block's own.  Lane l works on queries 16 t + (l % 16),
-// t = 0..3, of its wave and, per 16-candidate subtile, on candidates
-// 4 (l / 16) .. + 3 (the MFMA C layout).  A query's threshold and buffer
-// count are held (identically) by its four lanes.  Four blocks fit a CU
-// (at most 128 VGPRs, which the kernel fits without VGPR spills), and 1024
-// resident blocks cover 262144 queries in one round.  The kernel is bound by
-// the instructions of the appends (57 % of all; half of a wave's time) and
-// the waits of its four waves for each other (a third); what else cost was
+// from the block's own.  Lane l works on queries 16 t + (l % 16), t < QT, of
+// its wave and, per 16-candidate subtile, on candidates 4 (l / 16) .. + 3
+// (the MFMA C layout).  A query's threshold and buffer count are held
+// (identically) by its four lanes.
+// QT = 1 up to B_SMALL_N points, 2 above: few queries a wave make a narrow
+// box, little to wait for in the other waves of a block, five waves a SIMD
+// and short last blocks; many share a tile's load.  k = 90, QT = 1 / 2 / 4:
+// 20,000 points 0.86 / 1.2 / 1.8 ms, 250,000 6.8 / 7.3 / 8.7, 600,000 20.5 /
+// 20.4 / 21.7, 1,000,000 41 / 37 / 40; without clusters 200,000 17.7 / 17.6 /
+// 17.2, 600,000 105 / 84 / 83.
+// The kernel is bound by the instructions of the appends (half of a wave's
+// time), the waits of its four waves for each other and the last blocks (the
+// heaviest of 3907 took 0.75 of the kernel at QT = 4).  What else cost was
 // found by clocks in a copy: the compiler's wait for the prefetch of the next
 // tile before every LDS read (lds_read_b128), the code and masks of unrolled
 // subtiles and sorts (instruction cache, spills), box tests with 64 lines per
-// load.  1,000,000 points x 50, k = 90: 66 -> 31 ms; 1 or 2 waves a block: 57
-// and 48 ms when 4 took 47.
+// load.  1,000,000 points x 50, k = 90: 66 -> 29 ms.
 // Tile skipping.  A wave does not evaluate a tile in which no distance can
-// pass the threshold of any of its 64 queries, and the block does not
+// pass the threshold of any of its queries, and the block does not
 // fetch a tile that none of its waves evaluates.  With B the box of the
-// wave's queries (they are one tile of the order, so B is that tile's box)
+// wave's queries
 // and T the candidate tile's (leading BOX_D coordinates), LB = sum_c
 // gap_c(B, T)^2 is at most the squared distance of any of the queries to
 // any candidate of the tile, and the MFMA's distance differs from the
@@ -1006,10 +1017,10 @@ __device__ __forceinline__ void lds_read2_b128(uint32_t at0, uint32_t at1, bf16x
 // time (one position per lane, a ballot per wave, the four masks OR-ed
 // through LDS), with the thresholds of that moment; they only decrease, so
 // a window's stale value skips less, never wrongly.
-template <int EPL>
-__global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restrict__ Xq, const uint4* __restrict__ Xc,
+template <int EPL, int QT>
+__global__ __launch_bounds__(256, 5) void knn_bf16_kernel(const uint4* __restrict__ Xq, const uint4* __restrict__ Xc,
                                                        const int32_t* __restrict__ perm, const float4* __restrict__ box4,
-                                                       const float* __restrict__ tnrm, int64_t n, int ncand,
+                                                       const float* __restrict__ tnrm, int64_t n, int d, int ncand,
                                                        uint64_t* __restrict__ bufs, int32_t* __restrict__ cand) {
   constexpr int CAP = 64 * EPL;
   __shared__ uint4 tile[2][B_TJ * 8];  // double-buffered: 64 rows x 128 bytes each
@@ -1023,8 +1034,11 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
   // indices are 32-bit (n < 2^31 is checked by the caller); products that
   // address memory are taken in 64 bits
   const int n32 = int(n);
-  const int qblock = int(blockIdx.x) * 256;
-  const int qbase = qblock + w * 64;
+  // (a variable: the host pass drops a kernel whose calls of device builtins
+  // depend on its template parameters)
+  int qpw = 16 * QT;  // queries per wave
+  const int qblock = int(blockIdx.x) * 4 * qpw;
+  const int qbase = qblock + w * qpw;
   int cnt[4] = {0, 0, 0, 0};  // buffer count of query (t, q16), the same in its four lanes
   // query fragments: tile t, k-step s; lane holds query qbase + 16 t + q16,
   // k elements 32 s + 8 g4 ... + 7
@@ -1039,7 +1053,7 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
   int tau_key[4];
   auto key_of = [](float t) { return t >= 0.0f ? __float_as_int(t) : INT_MAX; };
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
+  for (int t = 0; t < QT; ++t) {
     const int qi = qbase + t * 16 + q16;
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
@@ -1076,14 +1090,27 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
     if (w == 0) __builtin_amdgcn_global_load_lds(perm + c0 + lane, &ptile[b][0], 4, 0, 0);
   };
   const int ntiles = (n32 + B_TJ - 1) / B_TJ;
-  const int t0 = qblock / B_TJ + 2 < ntiles ? qblock / B_TJ + 2 : ntiles - 1;
+  int t0 = (qblock + 2 * qpw) / B_TJ;  // the block's middle
+  t0 = t0 < ntiles ? t0 : ntiles - 1;
   auto tile_of = [&](int it) -> int { return outward(t0, it, ntiles); };
   auto tile_c0 = [&](int it) -> int { return tile_of(it) * B_TJ; };
-  // each wave's query box: its 64 queries are candidate tile qblock / 64 + w
-  const int qt = qblock / B_TJ + w;
+  // each wave's query box (rows past n repeat the last); the norms' bound is
+  // that of the candidate tile they lie in
+  const int qt = qbase / B_TJ;
   const bool has_q = qt < ntiles;  // else the wave holds only padding queries
   if (has_q) {
-    if (lane < BOX_D / 2) qbox[w][lane] = box4[int64_t(lane) * ntiles + qt];
+    const int c = lane & 31;
+    float lo = INFINITY, hi = -INFINITY;
+    for (int r = lane >> 5; r < qpw; r += 2) {
+      const int qi = qbase + r < n32 ? qbase + r : n32 - 1;
+      const float v = bf16_to_f(reinterpret_cast<const uint16_t*>(Xq)[int64_t(qi) * 64 + c]);
+      lo = fminf(lo, v);
+      hi = fmaxf(hi, v);
+    }
+    lo = fminf(lo, xor_lane_f(lo, 32));
+    hi = fmaxf(hi, xor_lane_f(hi, 32));
+    if (lane < BOX_D)
+      reinterpret_cast<float2*>(qbox[w])[lane] = lane < d ? make_float2(lo, hi) : make_float2(0.0f, 0.0f);
     if (lane == 0) qnrm_s[w] = tnrm[qt];
   }
   __syncthreads();
@@ -1092,7 +1119,9 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
   int wpar = 0;
   auto window = [&](int p0, int width, uint64_t& blk) -> uint64_t {
     // this wave's largest threshold now (padding queries hold -inf)
-    const float m4 = fmaxf(fmaxf(tau[0], tau[1]), fmaxf(tau[2], tau[3]));
+    float m4 = tau[0];
+#pragma unroll
+    for (int t = 1; t < QT; ++t) m4 = fmaxf(m4, tau[t]);
     const float tm = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(-wave_min(-m4))));
     const int p = p0 + lane;
     bool live = has_q && lane < width && p < ntiles;
@@ -1170,7 +1199,7 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
         lds_read2_b128(lds_address(tl + tile_slot(rloc, g4)), lds_address(tl + tile_slot(rloc, 4 + g4)), a0, a1);
         floatx4_t acc[4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
+        for (int t = 0; t < QT; ++t) {
           acc[t] = floatx4_t{0.0f, 0.0f, 0.0f, 0.0f};
           acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, bq[t][0], acc[t], 0, 0, 0);
           acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, bq[t][1], acc[t], 0, 0, 0);
@@ -1178,7 +1207,7 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
         // acc[t][r] = distance(query qbase + 16 t + q16, candidate c0 + 16 sub + 4 g4 + r)
         bool any = false;
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < QT; ++t)
           any |= min(min(__float_as_int(acc[t][0]), __float_as_int(acc[t][1])),
                      min(__float_as_int(acc[t][2]), __float_as_int(acc[t][3]))) <= tau_key[t];
         if (__ballot(any)) {
@@ -1187,7 +1216,7 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
           lds_read_b128(lds_address(pt + sub * 16 + 4 * g4), pj);
           const int pjr[4] = {pj[0], pj[1], pj[2], pj[3]};
 #pragma unroll
-          for (int t = 0; t < 4; ++t) {
+          for (int t = 0; t < QT; ++t) {
             const int qi = qbase + t * 16 + q16;
             bool p[4];
             int c = 0;
@@ -1223,14 +1252,14 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
       }
     };
     if (cur_mine) {
-      if (c0 < qblock + 256 && qblock < c0 + B_TJ) sweep(std::true_type{});
+      if (c0 < qblock + 4 * qpw && qblock < c0 + B_TJ) sweep(std::true_type{});
       else sweep(std::false_type{});
     }
     // compaction of queries that could overflow in the next tile; lanes
     // 0..15 speak for queries 16 t + lane
     uint64_t need = 0;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) need |= (__ballot(cnt[t] > CAP - B_TJ) & 0xFFFFull) << (16 * t);
+    for (int t = 0; t < QT; ++t) need |= (__ballot(cnt[t] > CAP - B_TJ) & 0xFFFFull) << (16 * t);
     while (need) {
       const int r = __ffsll((unsigned long long)need) - 1;
       need &= need - 1;
@@ -1239,7 +1268,7 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
       float nt;
       const int nc = compact_row<EPL>(bufs + int64_t(qbase + r) * CAP, c, ncand, SLACK, CAP - B_TJ, nt, hist_s[w]);
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt)
+      for (int tt = 0; tt < QT; ++tt)
         if (tt == t && q16 == q) {
           cnt[tt] = nc;
           tau[tt] = nt;
@@ -1250,7 +1279,7 @@ __global__ __launch_bounds__(256, 4) void knn_bf16_kernel(const uint4* __restric
     pos = nxt;
     cur_mine = nxt_mine;
   }
-  for (int r = 0; r < 64; ++r) {
+  for (int r = 0; r < qpw; ++r) {
     const int qi = qbase + r;
     if (qi >= n32) break;
     const int t = r >> 4;
@@ -1495,9 +1524,14 @@ extern "C" int tsne_knn(const float* X, int64_t n, int32_t d, int32_t k, int32_t
   float* tnrm = reinterpret_cast<float*>(ws + L.o_tnrm);
   hipLaunchKernelGGL(bf16_box_kernel, dim3(unsigned(ceil_div(ntiles, 4))), dim3(256), 0, s, Xq, n, d, ntiles, box, tnrm);
   TSNE_CHECK_LAUNCH();
-  hipLaunchKernelGGL(knn_bf16_kernel<8>, dim3(unsigned(ceil_div(n, 256))), dim3(256), 0, s,
-                     reinterpret_cast<const uint4*>(Xq), reinterpret_cast<const uint4*>(Xc), perm,
-                     reinterpret_cast<const float4*>(box), tnrm, n, n_cand, bufs, cand);
+  const uint4 *Xq4 = reinterpret_cast<const uint4*>(Xq), *Xc4 = reinterpret_cast<const uint4*>(Xc);
+  const float4* box4 = reinterpret_cast<const float4*>(box);
+  if (n <= B_SMALL_N)
+    hipLaunchKernelGGL((knn_bf16_kernel<8, 1>), dim3(unsigned(ceil_div(n, 64))), dim3(256), 0, s, Xq4, Xc4, perm, box4,
+                       tnrm, n, d, n_cand, bufs, cand);
+  else
+    hipLaunchKernelGGL((knn_bf16_kernel<8, 2>), dim3(unsigned(ceil_div(n, 128))), dim3(256), 0, s, Xq4, Xc4, perm, box4,
+                       tnrm, n, d, n_cand, bufs, cand);
   TSNE_CHECK_LAUNCH();
   const int dp = (d + 3) / 4 * 4;
   float* Xp = reinterpret_cast<float*>(ws + L.o_xp);

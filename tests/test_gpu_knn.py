@@ -238,3 +238,16 @@ def test_knn_nonfinite_pivots(dev, prec, every):
     back = np.searchsorted(fin, gi[fin])
     check_knn(X[fin], np.arange(fin.size), back.astype(np.int32), gd[fin], oi, od,
               **({"min_agree": 0.999} if prec == "bf16" else {}))
+
+
+@pytest.mark.parametrize("n", [524288, 524289, 524288 + 4096 + 33])
+def test_knn_bf16_queries_per_wave(dev, n):
+    # 16 queries a wave up to 2^19 points, 32 above; partial last waves
+    say("knn bf16 queries per wave", n)
+    d, k = 40, 10
+    X = separated_clusters(n, d, 40, 3)
+    gi, gd = gpu_knn(dev, X, k, "bf16", n_cand=2 * k)
+    rows = np.concatenate([np.random.default_rng(n).choice(n - 70, 60, replace=False), np.arange(n - 70, n, 7)])
+    oi, od = oracle.knn(X, k, rows=rows)
+    raw, adj = check_knn(X, rows, gi[rows], gd[rows], oi, od, min_agree=0.99)
+    say("bf16 agreement", n, raw, adj)
