@@ -415,7 +415,7 @@ int tsne_kl_backward(int32_t dtype, const void* Y, int64_t n, const int64_t* row
  * tsne_umap_weights -- the local fuzzy simplicial set of every row [MHM18]
  * Sec. 3.1: with d_j = sqrt(d2_j) (FP64), rho = the smallest positive d_j
  * (0 if none), sigma the root of sum_j exp(-max(0, d_j - rho) / sigma) =
- * log2(k) (FP64 bisection; sigma >= 1e-3 mean_j d_j, or 1e-3 when every
+ * log2(k) (found in FP64; sigma >= 1e-3 mean_j d_j, or 1e-3 when every
  * d_j is 0, and sigma stays at that floor when the floor already meets the
  * target), w_j = exp(-max(0, d_j - rho) / sigma).
  *   nbr_d2    [n][k] float: squared distances of the neighbour lists.
