@@ -277,7 +277,7 @@ int tsne_kl_grad_noalloc(const float* Y, int64_t n, const int64_t* row_ptr, cons
  *   max_box_width  upper bound of h while B < max_fft / (2 p) (> 0; 1.0).
  *   max_fft        largest F, a power of two in [64, 4096] with
  *                  2 p min_boxes <= max_fft (2048); the workspace grows as
- *                  24 max_fft^2 bytes plus 6 max_fft^2 for the node sums.
+ *                  48 max_fft^2 bytes plus 6 max_fft^2 for the node sums.
  */
 int tsne_kl_grad_fft(const float* Y, int64_t n, const int64_t* row_ptr, const int32_t* col, const float* val,
                      float exaggeration, int32_t n_interp, int32_t min_boxes, float max_box_width, int32_t max_fft,

@@ -790,7 +790,9 @@ FiPlan fi_plan(int64_t n, int max_fft) {
   // a heavy box of m > FI_HEAVY points has fewer than 2 m / FI_HEAVY chunks
   L.o_heavy = c.take(sizeof(int2) * size_t(2 * ceil_div(n, FI_HEAVY)));
   L.o_G = c.take(sizeof(unsigned long long) * 3 * size_t(Nmax) * size_t(Nmax));
-  L.o_C = c.take(sizeof(double2) * 3 * size_t(L.plane));
+  // three half planes are used; the size stays the 48 max_fft^2 bytes that the
+  // interface states, which callers may have laid out
+  L.o_C = c.take(sizeof(double2) * 3 * size_t(max_fft) * size_t(max_fft));
   L.o_R = c.take(sizeof(float2) * size_t(n));
   L.o_Zb = c.take(sizeof(double) * FI_GRID);
   L.o_kl = c.take(finalize_kl_bytes(n));
