@@ -244,25 +244,31 @@ __device__ __forceinline__ int outward(int t0, int it, int nt) {
 __device__ __forceinline__ int next_window(int w, int w0) { return w < w0 ? w0 : (w < 64 ? 2 * w : 64); }
 
 // ---------------------------------------------------------------------
-// FP32 exact path.  Block = 4 waves x 8 rows; each step covers 128 columns,
-// 2 per lane; the rows' coordinates are LDS broadcasts, the columns' are
-// per-lane LDS reads, dimension chunks of 56.  Rows and columns are
-// positions of the locality order (Xt = X in that order; perm maps a
-// position to its point, which keys and outputs name); a block sweeps the
-// column tiles outward from its own rows and skips those the box tests of
-// its waves rule out.  What bounds it is the last block: 32 rows a block (64
-// take 20 to 50 % longer from 30,000 clustered points up, and save 3 % at
-// d = 200 without clusters), thresholds and counts in one register each (a
+// FP32 exact path.  Block = 4 waves x 4 or 8 rows (fknn_few_rows); each step
+// covers 128 columns, 2 per lane; the rows' coordinates are LDS broadcasts,
+// the columns' are per-lane LDS reads, dimension chunks of 56.  Rows and
+// columns are positions of the locality order (Xt = X in that order; perm
+// maps a position to its point, which keys and outputs name); a block sweeps
+// the column tiles outward from its own rows and skips those the box tests of
+// its waves rule out.  What bounds it is the last block, whose rows have
+// neighbours in many tiles; thresholds and counts are in one register each (a
 // lane per row: arrays of them went to scratch), the next tile in registers
-// while this one is consumed.  20,011 points x 50, 30 clusters, k = 90: 2.61
-// -> 0.82 ms; 100,000: 24.9 -> 2.3 ms; 40,000 without clusters: 8.5 -> 5.9.
+// while this one is consumed.  64-row blocks take 20 to 50 % longer than
+// 32-row ones from 30,000 clustered points up.  20,011 points x 50, 30
+// clusters, k = 90: 2.61 -> 0.61 ms; 100,000: 24.9 -> 2.2 ms; 40,000 without
+// clusters: 8.5 -> 5.9.
 
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 constexpr int F_COLS = 128;
 constexpr int F_DC = 56;
 constexpr int XJ_S = F_COLS + 4;  // LDS row strides: multiples of 4 floats keep the
                                   // 16-byte reads aligned and spread the stores' banks
-constexpr int F_RW = 8;           // rows per wave
+// 4 rows per wave, so that no block is long and all CUs have several: 20,011
+// points of 30 clusters 0.81 -> 0.61 ms, 1,500 points 0.22 -> 0.17.  8 rows
+// above 32,768 points (100,000: 2.20 against 2.32 ms) and where a tile takes
+// several chunks of coordinates, which the rows of a block then re-read
+// (20,000 points x 200 without clusters: 6.4 against 9.0 ms).
+inline bool fknn_few_rows(int64_t n, int d) { return n <= 32768 && d <= F_DC; }
 
 // The rows of the locality order by column tiles, transposed: coordinate c of
 // position F_COLS u + r is Xt[(u d + c) F_COLS + r] (zeros past n), so that a
@@ -330,11 +336,12 @@ __device__ __forceinline__ int64_t xt_at(int64_t p, int d, int c) {
 // buffers, and the outputs, as the full sweep makes them.  The block
 // stages the tiles that some wave evaluates (the OR of the waves' window
 // masks, exchanged through LDS).
-template <int EPL>
+template <int EPL, int F_RW>
 __global__ __launch_bounds__(256, 3) void knn_fp32_kernel(const float* __restrict__ Xt, const int32_t* __restrict__ perm,
                                                        const float4* __restrict__ cbox4, int64_t n, int d, int k,
                                                        uint64_t* __restrict__ bufs, int32_t* __restrict__ out_idx,
                                                        float* __restrict__ out_d2) {
+  static_assert(F_RW % 4 == 0 && F_COLS % (4 * F_RW) == 0, "whole 16-byte reads, blocks within a tile");
   constexpr int F_ROWS = 4 * F_RW;
   constexpr int XI_S = F_ROWS + 4;
   constexpr int CAP = 64 * EPL;
@@ -523,6 +530,7 @@ __global__ __launch_bounds__(256, 3) void knn_fp32_kernel(const float* __restric
     if (npos < ntc) load(npos, ndc);
     __syncthreads();
     if (pos_mine) {  // else no distance of this tile can pass a threshold of this wave
+#pragma unroll(F_RW == 8 ? 8 : 1)
       for (int c = 0; c < dl; ++c) {
         const float4* ap = reinterpret_cast<const float4*>(&xi_s[c * XI_S + w * F_RW]);
         float a[F_RW];
@@ -1505,8 +1513,12 @@ extern "C" int tsne_knn(const float* X, int64_t n, int32_t d, int32_t k, int32_t
     hipLaunchKernelGGL(gather_tiles_kernel, dim3(unsigned(ntc)), dim3(256), 0, s, X, n, d, ntc, perm, Xs, box);
     TSNE_CHECK_LAUNCH();
     const float4* box4 = reinterpret_cast<const float4*>(box);
-    hipLaunchKernelGGL(knn_fp32_kernel<8>, dim3(unsigned(ceil_div(n, 4 * F_RW))), dim3(256), 0, s, Xs, perm, box4, n, d,
-                       k, bufs, nbr_idx, nbr_d2);
+    if (fknn_few_rows(n, d))
+      hipLaunchKernelGGL((knn_fp32_kernel<8, 4>), dim3(unsigned(ceil_div(n, 16))), dim3(256), 0, s, Xs, perm, box4, n, d,
+                         k, bufs, nbr_idx, nbr_d2);
+    else
+      hipLaunchKernelGGL((knn_fp32_kernel<8, 8>), dim3(unsigned(ceil_div(n, 32))), dim3(256), 0, s, Xs, perm, box4, n, d,
+                         k, bufs, nbr_idx, nbr_d2);
     TSNE_CHECK_LAUNCH();
     return TSNE_OK;
   }

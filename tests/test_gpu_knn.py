@@ -251,3 +251,16 @@ def test_knn_bf16_queries_per_wave(dev, n):
     oi, od = oracle.knn(X, k, rows=rows)
     raw, adj = check_knn(X, rows, gi[rows], gd[rows], oi, od, min_agree=0.99)
     say("bf16 agreement", n, raw, adj)
+
+
+@pytest.mark.parametrize("n,d", [(15, 20), (17, 56), (143, 57), (32768, 8), (32769, 8)])
+def test_knn_fp32_rows_per_wave(dev, n, d):
+    # 4 rows a wave up to 32,768 points and 56 coordinates (blocks of 16),
+    # 8 otherwise (blocks of 32); partial last blocks and waves
+    say("knn fp32 rows per wave", n, d)
+    k = min(n - 1, 12)
+    X = separated_clusters(n, d, 9, n)
+    rows = np.arange(n) if n < 1000 else np.concatenate([np.arange(0, n, 977), np.arange(n - 40, n)])
+    oi, od = oracle.knn(X, k, rows=rows)
+    gi, gd = gpu_knn(dev, X, k)
+    check_knn(X, rows, gi[rows], gd[rows], oi, od)
