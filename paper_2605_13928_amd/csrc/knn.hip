@@ -265,10 +265,11 @@ constexpr int XJ_S = F_COLS + 4;  // LDS row strides: multiples of 4 floats keep
                                   // 16-byte reads aligned and spread the stores' banks
 // 4 rows per wave, so that no block is long and all CUs have several: 20,011
 // points of 30 clusters 0.81 -> 0.61 ms, 1,500 points 0.22 -> 0.17.  8 rows
-// above 32,768 points (100,000: 2.20 against 2.32 ms) and where a tile takes
-// several chunks of coordinates, which the rows of a block then re-read
-// (20,000 points x 200 without clusters: 6.4 against 9.0 ms).
-inline bool fknn_few_rows(int64_t n, int d) { return n <= 32768 && d <= F_DC; }
+// above 32,768 points (100,000: 2.20 against 2.32 ms); where a tile takes
+// several chunks of coordinates, which the rows of a block then re-read,
+// above the 768 blocks of 16 rows that are resident at once (12,000 points x
+// 200 without clusters: 4 rows 2.95, 8 rows 3.6 ms; 20,000: 9.0, 6.4).
+inline bool fknn_few_rows(int64_t n, int d) { return n <= (d <= F_DC ? 32768 : 12288); }
 
 // The rows of the locality order by column tiles, transposed: coordinate c of
 // position F_COLS u + r is Xt[(u d + c) F_COLS + r] (zeros past n), so that a
@@ -632,8 +633,13 @@ constexpr uint16_t BF16_INF = 0x7F80;
 constexpr int LOC_BINS = 1 << 16;
 constexpr int LOC_PIV = 256;     // pivots, at most; 64 points per pivot at least
 constexpr int LOC_CEN = 32;
+// Few points keep their own order: at 1,500 x 50 the sweep of all tiles took
+// 0.115 ms, the order and the sweep after it 0.17 (4,000: 0.25 and 0.29;
+// 8,000: 0.46 and 0.45).
+constexpr int64_t LOC_MIN_N = 4096;
 inline int loc_kpad(int d) { return (d + 31) / 32 * 32; }
-inline int loc_pivots(int64_t n) { return n / 64 < 1 ? 1 : (n / 64 < LOC_PIV ? int(n / 64) : LOC_PIV); }
+static_assert(LOC_MIN_N / 64 >= LOC_CEN, "at least a pivot per centre");
+inline int loc_pivots(int64_t n) { return n / 64 < LOC_PIV ? int(n / 64) : LOC_PIV; }
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
@@ -663,7 +669,7 @@ __global__ __launch_bounds__(256) void loc_pivot_kernel(const float* __restrict_
 // and the points of the shorter run were near their neighbours only at the
 // far end of their sweep.)
 __global__ __launch_bounds__(LOC_PIV) void loc_rank_kernel(const uint16_t* __restrict__ piv,
-                                                           const float* __restrict__ pnorm, int m, int kp,
+                                                           const float* __restrict__ pnorm, int kp,
                                                            int* __restrict__ rank) {
   __shared__ float4 coord[LOC_PIV][9];  // 8 used: rows of an odd number of 16 bytes
   __shared__ float dist_s[LOC_CEN][LOC_CEN + 1];
@@ -699,10 +705,9 @@ __global__ __launch_bounds__(LOC_PIV) void loc_rank_kernel(const uint16_t* __res
     }
     return s;
   };
-  const int nc = m < LOC_CEN ? m : LOC_CEN;
   float near_d = INFINITY;
   int near = 0, cur = 0;
-  for (int s = 0; s < nc; ++s) {
+  for (int s = 0; s < LOC_CEN; ++s) {
     if (p == 0) cen_s[s] = cur;
     const float dist = distance(cur);
     if (dist < near_d) {
@@ -729,29 +734,28 @@ __global__ __launch_bounds__(LOC_PIV) void loc_rank_kernel(const uint16_t* __res
   __syncthreads();
   for (int e = p; e < LOC_CEN * LOC_CEN; e += LOC_PIV) {
     const int a = e / LOC_CEN, b = e % LOC_CEN;
-    if (a < nc && b < nc) {
-      float s = 0.0f;
+    float s = 0.0f;
 #pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const float4 v = coord[cen_s[a]][c], y = coord[cen_s[b]][c];
-        const float u0 = v.x - y.x, u1 = v.y - y.y, u2 = v.z - y.z, u3 = v.w - y.w;
-        s = fmaf(u0, u0, fmaf(u1, u1, fmaf(u2, u2, fmaf(u3, u3, s))));
-      }
-      dist_s[a][b] = s;
+    for (int c = 0; c < 8; ++c) {
+      const float4 v = coord[cen_s[a]][c], y = coord[cen_s[b]][c];
+      const float u0 = v.x - y.x, u1 = v.y - y.y, u2 = v.z - y.z, u3 = v.w - y.w;
+      s = fmaf(u0, u0, fmaf(u1, u1, fmaf(u2, u2, fmaf(u3, u3, s))));
     }
+    dist_s[a][b] = s;
   }
   __syncthreads();
   if (w == 0) {
     int at = 0;
-    bool open = lane < nc;
-    for (int s = 0; s < nc; ++s) {
+    bool open = lane < LOC_CEN;
+    for (int s = 0; s < LOC_CEN; ++s) {
       if (lane == 0) {
         chain_s[s] = at;
         place_s[at] = s;
       }
       open = open && lane != at;
       const float v = open ? dist_s[at][lane & (LOC_CEN - 1)] : INFINITY;
-      const uint64_t who = __ballot(open && v == wave_min(v));
+      const float low = wave_min(v);  // (by all lanes)
+      const uint64_t who = __ballot(open && v == low);
       // (none is left after the last; distances that are not finite leave the lowest open one)
       const uint64_t left = who ? who : __ballot(open);
       at = left ? __builtin_ctzll(left) : 0;
@@ -759,7 +763,7 @@ __global__ __launch_bounds__(LOC_PIV) void loc_rank_kernel(const uint16_t* __res
   }
   __syncthreads();
   const int place = place_s[near];
-  const int before = chain_s[place > 0 ? place - 1 : 0], after = chain_s[place + 1 < nc ? place + 1 : nc - 1];
+  const int before = chain_s[place > 0 ? place - 1 : 0], after = chain_s[place + 1 < LOC_CEN ? place + 1 : LOC_CEN - 1];
   const uint32_t t = __float_as_uint(distance(cen_s[before]) - distance(cen_s[after]));
   const uint32_t ord = (t >> 31) ? ~t : t | 0x80000000u;
   // (distinct; the slots past m and pivots that are not finite come last)
@@ -872,6 +876,11 @@ __global__ __launch_bounds__(256) void loc_key_kernel(const float* __restrict__ 
       atomicAdd(&hist[k], 1);
     }
   }
+}
+
+__global__ __launch_bounds__(256) void loc_identity_kernel(int64_t n, int32_t* __restrict__ perm) {
+  const int64_t i = gtid();
+  if (i < n) perm[i] = int32_t(i);
 }
 
 // perm[off[key] + rank among the points of that key] = i.
@@ -1482,7 +1491,7 @@ extern "C" int tsne_knn(const float* X, int64_t n, int32_t d, int32_t k, int32_t
     TSNE_CHECK_LAUNCH();
   }
   // locality order (both paths): pivots, keys and their counts, offsets,
-  // scatter
+  // scatter; the input's own order for few points
   uint16_t* piv = reinterpret_cast<uint16_t*>(ws + L.o_piv);
   float* pnorm = reinterpret_cast<float*>(ws + L.o_pnorm);
   int* prank = reinterpret_cast<int*>(ws + L.o_prank);
@@ -1492,20 +1501,25 @@ extern "C" int tsne_knn(const float* X, int64_t n, int32_t d, int32_t k, int32_t
   int64_t* off = reinterpret_cast<int64_t*>(ws + L.o_off);
   int64_t* bsum = reinterpret_cast<int64_t*>(ws + L.o_bsum);
   int32_t* perm = reinterpret_cast<int32_t*>(ws + L.o_perm);
-  // (hist and cur are adjacent)
-  if ((rc = launch_fill<int>(hist, 2 * LOC_BINS, 0, s))) return rc;
-  const dim3 lgrid(unsigned(ceil_div(n, 256) < 2048 ? ceil_div(n, 256) : 2048));
-  const int m = loc_pivots(n), kp = loc_kpad(d);
-  hipLaunchKernelGGL(loc_pivot_kernel, dim3(LOC_PIV / 4), dim3(256), 0, s, X, n, d, m, kp, piv, pnorm);
-  TSNE_CHECK_LAUNCH();
-  hipLaunchKernelGGL(loc_rank_kernel, dim3(1), dim3(LOC_PIV), 0, s, piv, pnorm, m, kp, prank);
-  TSNE_CHECK_LAUNCH();
-  hipLaunchKernelGGL(loc_key_kernel, dim3(unsigned(ceil_div(n, 128))), dim3(256), 0, s, X, n, d, m, kp, piv, pnorm,
-                     prank, key, hist);
-  TSNE_CHECK_LAUNCH();
-  if ((rc = exclusive_scan<int>(hist, LOC_BINS, off, bsum, s))) return rc;
-  hipLaunchKernelGGL(loc_scatter_kernel, lgrid, dim3(256), 0, s, key, n, off, cur, perm);
-  TSNE_CHECK_LAUNCH();
+  if (n <= LOC_MIN_N) {
+    hipLaunchKernelGGL(loc_identity_kernel, dim3(unsigned(ceil_div(n, 256))), dim3(256), 0, s, n, perm);
+    TSNE_CHECK_LAUNCH();
+  } else {
+    // (hist and cur are adjacent)
+    if ((rc = launch_fill<int>(hist, 2 * LOC_BINS, 0, s))) return rc;
+    const dim3 lgrid(unsigned(ceil_div(n, 256) < 2048 ? ceil_div(n, 256) : 2048));
+    const int m = loc_pivots(n), kp = loc_kpad(d);
+    hipLaunchKernelGGL(loc_pivot_kernel, dim3(LOC_PIV / 4), dim3(256), 0, s, X, n, d, m, kp, piv, pnorm);
+    TSNE_CHECK_LAUNCH();
+    hipLaunchKernelGGL(loc_rank_kernel, dim3(1), dim3(LOC_PIV), 0, s, piv, pnorm, kp, prank);
+    TSNE_CHECK_LAUNCH();
+    hipLaunchKernelGGL(loc_key_kernel, dim3(unsigned(ceil_div(n, 128))), dim3(256), 0, s, X, n, d, m, kp, piv, pnorm,
+                       prank, key, hist);
+    TSNE_CHECK_LAUNCH();
+    if ((rc = exclusive_scan<int>(hist, LOC_BINS, off, bsum, s))) return rc;
+    hipLaunchKernelGGL(loc_scatter_kernel, lgrid, dim3(256), 0, s, key, n, off, cur, perm);
+    TSNE_CHECK_LAUNCH();
+  }
   if (precision == TSNE_KNN_FP32) {
     float* Xs = reinterpret_cast<float*>(ws + L.o_xs);
     float2* box = reinterpret_cast<float2*>(ws + L.o_box);

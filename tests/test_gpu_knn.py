@@ -253,10 +253,10 @@ def test_knn_bf16_queries_per_wave(dev, n):
     say("bf16 agreement", n, raw, adj)
 
 
-@pytest.mark.parametrize("n,d", [(15, 20), (17, 56), (143, 57), (32768, 8), (32769, 8)])
+@pytest.mark.parametrize("n,d", [(15, 20), (17, 56), (143, 57), (32768, 8), (32769, 8), (12288, 57), (12289, 57)])
 def test_knn_fp32_rows_per_wave(dev, n, d):
-    # 4 rows a wave up to 32,768 points and 56 coordinates (blocks of 16),
-    # 8 otherwise (blocks of 32); partial last blocks and waves
+    # 4 rows a wave up to 32,768 points (12,288 of more than 56 coordinates),
+    # blocks of 16; 8 above, blocks of 32; partial last blocks and waves
     say("knn fp32 rows per wave", n, d)
     k = min(n - 1, 12)
     X = separated_clusters(n, d, 9, n)
@@ -264,3 +264,15 @@ def test_knn_fp32_rows_per_wave(dev, n, d):
     oi, od = oracle.knn(X, k, rows=rows)
     gi, gd = gpu_knn(dev, X, k)
     check_knn(X, rows, gi[rows], gd[rows], oi, od)
+
+
+@pytest.mark.parametrize("n", [4096, 4097])
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+def test_knn_own_order(dev, n, prec):
+    # up to 4,096 points the sweeps take them in their own order
+    say("knn own order", n, prec)
+    d, k = 30, 20
+    X = separated_clusters(n, d, 5, 11)
+    oi, od = oracle.knn(X, k)
+    gi, gd = gpu_knn(dev, X, k, prec, n_cand=2 * k if prec == "bf16" else None)
+    check_knn(X, np.arange(n), gi, gd, oi, od, **({"min_agree": 0.999} if prec == "bf16" else {}))
