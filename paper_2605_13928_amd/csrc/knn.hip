@@ -229,7 +229,7 @@ constexpr int BOX_D = 32;
 // FP32: before a window the rows with more than F_TIGHTEN keys over k are
 // compacted, and if at least F_BY_ROW tiles of it stay, the test is repeated
 // with each row in place of the box of the wave's rows (a wave that holds rows
-// of two clusters has a box between them: 1.20 -> 1.02 ms at 20,011 points).
+// of two clusters has a box between them: 0.41 -> 0.30 ms at 20,011 points).
 constexpr int F_WIN0 = 4, B_WIN0 = 8;
 constexpr int64_t B_SMALL_N = 1 << 19;  // BF16: 16 queries a wave up to here, 32 above (knn_bf16_kernel)
 constexpr int F_TIGHTEN = 64, F_BY_ROW = 2;
@@ -253,22 +253,21 @@ __device__ __forceinline__ int next_window(int w, int w0) { return w < w0 ? w0 :
 // its waves rule out.  What bounds it is the last block, whose rows have
 // neighbours in many tiles; thresholds and counts are in one register each (a
 // lane per row: arrays of them went to scratch), the next tile in registers
-// while this one is consumed.  64-row blocks take 20 to 50 % longer than
-// 32-row ones from 30,000 clustered points up.  20,011 points x 50, 30
-// clusters, k = 90: 2.61 -> 0.61 ms; 100,000: 24.9 -> 2.2 ms; 40,000 without
-// clusters: 8.5 -> 5.9.
+// while this one is consumed.  20,011 points x 50, 30 clusters, k = 90: 2.61
+// -> 0.30 ms; 100,000: 24.9 -> 2.0 ms; 40,000 without clusters: 8.5 -> 5.9.
 
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 constexpr int F_COLS = 128;
 constexpr int F_DC = 56;
 constexpr int XJ_S = F_COLS + 4;  // LDS row strides: multiples of 4 floats keep the
                                   // 16-byte reads aligned and spread the stores' banks
-// 4 rows per wave, so that no block is long and all CUs have several: 20,011
-// points of 30 clusters 0.81 -> 0.61 ms, 1,500 points 0.22 -> 0.17.  8 rows
-// above 32,768 points (100,000: 2.20 against 2.32 ms); where a tile takes
-// several chunks of coordinates, which the rows of a block then re-read,
-// above the 768 blocks of 16 rows that are resident at once (12,000 points x
-// 200 without clusters: 4 rows 2.95, 8 rows 3.6 ms; 20,000: 9.0, 6.4).
+// 4 rows per wave, so that no block is long and all CUs have several: 1,500
+// points 0.22 -> 0.17 ms, 20,000 in 30 clusters of many sizes 1.12 -> 0.92
+// (of one size 0.30 both ways).  8 rows above 32,768 points (50,000: 0.87
+// against 0.90) and, where a tile takes several chunks of coordinates, which
+// the rows of a block then re-read, above the 768 blocks of 16 rows that are
+// resident at once (points x 200 without clusters: 12,000 2.95 with 4 rows,
+// 3.6 with 8; 20,000 9.0, 6.4).
 inline bool fknn_few_rows(int64_t n, int d) { return n <= (d <= F_DC ? 32768 : 12288); }
 
 // The rows of the locality order by column tiles, transposed: coordinate c of
@@ -635,7 +634,7 @@ constexpr int LOC_PIV = 256;     // pivots, at most; 64 points per pivot at leas
 constexpr int LOC_CEN = 32;
 // Few points keep their own order: at 1,500 x 50 the sweep of all tiles took
 // 0.115 ms, the order and the sweep after it 0.17 (4,000: 0.25 and 0.29;
-// 8,000: 0.46 and 0.45).
+// 8,000: 0.46 and 0.19 to 0.44).
 constexpr int64_t LOC_MIN_N = 4096;
 inline int loc_kpad(int d) { return (d + 31) / 32 * 32; }
 static_assert(LOC_MIN_N / 64 >= LOC_CEN, "at least a pivot per centre");
@@ -1005,10 +1004,11 @@ __device__ __forceinline__ void lds_read2_b128(uint32_t at0, uint32_t at1, bf16x
 // (identically) by its four lanes.
 // QT = 1 up to B_SMALL_N points, 2 above: few queries a wave make a narrow
 // box, little to wait for in the other waves of a block, five waves a SIMD
-// and short last blocks; many share a tile's load.  k = 90, QT = 1 / 2 / 4:
-// 20,000 points 0.86 / 1.2 / 1.8 ms, 250,000 6.8 / 7.3 / 8.7, 600,000 20.5 /
-// 20.4 / 21.7, 1,000,000 41 / 37 / 40; without clusters 200,000 17.7 / 17.6 /
-// 17.2, 600,000 105 / 84 / 83.
+// and short last blocks; many share a tile's load.  k = 90, QT = 1 / 2:
+// 20,000 points 0.64 / 0.85 ms, 250,000 5.7 / 6.3, 600,000 19.0 / 18.7,
+// 1,000,000 37 / 35; without clusters 200,000 18.0 / 17.8, 600,000 107 / 84.
+// (QT = 4: 1.4 to 2 times QT = 1 up to 100,000 points, 3 % more than QT = 2
+// at 1,000,000.)
 // The kernel is bound by the instructions of the appends (half of a wave's
 // time), the waits of its four waves for each other and the last blocks (the
 // heaviest of 3907 took 0.75 of the kernel at QT = 4).  What else cost was
