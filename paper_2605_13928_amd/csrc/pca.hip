@@ -657,7 +657,7 @@ __global__ __launch_bounds__(256) void pca_sign_kernel(const float* __restrict__
   __shared__ int bi[256];
   const int c = blockIdx.x, tid = threadIdx.x;
   float best = -1.0f;
-  int bidx = 0x7fffffff;
+  int bidx = tid < g ? tid : 0;  // a row of V whatever the comparisons say (of NaN they are all false)
   for (int j = tid; j < g; j += 256) {
     const float a = fabsf(V[int64_t(j) * PCA_L + c]);
     if (a > best) {  // j increases per thread: keeps the first maximum

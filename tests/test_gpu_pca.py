@@ -163,3 +163,17 @@ def test_pca_low_rank(dev):
     assert np.abs(sv - s[:r]).max() <= 2e-5 * s[0]
     assert np.all(np.abs(np.sum(comp * Vt[:r], axis=1)) > 1 - 1e-4)
     np.testing.assert_allclose(comp @ comp.T, np.eye(r), atol=2e-5)
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_pca_non_finite_input(dev, bad):
+    # one such entry makes its column's mean, and with it every product with
+    # X, NaN: the call returns NaN and no comparison that is false for NaN
+    # leaves an index at a value outside the matrices
+    say("pca non-finite", bad)
+    n, g, k = 1000, 300, 20
+    X = synth.make_expression(n, g, 91)
+    X[123, 45] = bad
+    sc, comp, sv, mu = run(dev, X, k, synth.make_omega(g, 92), 2)
+    assert np.isnan(sc).all() and np.isnan(comp).all()
+    assert not np.isfinite(mu[45]) and np.isfinite(np.delete(mu, 45)).all()
