@@ -624,24 +624,26 @@ __global__ __launch_bounds__(256, 1) void pca_jacobi_kernel(const double* __rest
     if (!rough) break;
   }
   const double l = sqrt(norm2());
-  int rank = 0;  // place of this column in descending order
+  // place of this column in descending order, a NaN after all numbers: the
+  // places are a permutation whatever the input
+  const double key = l >= 0.0 ? l : -1.0;
+  int rank = 0;
   for (int q = 0; q < PCA_L; ++q) {
-    const double lq = readlane_d(l, q);
-    rank += lq > l || (lq == l && q < c) ? 1 : 0;
+    const double kq = readlane_d(key, q);
+    rank += kq > key || (kq == key && q < c) ? 1 : 0;
   }
-  rank = rank < PCA_L ? rank : PCA_L - 1;
   if (w == 0) lam[rank] = ldexp(l, ex);
   const double inv = l > 0.0 ? 1.0 / l : 0.0;
 #pragma unroll
   for (int r = 0; r < NR; ++r) U[(NR * w + r) * PCA_L + rank] = a[r] * inv;
 }
 
-// W1 = U diag(1/s) (float), s = sqrt(max(lam, 0)).
+// W1 = U diag(1/s) (float), s = sqrt(lam); 0 for s = 0.
 __global__ __launch_bounds__(256) void pca_post_eig_kernel(const double* __restrict__ lam,
                                                            const double* __restrict__ U, float* __restrict__ W1) {
   for (int e = threadIdx.x; e < PCA_L * PCA_L; e += 256) {
-    const double s = sqrt(fmax(lam[e % PCA_L], 0.0));
-    W1[e] = float(s > 0.0 ? U[e] / s : 0.0);
+    const double s = sqrt(lam[e % PCA_L]);  // (lam >= 0, or NaN)
+    W1[e] = float(s == 0.0 ? 0.0 : U[e] / s);
   }
 }
 
@@ -681,7 +683,7 @@ __global__ __launch_bounds__(256) void pca_sign_kernel(const float* __restrict__
   }
   const float sign = V[int64_t(bi[0]) * PCA_L + c] < 0.0f ? -1.0f : 1.0f;
   for (int j = tid; j < g; j += 256) comps[int64_t(c) * g + j] = sign * V[int64_t(j) * PCA_L + c];
-  const double s = sqrt(fmax(lam[c], 0.0));
+  const double s = sqrt(lam[c]);
   if (tid == 0) sv[c] = s;
   if (tid < PCA_L) W2[tid * PCA_L + c] = float(U[tid * PCA_L + c] * s * double(sign));
 }

@@ -177,3 +177,21 @@ def test_pca_non_finite_input(dev, bad):
     sc, comp, sv, mu = run(dev, X, k, synth.make_omega(g, 92), 2)
     assert np.isnan(sc).all() and np.isnan(comp).all()
     assert not np.isfinite(mu[45]) and np.isfinite(np.delete(mu, 45)).all()
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_pca_non_finite_input_uses_nothing_stale(dev, bad):
+    # the eigenvalues' places are a permutation for NaN too: every singular
+    # value is written, and no output depends on what the workspace held
+    say("pca non-finite, workspace", bad)
+    n, g, k = 500, 128, 64
+    X = synth.make_expression(n, g, 93)
+    X[7, 3] = bad
+    Xd, Om = to_dev(X, dev), to_dev(synth.make_omega(g, 94), dev)
+    ws = api.Workspace()
+    api.pca(to_dev(synth.make_expression(n, g, 95), dev), k, Om, 2, ws=ws)  # sizes it, leaves finite numbers in it
+    for fill in (None, 0, 0x3F):
+        if fill is not None:
+            ws.buf.fill_(fill)
+        sc, comp, sv, _ = api.pca(Xd, k, Om, 2, ws=ws)
+        assert torch.isnan(sv).all() and torch.isnan(comp).all() and torch.isnan(sc).all()
