@@ -195,3 +195,30 @@ def test_pca_non_finite_input_uses_nothing_stale(dev, bad):
             ws.buf.fill_(fill)
         sc, comp, sv, _ = api.pca(Xd, k, Om, 2, ws=ws)
         assert torch.isnan(sv).all() and torch.isnan(comp).all() and torch.isnan(sc).all()
+
+
+@pytest.mark.parametrize("rows", [1, 2, 5, 20, 63])
+def test_pca_few_distinct_rows(dev, rows):
+    # `rows` distinct cells, repeated (1: a constant X): equal rows stay equal
+    # bit for bit in every product, so the 64 columns of the subspace are
+    # exactly dependent and the Gram matrices' last pivots are zero or
+    # rounding errors of either sign.  Rank rows - 1 after centring: those
+    # components and values as of the dense SVD, the rest zero or rounding
+    # (the mean's, 6e-8 of the entries, over sqrt(n)).
+    say("pca few distinct rows", rows)
+    rng = np.random.default_rng(96 + rows)
+    n, g = 700, 96
+    r = rows - 1
+    k = max(r, 1)
+    X = (3.0 * rng.standard_normal((rows, g)) + 1.0)[np.arange(n) % rows].astype(np.float32)
+    sc, comp, sv, mu = run(dev, X, k, synth.make_omega(g, 97), 2)
+    assert np.isfinite(sc).all() and np.isfinite(comp).all() and np.isfinite(sv).all()
+    if r == 0:
+        assert np.all(sv <= 1e-4) and np.all(np.abs(sc) <= 1e-4)
+        return
+    U, s, Vt = np.linalg.svd(X.astype(np.float64) - X.astype(np.float64).mean(0), full_matrices=False)
+    assert np.abs(sv - s[:r]).max() <= 2e-5 * s[0], (sv, s[:r])
+    # spans instead of vectors: neighbouring values may be close
+    np.testing.assert_allclose(comp.T @ (comp @ Vt[:r].T), Vt[:r].T, atol=1e-3)
+    np.testing.assert_allclose(comp @ comp.T, np.eye(r), atol=1e-3)
+    np.testing.assert_allclose(sc @ comp, (U[:, :r] * s[:r]) @ Vt[:r], atol=1e-3 * s[0] / np.sqrt(n))
