@@ -443,13 +443,13 @@ __device__ __forceinline__ double readlane_d(double v, int src) {
 // with E G = R, i.e. E = R^-T; applied to X = I alongside, they leave X =
 // R^-T (lower triangular).  Rinv = X^T (float, 64 x 64 row-major) is the W of
 // the next product Q = Y Rinv.
-// A pivot at the limit leaves a zero column in Rinv and in Q: the columns of Y
-// are dependent there (a constant X, fewer than 64 distinct rows), and its
-// root would scale rounding errors to an infinity or to a column that is not
-// orthogonal to the others.  With a shift only a pivot of zero is; without
-// one, after the shifted pass, the norms of a basis are 0.4 to 1 and those of
-// dependent columns 1e-4 (FP32) and less: the limit is the square of 1e-3 of
-// the mean norm, at which a kept column is orthogonal to 6e-5.
+// Pivots are taken as at least `lim`: where the columns of Y are dependent (a
+// constant X, fewer than 64 distinct rows) they are zero or rounding errors of
+// either sign, whose roots would scale such a column to infinity or to one
+// that is not orthogonal to the others.  After the shifted pass the squared
+// norms of a basis are 0.2 to 1 and what is left of dependent columns some
+// 1e-4 and less: a limit of 1e-6 of the mean keeps it below 1e-3 of a basis
+// vector, or orthogonal to 6e-5.
 // What bounds it: a chain of 64 pivots.  Lane c holds column c of A and X in
 // registers, wave w the rows 16 u + 4 w .. + 3 (u < 4).  A step takes the four
 // rows of one wave: its pivots one after another, their effect on the four
@@ -463,7 +463,8 @@ __global__ __launch_bounds__(256, 1) void pca_cholinv_kernel(const double* __res
   __shared__ __attribute__((aligned(16))) double rowR[2][PCA_L][4], rowX[2][PCA_L][4];  // [buffer][column][row]
   const int w = threadIdx.x >> 6, c = threadIdx.x & 63;
   const double mean = wave_sum_d(Gin[c * (PCA_L + 1)]) / PCA_L;
-  const double add = shift * mean, lim = shift > 0.0 ? 1e-300 : fmax(1e-300, 1e-6 * mean);
+  const double add = shift * mean;
+  const double lim = readlane_d(mean > 0.0 ? (shift > 0.0 ? 1e-300 : 1e-6 * mean) : 1.0, 0);
   double a[4][4], x[4][4];
 #pragma unroll
   for (int u = 0; u < 4; ++u)
@@ -481,7 +482,7 @@ __global__ __launch_bounds__(256, 1) void pca_cholinv_kernel(const double* __res
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
           const double d = readlane_d(a[u0][p], j + p);
-          const double ri = d > lim ? rsqrt_d(d) : 0.0;
+          const double ri = rsqrt_d(d > lim ? d : lim);
           a[u0][p] *= ri;
           x[u0][p] *= ri;
 #pragma unroll
