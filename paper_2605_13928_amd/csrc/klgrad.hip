@@ -281,27 +281,34 @@ __global__ __launch_bounds__(256) void finalize_tsne_kernel(
 // per row: g_i = 4 (alpha A_i - R_i / Z), the same bits as the kernel above.
 //
 // What bounds the gather of y_j: a wave's 64 random 8-byte reads are 64 lines
-// of 128 bytes from L2, and at 10^6 points (149 M entries, 126 M lines, 85 %
-// of them in L2) that kernel ran at 17 TB/s of line traffic, 0.95 ms.  But
-// the rows of a block are neighbours, so their ~9,500 entries name only some
-// hundreds of points.  The block therefore reads each of those once, into a
+// of 128 bytes from L2.  But the rows of a block are neighbours and name some
+// points several times, so the block reads each of those once, into a
 // direct-mapped table in LDS: every entry writes its column to its slot's
 // tag, the owners of the slots fetch the points that won, and an entry reads
-// its point from LDS, or from memory when another column took its slot.  (A
-// graph without locality loses nothing but the table's passes: every slot's
-// point was needed by some entry.)  16 lanes take a row, lane l its entries
-// l, l + 16, ... in order, FLT_EPT at a time.  A row of more than FLT_LONG
-// entries is taken by the whole block, its terms going through LDS.
-// Measured at 10^6 points, 149 M entries: 0.95 -> 0.655 ms (half the lines
-// from L2; the stream of entries alone, whole rows in a random order, takes
-// about 0.5 ms); 70,001 points 68 -> 48 us.  Blocks of 32 rows with half
-// the table were 2 % slower, of 16 rows 10 %.
+// its point from LDS, or from memory when another column took its slot.
+// 16 lanes take a row, lane l its entries l, l + 16, ... in order, FLT_EPT at
+// a time: a pass of FLT_PASS entries of every row.  How long a block takes is
+// set by its passes more than by the points it saves: of a kNN graph in 50
+// dimensions, where some points are named by many rows, the longest row of a
+// block is about four times the mean one (c5: 145 entries, and four passes up
+// to the longest), and with passes up to it the kernel took 1.59 ms where the
+// one above took 1.27.  The passes therefore stop where less than
+// half of the rows fill half of one, and the entries past them are dealt
+// flat over the threads, their points from memory.
+// The whole call at 10^6 points, the kernel above in this one's place / passes
+// up to the longest row / as it is: c5's graph after 1,000 iterations 1.47 /
+// 1.77 / 1.36 ms, a graph in 2 dimensions 0.95 / 0.76 / 0.72, one along the
+// embedding's own order 1.21 / 0.92 / 0.88; c5 at 70,001 points 0.183 / 0.206 /
+// 0.158.  An embedding without any locality (the first hundred iterations at
+// 10^6 points) 1.80 / 2.05 / 1.90: nothing is saved there and the entries go
+// through the table all the same; reading them directly where nearly all slots
+// are filled made every block slower (1.36 -> 1.45: registers).
 constexpr int FLT_ROWS = 64;
 constexpr int FLT_T = 16 * FLT_ROWS;  // threads
 constexpr int FLT_EPT = 10;  // entries of a lane per pass
+constexpr int FLT_PASS = 16 * FLT_EPT;  // entries of a row per pass
 constexpr int FLT_LOG = 12;
 constexpr int FLT_SLOTS = 1 << FLT_LOG;  // points of the table
-constexpr int FLT_LONG = 1024;
 
 __global__ __launch_bounds__(FLT_T, 8) void finalize_local_kernel(
     const float2* __restrict__ Y, int64_t n, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
@@ -311,50 +318,71 @@ __global__ __launch_bounds__(FLT_T, 8) void finalize_local_kernel(
 #pragma clang fp contract(off)
   __shared__ int32_t tag[FLT_SLOTS];
   __shared__ float2 pt[FLT_SLOTS];
+  __shared__ float2 yrow[FLT_ROWS];
+  __shared__ int64_t rp0[FLT_ROWS];      // first CSR entry of each row of the block
+  __shared__ int64_t rlen[FLT_ROWS];     // ... and their number
+  __shared__ int64_t cum[FLT_ROWS + 1];  // flat offsets of the rows' entries past the passes
   __shared__ double red[4];
-  __shared__ int maxlen;
+  __shared__ int passes_s;
   const int tid = threadIdx.x, g = tid >> 4, sl = tid & 15;
   const uint32_t n32 = uint32_t(n);  // n <= 2^31
   const int64_t p = xcd_block() * FLT_ROWS + g;
   const int64_t row = p < n ? int64_t(rows[p]) : n;
-  int64_t a = 0;
-  int len = 0;
+  int64_t a = 0, len = 0;
   float2 yi = make_float2(0.0f, 0.0f), Ri = yi;
   if (row < n) {
     a = row_ptr[row];
-    len = int(row_ptr[row + 1] - a);
+    len = row_ptr[row + 1] - a;
     yi = Y[row];
     Ri = R[row];
   }
-  if (tid == 0) maxlen = 0;
+  if (sl == 0) {
+    yrow[g] = yi;
+    rp0[g] = a;
+    rlen[g] = len;
+  }
   for (int q = tid; q < FLT_SLOTS; q += FLT_T) tag[q] = -1;
-  const double zt = tid < 256 ? zblock_thread_sum(Zblock, nZ) : 0.0;
-  __syncthreads();
-  if (sl == 0) atomicMax(&maxlen, len);
   // Z as finalize_tsne_kernel sums it: 256 threads, four wave sums in order
-  const double zw = wave_sum_d(zt);
+  const double zw = wave_sum_d(tid < 256 ? zblock_thread_sum(Zblock, nZ) : 0.0);
   if (tid < 256 && lane_id() == 0) red[tid >> 6] = zw;
+  __syncthreads();
+  if (tid < FLT_ROWS) {  // wave 0, a row per lane
+    int64_t c = rlen[tid];
+    // a further pass while half of the rows fill half of it
+    int passes = 1;
+    while (__popcll(__ballot(c > int64_t(passes) * FLT_PASS + FLT_PASS / 2)) >= FLT_ROWS / 2) ++passes;
+    c = c > int64_t(passes) * FLT_PASS ? c - int64_t(passes) * FLT_PASS : 0;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int64_t u = int64_t(__shfl_up(uint64_t(c), o));
+      if (tid >= o) c += u;
+    }
+    cum[tid + 1] = c;
+    if (tid == 0) {
+      cum[0] = 0;
+      passes_s = passes;
+    }
+  }
   __syncthreads();
   const double Z = (red[0] + red[1]) + (red[2] + red[3]);
   if (blockIdx.x == 0 && tid == 0 && Z_out) *Z_out = Z;
-  const bool lng = maxlen > FLT_LONG;  // (the same in every thread)
-  const int top = lng ? FLT_LONG : maxlen;
-  const int own = len <= FLT_LONG ? len : 0;
-  const int32_t* cp = col + a;
-  const float* vp = val + a;
+  const int64_t top = int64_t(passes_s) * FLT_PASS;  // (the same in every thread)
+  const int64_t own = len < top ? len : top;
   float ax = 0.0f, ay = 0.0f;
   int32_t seen[FLT_SLOTS / FLT_T];  // the tags this thread's slots were last filled for
 #pragma unroll
   for (int q = 0; q < FLT_SLOTS / FLT_T; ++q) seen[q] = -1;
   auto slot_of = [](int32_t j) { return int((uint32_t(j) * 2654435761u) >> (32 - FLT_LOG)); };
-  for (int m0 = 0; m0 < top; m0 += 16 * FLT_EPT) {
-    const bool some = m0 + sl < own;
+  for (int64_t m0 = 0; m0 < top; m0 += FLT_PASS) {
+    const int left = int(own - m0 < FLT_PASS ? own - m0 : FLT_PASS) - sl;  // entries 0, 16, ... below it
+    const int32_t* cp = col + a + m0 + sl;
+    const float* vp = val + a + m0 + sl;
     int32_t jj[FLT_EPT];
     float pp[FLT_EPT];
-    if (some) {
+    if (left > 0) {
 #pragma unroll
       for (int u = 0; u < FLT_EPT; ++u) {
-        const int e = m0 + sl + 16 * u < own ? m0 + sl + 16 * u : m0 + sl;
+        const int e = 16 * u < left ? 16 * u : 0;
         // (not non-temporal: two loads share a line of 128 bytes)
         jj[u] = cp[e];
         pp[u] = vp[e];
@@ -378,7 +406,7 @@ __global__ __launch_bounds__(FLT_T, 8) void finalize_local_kernel(
       }
     }
     __syncthreads();
-    if (some) {
+    if (left > 0) {
 #pragma unroll
       for (int u = 0; u < FLT_EPT; ++u) {
         const int sj = slot_of(jj[u]);
@@ -386,44 +414,60 @@ __global__ __launch_bounds__(FLT_T, 8) void finalize_local_kernel(
         const float dx = yi.x - yj.x, dy = yi.y - yj.y;
         const float q = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, 1.0f));
         const float pw = pp[u] * __builtin_amdgcn_rcpf(q);
-        if (m0 + sl + 16 * u < own) {
+        if (16 * u < left) {
           ax += pw * dx;
           ay += pw * dy;
         }
       }
     }
-    __syncthreads();  // the tags are rewritten by the next pass
+    __syncthreads();  // the tags are rewritten by the next pass, the points by the entries below
   }
-  if (lng) {
-    for (int gg = 0; gg < FLT_ROWS; ++gg) {
-      const int64_t pg = xcd_block() * FLT_ROWS + gg;
-      if (pg >= n) break;
-      const int64_t rg = rows[pg], ag = row_ptr[rg], lg = row_ptr[rg + 1] - ag;
-      if (lg <= FLT_LONG) continue;
-      const float2 yg = Y[rg];
-      for (int64_t c0 = 0; c0 < lg; c0 += FLT_SLOTS) {
-        for (int64_t e = c0 + tid; e < lg && e < c0 + FLT_SLOTS; e += FLT_T) {
-          int32_t j = col[ag + e];
-          float pv = val[ag + e];
-          if (j < 0 || j >= n) {
-            j = 0;
-            pv = 0.0f;
-          }
-          const float2 yj = Y[j];
-          const float dx = yg.x - yj.x, dy = yg.y - yj.y;
-          const float q = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, 1.0f));
-          const float pw = pv * __builtin_amdgcn_rcpf(q);
-          pt[e - c0] = make_float2(pw * dx, pw * dy);
-        }
-        __syncthreads();
-        if (g == gg)
-          for (int64_t e = c0 + sl; e < lg && e < c0 + FLT_SLOTS; e += 16) {
-            ax += pt[e - c0].x;
-            ay += pt[e - c0].y;
-          }
-        __syncthreads();
-      }
+  // the entries past the passes, a chunk of the table's size at a time, flat
+  // over the threads; the terms go to their rows' lanes through LDS
+  const int64_t F = cum[FLT_ROWS], ga = cum[g], gb = cum[g + 1];
+  constexpr int TE = FLT_SLOTS / FLT_T;
+  for (int64_t c0 = 0; c0 < F; c0 += FLT_SLOTS) {
+    int32_t jj[TE];
+    float pp[TE];
+    int rr[TE];
+#pragma unroll
+    for (int u = 0; u < TE; ++u) {
+      const int64_t f = c0 + tid + FLT_T * u < F ? c0 + tid + FLT_T * u : F - 1;
+      int r = 0;  // the last row with cum[r] <= f
+#pragma unroll
+      for (int h = FLT_ROWS / 2; h > 0; h >>= 1) r += cum[r + h] <= f ? h : 0;
+      rr[u] = r;
+      const int64_t e = rp0[r] + top + (f - cum[r]);
+      jj[u] = col[e];
+      pp[u] = val[e];
     }
+    float2 yj[TE];
+#pragma unroll
+    for (int u = 0; u < TE; ++u) {
+      if (uint32_t(jj[u]) >= n32) {
+        jj[u] = 0;
+        pp[u] = 0.0f;
+      }
+      yj[u] = Y[jj[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < TE; ++u) {
+      const float2 y = yrow[rr[u]];
+      const float dx = y.x - yj[u].x, dy = y.y - yj[u].y;
+      const float q = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, 1.0f));
+      const float pw = pp[u] * __builtin_amdgcn_rcpf(q);
+      pt[tid + FLT_T * u] = make_float2(pw * dx, pw * dy);
+    }
+    __syncthreads();
+    const int64_t lo = ga > c0 ? ga : c0, hi = gb < c0 + FLT_SLOTS ? gb : c0 + FLT_SLOTS;
+    int64_t f = ga + sl;  // this lane's entries of row g: ga + sl + 16 m
+    if (f < lo) f += (lo - f + 15) / 16 * 16;
+    for (; f < hi; f += 16) {
+      const float2 c = pt[f - c0];
+      ax += c.x;
+      ay += c.y;
+    }
+    __syncthreads();
   }
   ax = row16_sum(ax);
   ay = row16_sum(ay);

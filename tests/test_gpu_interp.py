@@ -202,10 +202,10 @@ def test_fft_grad_box_occupancies(dev, p):
 
 
 def test_fft_grad_long_rows(dev):
-    """The attraction of the box order takes rows in passes of 160 entries and
-    rows of more than 1,024 by the whole block: row lengths around those
-    edges, empty rows and columns outside [0, n) (which contribute nothing),
-    in a last block that is not full.  Against the index order, bit for bit,
+    """The attraction of the box order takes the rows of a block in passes of
+    160 entries, and what is longer over the whole block: row lengths around
+    the passes' edges and far past them, empty rows and columns outside
+    [0, n) (which contribute nothing), in a last block that is not full.  Against the index order, bit for bit,
     and against FP64 sums (an FP32 sum of m terms is within m 2^-24 of the
     terms' absolute sum; the longest row has 7,000)."""
     say("fft grad long rows")
@@ -237,3 +237,27 @@ def test_fft_grad_long_rows(dev):
     tol = 4.0 * (lens[:, None] * 2.0**-24 + 1e-6) * absA + 1e-6 * np.abs(4.0 * Ro / Zo) + 1e-12
     err = np.abs(a.cpu().numpy() - 4.0 * (A - Ro / Zo))
     assert (err <= tol).all(), (err / tol).max()
+
+
+# Rows of a block in passes of 160 entries while half of the rows fill half of
+# one, what lies past them flat over the block, 4,096 at a time: all rows at
+# the last length without a second pass and the first with one, half of the
+# rows long, some, and so many that their ends take several chunks.
+@pytest.mark.parametrize("lens", ["240", "241", "half", "some", "many"])
+def test_fft_grad_uneven_rows(dev, lens):
+    say("fft grad uneven rows", lens)
+    rng = np.random.default_rng(43)
+    n = 705
+    if lens in ("240", "241"):
+        m = np.full(n, int(lens))
+    else:
+        share = {"half": 0.5, "some": 0.05, "many": 0.4}[lens]
+        m = np.where(rng.random(n) < share, rng.integers(600, 700, n), rng.integers(0, 40, n))
+    row_ptr = np.concatenate([[0], np.cumsum(m)]).astype(np.int64)
+    col = np.concatenate([np.sort(rng.choice(n, q, replace=False)) for q in m]).astype(np.int32)
+    val = rng.uniform(0.5, 1.5, col.size).astype(np.float32) / np.float32(col.size)
+    P = api.SparseP(to_dev(row_ptr, dev), to_dev(col, dev), to_dev(val, dev), None, n)
+    Y = to_dev(synth.random_embedding(n, 8.0, 4300), dev)
+    a, Za, _ = api.kl_grad_fft(Y, P, 1.0, want_Z=True)
+    b, Zb, _ = api.kl_grad_fft(Y, P, 1.0, want_Z=True, want_kl=True)  # the rows in index order
+    assert torch.equal(a, b) and torch.equal(Za, Zb)
