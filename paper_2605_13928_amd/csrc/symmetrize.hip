@@ -17,7 +17,8 @@
 //   5. tpos: the entries (i, j), numbered in (i, j) order, stably sorted by j
 //      are in the order of their transposes (j, i), and the pattern is
 //      symmetric, so the number at place p is the position of the transpose
-//      of entry p: a radix sort of the columns with their positions
+//      of entry p: a radix sort of the columns with their positions (few
+//      entries search row col[e] instead)
 // What bounds it: the passes over the n k directed and about 1.6 n k stored
 // entries (about 15 GB at 10^6 points, k = 90).  The values travel with the
 // sort (12 bytes per entry and pass): gathered afterwards by entry number,
@@ -218,6 +219,32 @@ __global__ __launch_bounds__(256) void sym_write_kernel(int64_t n, int k, int sb
   }
 }
 
+// tpos of few entries (2 n k at most SYM_SEARCH): a thread per stored entry e
+// finds its row, then the row's number among the entries of row col[e].  The
+// sort's launches take some 40 us however few the entries are, the searches
+// as long as their random lines.  Whole call, sort / search: 1,000 x 15 113 /
+// 78 us, 5,000 x 90 152 / 128, 20,000 x 30 168 / 151; 10,000 x 90 173 / 172,
+// 20,000 x 90 211 / 273.
+constexpr int64_t SYM_SEARCH = 1200000;
+__global__ __launch_bounds__(256) void sym_tpos_kernel(int64_t n, const int64_t* __restrict__ row_ptr,
+                                                       const int32_t* __restrict__ col, int32_t* __restrict__ tpos) {
+  const int64_t e = gtid();
+  if (e >= row_ptr[n]) return;
+  int32_t row = 0;  // the last row that starts at or before e
+  for (int32_t m = int32_t(n); m > 1;) {
+    const int32_t half = m >> 1;
+    row = row_ptr[row + half] <= e ? row + half : row;
+    m -= half;
+  }
+  const int32_t j = col[e];
+  int32_t t = -1;
+  if (j >= 0 && j < n) {  // (else an input that is reported)
+    const int64_t a = row_ptr[j];
+    t = int32_t(a + lower_bound_i32(col + a, int(row_ptr[j + 1] - a), row));
+  }
+  tpos[e] = t;
+}
+
 __global__ void sym_nnz_kernel(const int64_t* __restrict__ row_ptr, int64_t n, const int* __restrict__ err,
                                int64_t* __restrict__ nnz) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *nnz = *err ? int64_t(-1) : row_ptr[n];
@@ -302,7 +329,10 @@ int symmetrize_impl(const int32_t* nbr_idx, const float* P_cond, int64_t n, int3
   auto write = k <= 64 ? sym_write_kernel<MODE, 1> : (k <= 128 ? sym_write_kernel<MODE, 2> : sym_write_kernel<MODE, 4>);
   hipLaunchKernelGGL(write, g_rows, b, 0, s, n, int(k), sb, nbr_idx, P_cond, in_ptr, s_src, s_val, row_ptr, col, val);
   TSNE_CHECK_LAUNCH();
-  if (tpos) {
+  if (tpos && 2 * nk <= SYM_SEARCH) {
+    hipLaunchKernelGGL(sym_tpos_kernel, dim3(unsigned(ceil_div(2 * nk, 256))), b, 0, s, n, row_ptr, col, tpos);
+    TSNE_CHECK_LAUNCH();
+  } else if (tpos) {
     // the lists are no longer needed
     uint32_t* tp = reinterpret_cast<uint32_t*>(tpos);
     const RsBuffers t1{buf, buf + 2 * nk, nullptr}, t2{buf + 4 * nk, tp, nullptr};

@@ -113,3 +113,15 @@ def test_symmetrize_sort_edges(dev, n, k):
     Pc /= Pc.sum(1, keepdims=True)
     S, G = run_both(dev, idx, Pc)
     check(S, G, n)
+
+
+# tpos by searching (2 n k to 1,200,000: the last such size and the first that
+# is sorted) and by a sort of two and of three passes
+@pytest.mark.parametrize("n,k", [(6000, 100), (6001, 100), (65_537, 10), (131_073, 5)])
+def test_symmetrize_tpos_routes(dev, n, k):
+    say("symmetrize tpos routes", n, k)
+    idx, _ = synth.random_knn_graph(n, k, n + k)
+    Pc = np.random.default_rng(n).random((n, k))
+    Pc /= Pc.sum(1, keepdims=True)
+    S, G = run_both(dev, idx, Pc)
+    check(S, G, n)
