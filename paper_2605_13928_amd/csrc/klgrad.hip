@@ -14,10 +14,7 @@
 
 namespace tsne {
 
-// Finalize, 16 rows per block: rows 16 b .. 16 b + 15, or with `rows` the
-// rows rows[16 c .. 16 c + 15] (a permutation of 0 .. n - 1: a spatial order
-// makes the y_j gathers of the rows resident together overlap in L2), with c
-// the block's place in the eighth of the blocks on its XCD.
+// Finalize, 16 rows per block: rows 16 b .. 16 b + 15.
 // Attraction A_i = sum_{e in row i} p_e w_e (y_i - y_j), entry-parallel: the
 // block's CSR entries, numbered flat over its rows, are dealt to all 256
 // threads in chunks of FIN_CHUNK (thread t takes flat entries c0 + t + 256 m,
@@ -51,7 +48,7 @@ __global__ __launch_bounds__(256) void finalize_tsne_kernel(
     const float* __restrict__ val, float alpha, const float2* __restrict__ Rpart, const float* __restrict__ Zrowpart,
     const float2* __restrict__ Apart, int64_t ns, bool grouped, const double* __restrict__ Zblock, int64_t nZ,
     float2* __restrict__ grad, double* __restrict__ Zrow, double* __restrict__ Z_out, double* __restrict__ klpart,
-    FusedStep st, unsigned long long* __restrict__ nonfinite, const int32_t* __restrict__ rows) {
+    FusedStep st, unsigned long long* __restrict__ nonfinite) {
   constexpr int NPR = ATTP ? 5 : 3;  // per-thread sums: R x, R y, Z_row (, A x, A y)
   __shared__ float2 contrib[ATTP ? 1 : FIN_CHUNK];
   __shared__ int64_t rp0[FIN_ROWS];      // first CSR entry of each row of the block
@@ -62,17 +59,9 @@ __global__ __launch_bounds__(256) void finalize_tsne_kernel(
   __shared__ float2 att[FIN_ROWS];
   const int tid = threadIdx.x;
   const int g = tid >> 4, sl = tid & 15;
-  // With a row order, workgroups (dealt round-robin over the 8 XCDs) take
-  // their group of 16 from the contiguous eighth of the order that belongs
-  // to their XCD, so each XCD's L2 holds the y_j of one compact region.
-  const int64_t r0 = (rows ? xcd_block() : int64_t(blockIdx.x)) * FIN_ROWS;
-  // the block's row of local index q (n past the last one)
-  auto row_of = [&](int q) -> int64_t {
-    const int64_t p = r0 + q;
-    return p < n ? (rows ? int64_t(rows[p]) : p) : n;
-  };
-  const int64_t prow = row_of(sl);  // partial-sum row of this thread
-  const int64_t myrow = tid < FIN_ROWS ? row_of(tid) : n;
+  const int64_t r0 = int64_t(blockIdx.x) * FIN_ROWS;
+  const int64_t prow = r0 + sl;                        // partial-sum row of this thread
+  const int64_t myrow = tid < FIN_ROWS ? r0 + tid : n;  // (n or more: none)
 
   // --- loads with no dependences -----------------------------------------
   int64_t len = 0;
@@ -519,8 +508,7 @@ int finalize_csr_launch(const float* Y, int64_t n, const int64_t* row_ptr, const
                      reinterpret_cast<const float2*>(Y), n, row_ptr, col, val, alpha,
                      reinterpret_cast<const float2*>(R), static_cast<const float*>(nullptr),
                      static_cast<const float2*>(nullptr), int64_t(1), false, Zblock, nZ,
-                     reinterpret_cast<float2*>(grad), static_cast<double*>(nullptr), Z, kp, FusedStep{}, nonfinite,
-                     rows);
+                     reinterpret_cast<float2*>(grad), static_cast<double*>(nullptr), Z, kp, FusedStep{}, nonfinite);
   TSNE_CHECK_LAUNCH();
   if (kl) {
     hipLaunchKernelGGL(kl_reduce_kernel, dim3(1), dim3(256), 0, s, kp, nfin, Zblock, nZ, kl);
@@ -729,8 +717,7 @@ int klgrad_launch(const KlGradPlan& L, char* ws, const float* Y, int64_t n, cons
   const FusedStep st = step ? *step : FusedStep{};
 #define TSNE_FIN(STEP, A, GR, KLP, NF)                                                                      \
   hipLaunchKernelGGL((finalize_tsne_kernel<STEP, A>), fgrid, block, 0, s, Y2, n, row_ptr, col, val, alpha, R2, \
-                     Zrowpart, Apart, g.ns, grp, Zblock, g.nwg, GR, Zrow, Z, KLP, st, NF,                    \
-                     static_cast<const int32_t*>(nullptr))
+                     Zrowpart, Apart, g.ns, grp, Zblock, g.nwg, GR, Zrow, Z, KLP, st, NF)
   if (fused) {
     if (step) TSNE_FIN(true, true, nullptr, nullptr, nonfinite);
     else TSNE_FIN(false, true, gr, nullptr, nonfinite);

@@ -69,9 +69,10 @@ int klgrad_launch(const KlGradPlan& L, char* ws, const float* Y, int64_t n, cons
 // block partials (Z = their sum, in index order) were computed elsewhere:
 // attraction over the CSR rows, g = 4 (alpha A - R / Z), optional Z and KL
 // outputs.  klpart: finalize_kl_bytes(n) of workspace (used when kl).
-// rows (nullable): a permutation of the rows, the order the blocks take them
-// in (a row's result does not depend on it; the KL's per-block sums do, so
-// pass none when kl is requested and the order is not reproducible).
+// rows (nullable): a permutation of the rows, near ones together, the order
+// the blocks take them in (finalize_local_kernel).  A row's result does not
+// depend on it; a requested KL's per-block sums would, so with kl the rows go
+// in index order.
 size_t finalize_kl_bytes(int64_t n);
 int finalize_csr_launch(const float* Y, int64_t n, const int64_t* row_ptr, const int32_t* col, const float* val,
                         float alpha, const float* R, const double* Zblock, int64_t nZ, float* grad, double* Z,
