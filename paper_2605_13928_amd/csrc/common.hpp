@@ -305,19 +305,6 @@ __device__ __forceinline__ void wave_sort32(uint32_t (&v)[EPL]) {
   }
 }
 
-// Read register r of lane `src` (both wave-uniform) as a uniform value.
-template <int EPL>
-__device__ __forceinline__ uint64_t wave_pick(const uint64_t (&v)[EPL], int e) {
-  const int r = e >> 6, src = e & 63;
-  uint64_t x = 0;
-#pragma unroll
-  for (int t = 0; t < EPL; ++t)
-    if (t == r) x = v[t];
-  uint32_t lo = __builtin_amdgcn_readlane(uint32_t(x), src);
-  uint32_t hi = __builtin_amdgcn_readlane(uint32_t(x >> 32), src);
-  return (uint64_t(hi) << 32) | lo;
-}
-
 // Small fill kernel (used instead of memset so the enqueued work is plain
 // kernels only).
 template <typename T>
