@@ -1040,6 +1040,7 @@ __global__ __launch_bounds__(256, 5) void knn_bf16_kernel(const uint4* __restric
                                                        const int32_t* __restrict__ perm, const float4* __restrict__ box4,
                                                        const float* __restrict__ tnrm, int64_t n, int d, int ncand,
                                                        uint64_t* __restrict__ bufs, int32_t* __restrict__ cand) {
+  static_assert(QT == 1 || QT == 2, "the selects of a query's count");
   constexpr int CAP = 64 * EPL;
   __shared__ uint4 tile[2][B_TJ * 8];  // double-buffered: 64 rows x 128 bytes each
   __shared__ int32_t ptile[2][B_TJ];    // the original indices of those rows
@@ -1057,18 +1058,18 @@ __global__ __launch_bounds__(256, 5) void knn_bf16_kernel(const uint4* __restric
   int qpw = 16 * QT;  // queries per wave
   const int qblock = int(blockIdx.x) * 4 * qpw;
   const int qbase = qblock + w * qpw;
-  int cnt[4] = {0, 0, 0, 0};  // buffer count of query (t, q16), the same in its four lanes
+  int cnt[QT] = {};  // buffer count of query (t, q16), the same in its four lanes
   // query fragments: tile t, k-step s; lane holds query qbase + 16 t + q16,
   // k elements 32 s + 8 g4 ... + 7
-  bf16x8_t bq[4][2];
-  float tau[4];
+  bf16x8_t bq[QT][2];
+  float tau[QT];
   // the subtile filter compares raw bit patterns as signed integers: for a
   // non-negative threshold, d <= tau implies bits(d) <= bits(tau) (a
   // negative d has a negative pattern), so no candidate that passes is
   // filtered out; a negative threshold (the padding queries, or a row whose
   // best distances round below 0) lets every subtile through to the exact
   // per-candidate test
-  int tau_key[4];
+  int tau_key[QT];
   auto key_of = [](float t) { return t >= 0.0f ? __float_as_int(t) : INT_MAX; };
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
@@ -1215,7 +1216,7 @@ __global__ __launch_bounds__(256, 5) void knn_bf16_kernel(const uint4* __restric
         const int rloc = sub * 16 + q16;
         bf16x8_t a0, a1;
         lds_read2_b128(lds_address(tl + tile_slot(rloc, g4)), lds_address(tl + tile_slot(rloc, 4 + g4)), a0, a1);
-        floatx4_t acc[4];
+        floatx4_t acc[QT];
 #pragma unroll
         for (int t = 0; t < QT; ++t) {
           acc[t] = floatx4_t{0.0f, 0.0f, 0.0f, 0.0f};
@@ -1282,7 +1283,7 @@ __global__ __launch_bounds__(256, 5) void knn_bf16_kernel(const uint4* __restric
       const int r = __ffsll((unsigned long long)need) - 1;
       need &= need - 1;
       const int t = r >> 4, q = r & 15;
-      const int c = __builtin_amdgcn_readlane(t == 0 ? cnt[0] : t == 1 ? cnt[1] : t == 2 ? cnt[2] : cnt[3], q);
+      const int c = __builtin_amdgcn_readlane(t == 0 ? cnt[0] : cnt[QT - 1], q);
       float nt;
       const int nc = compact_row<EPL>(bufs + int64_t(qbase + r) * CAP, c, ncand, SLACK, CAP - B_TJ, nt, hist_s[w]);
 #pragma unroll
@@ -1301,7 +1302,7 @@ __global__ __launch_bounds__(256, 5) void knn_bf16_kernel(const uint4* __restric
     const int qi = qbase + r;
     if (qi >= n32) break;
     const int t = r >> 4;
-    const int c = __builtin_amdgcn_readlane(t == 0 ? cnt[0] : t == 1 ? cnt[1] : t == 2 ? cnt[2] : cnt[3], r & 15);
+    const int c = __builtin_amdgcn_readlane(t == 0 ? cnt[0] : cnt[QT - 1], r & 15);
     emit_set<EPL>(bufs + int64_t(qi) * CAP, c, ncand, cand + int64_t(perm[qi]) * ncand, hist_s[w]);
   }
 }
