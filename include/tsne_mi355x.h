@@ -292,11 +292,16 @@ int tsne_kl_grad_fft(const float* Y, int64_t n, const int64_t* row_ptr, const in
  *   Z = Xc^T Q, Z^T Z = U diag(s^2) U^T (s descending);
  *   components = (Z U diag(1/s))^T, scores = Q U diag(s) (= Xc components^T
  *   when Q spans the range of Xc).
- * orth() is the Q factor with a positive R diagonal (CholeskyQR2 here).
+ * orth() is the Q factor with a positive R diagonal, by shifted CholeskyQR:
+ * one pass inside the iteration, whose next product needs only the span and
+ * a condition number near 1, and a second one, unshifted, for the last Q,
+ * which has to be orthonormal.
  * Sign convention: each component's entry of largest magnitude is positive
  * (the first on ties); the scores follow.  Products with X run on the FP32
  * matrix cores, the 64 x 64 steps in FP64; bitwise reproducible.  Xc must
- * have rank >= 64 (else the trailing directions are not defined).
+ * have rank >= 64 (else the trailing directions are not defined; they are
+ * finite).  A NaN or an infinity in X makes all outputs but the means of the
+ * other columns NaN.
  *
  *   X          [n][g] float, read-only; 64 <= n <= 65535 * 2048, 64 <= g <= 2^20.
  *   k          components returned, 1..64.

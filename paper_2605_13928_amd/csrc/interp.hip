@@ -494,8 +494,8 @@ __device__ __forceinline__ int fi_tid() {
   return t;
 }
 
-// Pass of radix R over the 16 elements a thread holds, v[u R + r] = element
-// num + r F / R of butterfly u (q = tid + 256 u): twiddles for sub-transforms
+// Pass of radix R over the 8 elements a thread holds, v[u R + r] = element
+// num + r F / R of butterfly u (q = tid + T u): twiddles for sub-transforms
 // of length Ns = 2^logNs, then the length-R DFTs.
 template <int T, int R>
 __device__ __forceinline__ void fi_pass(const FiLines& f, double2 (&v)[8], int logNs) {

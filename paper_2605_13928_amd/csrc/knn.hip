@@ -1005,18 +1005,18 @@ __device__ __forceinline__ void lds_read2_b128(uint32_t at0, uint32_t at1, bf16x
 // (identically) by its four lanes.
 // QT = 1 up to B_SMALL_N points, 2 above: few queries a wave make a narrow
 // box, little to wait for in the other waves of a block, five waves a SIMD
-// and short last blocks; many share a tile's load.  k = 90, QT = 1 / 2:
-// 20,000 points 0.64 / 0.85 ms, 250,000 5.7 / 6.3, 600,000 19.0 / 18.7,
-// 1,000,000 37 / 35; without clusters 200,000 18.0 / 17.8, 600,000 107 / 84.
-// (QT = 4: 1.4 to 2 times QT = 1 up to 100,000 points, 3 % more than QT = 2
-// at 1,000,000.)
+// and short last blocks; many share a tile's load.  Whole calls on the c5
+// points, k = 90, QT = 1 / 2: 20,000 0.92 / 1.24 ms, 250,000 6.0 / 6.8, 600,000
+// 20.6 / 20.0, 1,000,000 45 / 40; without clusters 200,000 18.5 / 18.1, 600,000
+// 109 / 87.  (QT = 4: 1.4 to 2 times QT = 1 up to 100,000 points, 3 % more
+// than QT = 2 at 1,000,000.)
 // The kernel is bound by the instructions of the appends (half of a wave's
 // time), the waits of its four waves for each other and the last blocks (the
 // heaviest of 3907 took 0.75 of the kernel at QT = 4).  What else cost was
 // found by clocks in a copy: the compiler's wait for the prefetch of the next
 // tile before every LDS read (lds_read_b128), the code and masks of unrolled
 // subtiles and sorts (instruction cache, spills), box tests with 64 lines per
-// load.  1,000,000 points x 50, k = 90: 66 -> 29 ms.
+// load.  This kernel alone, c5, k = 90: 55 -> 35 ms.
 // Tile skipping.  A wave does not evaluate a tile in which no distance can
 // pass the threshold of any of its queries, and the block does not
 // fetch a tile that none of its waves evaluates.  With B the box of the
@@ -1031,10 +1031,12 @@ __device__ __forceinline__ void lds_read2_b128(uint32_t at0, uint32_t at1, bf16x
 // wave's largest threshold, means every distance of the tile exceeds every
 // threshold of the wave: the tile would append nothing for it, and
 // skipping it changes no buffer.  The outputs are those of the full sweep,
-// bit for bit.  The test is taken for windows of 64 sweep positions at a
-// time (one position per lane, a ballot per wave, the four masks OR-ed
-// through LDS), with the thresholds of that moment; they only decrease, so
-// a window's stale value skips less, never wrongly.
+// bit for bit, but where squared distances underflow: the matrix cores
+// flush what is below 2^-126 to zero, the box test does not.  The test is
+// taken for windows of B_WIN0 up to 64 sweep positions at a time (one
+// position per lane, a ballot per wave, the four masks OR-ed through LDS),
+// with the thresholds of that moment; they only decrease, so a window's
+// stale value skips less, never wrongly.
 template <int EPL, int QT>
 __global__ __launch_bounds__(256, 5) void knn_bf16_kernel(const uint4* __restrict__ Xq, const uint4* __restrict__ Xc,
                                                        const int32_t* __restrict__ perm, const float4* __restrict__ box4,

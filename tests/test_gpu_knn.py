@@ -76,7 +76,7 @@ def test_knn_massive_ties(dev):
     assert all(len(set(r)) == k for r in bi.tolist())
 
 
-# 20,000 (the c2 workload) runs 32-row blocks, 30,000 (c2 shape) 64-row ones
+# 20,000 (the c2 workload) and 30,000 rows, both in blocks of 16
 @pytest.mark.parametrize("n", [20_000, 30_000])
 def test_knn_fp32_c2_sampled_rows(dev, n):
     say("knn fp32 c2 shape", n)
