@@ -16,8 +16,8 @@
 // satisfy d <= tau, so nothing is lost; ties are resolved by index at the
 // end (a wave-wide bitonic sort of the (d, j) keys).  Since the kept keys
 // are the best ones whatever order the candidates arrive in, both paths
-// sweep them in a locality order (points sorted by their nearest two of up
-// to 256 pivots, each query block sweeping outward from its own queries),
+// sweep them in a locality order (points sorted by their nearest of up to 256
+// pivots, each query block sweeping outward from its own queries),
 // so that tau is tight after a few tiles and few candidates are appended,
 // and skip the candidate tiles whose bounding box lies beyond every
 // threshold of the block (a bound that leaves the results those of the full
@@ -615,24 +615,31 @@ __device__ __forceinline__ float bf16_to_f(uint16_t h) { return __uint_as_float(
 constexpr uint16_t BF16_ONE = 0x3F80;
 constexpr uint16_t BF16_INF = 0x7F80;
 
-// Locality order (both paths).  Points are counting-sorted by a 16-bit key
-// that names the nearest and the second nearest of up to 256 pivots (points
-// taken at equal steps of the input): the cells of the pivots adapt to the
-// clusters of the data and are narrow in every coordinate, and the second
-// pivot divides them further.  Cells that are near each other get near
-// numbers (loc_rank_kernel).  Position p of the sorted order holds point
-// perm[p]; within a key the order is that of the scatter's atomics.
+// Locality order (both paths).  Points are counting-sorted by a 16-bit key:
+// the rank of the nearest of up to 256 pivots (points taken at equal steps of
+// the input), then a Morton key of two coordinates of the offset from that
+// pivot, four bits each.  The cells of the pivots adapt to the clusters of the
+// data and are narrow in every coordinate, cells that are near each other get
+// near numbers (loc_rank_kernel), and the offsets divide them by the leading
+// coordinates, the widest ones of PCA scores.  Position p of the sorted order
+// holds point perm[p]; within a key the order is that of the scatter's atomics.
 // Nothing downstream depends on any of it (the selection keeps the best keys
 // (d, original index) whatever order they arrive in), so non-finite
 // coordinates and ties may fall anywhere.
-// Against a Morton key of the points' first three coordinates, whose tiles
-// mix the clusters that overlap in those, the sweeps evaluate (with boxes of
-// 32 coordinates, 16 before) 3.6 % of the tiles in place of 42 % (200,000
-// points x 50 in 30 clusters of one size and shape) and 6.0 % in place of
-// 14 % (of many sizes, variances falling with the coordinate).
+// The pivots alone against a Morton key of the points' first three coordinates,
+// whose tiles mix the clusters that overlap in those: 3.6 % of the tiles
+// evaluated in place of 42 % (200,000 points x 50 in 30 clusters of one size
+// and shape), 6.0 % in place of 14 % (of many sizes, variances falling with the
+// coordinate).  Points without clusters need the offsets: with the second
+// nearest pivot in their place 1,000,000 normal points of deviations 1 / j took
+// 107 ms against 82 with the Morton key, now 71; PCA scores of 10^6 cells
+// without clusters 176, 166, 167; c5 at 10^6 points 39.5, 63.3, 35.0; 20,000
+// to 32,000 points in uneven clusters 2 to 4 % more than with the second pivot
+// or up to 13 % less.
 constexpr int LOC_BINS = 1 << 16;
 constexpr int LOC_PIV = 256;     // pivots, at most; 64 points per pivot at least
 constexpr int LOC_CEN = 32;
+constexpr int LOC_SUB = 2;       // coordinates of the offset from the pivot
 // Few points keep their own order: at 1,500 x 50 the sweep of all tiles took
 // 0.115 ms, the order and the sweep after it 0.17 (4,000: 0.25 and 0.29;
 // 8,000: 0.46 and 0.19 to 0.44).
@@ -670,7 +677,7 @@ __global__ __launch_bounds__(256) void loc_pivot_kernel(const float* __restrict_
 // far end of their sweep.)
 __global__ __launch_bounds__(LOC_PIV) void loc_rank_kernel(const uint16_t* __restrict__ piv,
                                                            const float* __restrict__ pnorm, int kp,
-                                                           int* __restrict__ rank) {
+                                                           int* __restrict__ rank, float* __restrict__ scale) {
   __shared__ float4 coord[LOC_PIV][9];  // 8 used: rows of an odd number of 16 bytes
   __shared__ float dist_s[LOC_CEN][LOC_CEN + 1];
   __shared__ int cen_s[LOC_CEN], chain_s[LOC_CEN], place_s[LOC_CEN];
@@ -732,6 +739,28 @@ __global__ __launch_bounds__(LOC_PIV) void loc_rank_kernel(const uint16_t* __res
       }
   }
   __syncthreads();
+  // the offsets' unit: four deviations of the pivots about their centres
+#pragma unroll
+  for (int c = 0; c < LOC_SUB; ++c) {
+    const float4 v = coord[cen_s[near]][0];
+    const float r = ok ? x[c] - (c == 0 ? v.x : v.y) : 0.0f;
+    const float q = wave_sum(r * r), m = wave_sum(ok ? 1.0f : 0.0f);
+    if (lane == 0) {
+      part_d[0][w] = q;
+      part_d[1][w] = m;
+    }
+    __syncthreads();
+    if (p == 0) {
+      float sq = 0.0f, sm = 0.0f;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        sq += part_d[0][u];
+        sm += part_d[1][u];
+      }
+      scale[c] = sq > 0.0f ? 0.25f * sqrtf(sm / sq) : 0.0f;
+    }
+    __syncthreads();
+  }
   for (int e = p; e < LOC_CEN * LOC_CEN; e += LOC_PIV) {
     const int a = e / LOC_CEN, b = e % LOC_CEN;
     float s = 0.0f;
@@ -779,32 +808,30 @@ __global__ __launch_bounds__(LOC_PIV) void loc_rank_kernel(const uint16_t* __res
   rank[p] = r;
 }
 
-// key[i] = (rank of the nearest pivot) << 8 | (rank of the second), and its
-// count in hist.  A wave takes 32 points against all pivots on the bf16
+// key[i] = (rank of the nearest pivot) << 8 | (Morton key of the offset), and
+// its count in hist.  A wave takes 32 points against all pivots on the bf16
 // matrix cores (the order needs no more precision): MFMA operands lane l,
 // pivot or point l % 16, k elements 32 s + 8 (l / 16) .. + 7; result register
 // r: pivot 4 (l / 16) + r of the tile, point l % 16.
 __global__ __launch_bounds__(256) void loc_key_kernel(const float* __restrict__ X, int64_t n, int d, int m, int kp,
                                                       const uint16_t* __restrict__ piv,
                                                       const float* __restrict__ pnorm, const int* __restrict__ rank,
-                                                      uint16_t* __restrict__ key, int* __restrict__ hist) {
+                                                      const float* __restrict__ scale, uint16_t* __restrict__ key,
+                                                      int* __restrict__ hist) {
   constexpr int PT = 2;  // tiles of 16 points
   const int lane = lane_id(), q16 = lane & 15, g4 = lane >> 4;
   const int64_t i0 = (int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6)) * (16 * PT);
   if (i0 >= n) return;
-  float b1[PT], b2[PT];
-  int i1[PT], i2[PT];
+  float best[PT];
+  int at[PT];
 #pragma unroll
   for (int t = 0; t < PT; ++t) {
-    b1[t] = b2[t] = INFINITY;
-    i1[t] = i2[t] = 0;
+    best[t] = INFINITY;
+    at[t] = 0;
   }
   auto offer = [&](int t, float dist, int u) {
-    const bool first = dist < b1[t], second = dist < b2[t];
-    b2[t] = first ? b1[t] : (second ? dist : b2[t]);
-    i2[t] = first ? i1[t] : (second ? u : i2[t]);
-    b1[t] = first ? dist : b1[t];
-    i1[t] = first ? u : i1[t];
+    at[t] = dist < best[t] ? u : at[t];
+    best[t] = fminf(dist, best[t]);
   };
   auto point = [&](int t, int k0) {  // 8 coordinates from k0 + 8 g4
     const int64_t i = i0 + 16 * t + q16;
@@ -862,16 +889,19 @@ __global__ __launch_bounds__(256) void loc_key_kernel(const float* __restrict__ 
 #pragma unroll
   for (int t = 0; t < PT; ++t) {
 #pragma unroll
-    for (int s = 16; s < 64; s <<= 1) {
-      const float o1 = xor_lane_f(b1[t], s), o2 = xor_lane_f(b2[t], s);
-      const int j1 = int(xor_lane(uint32_t(i1[t]), s)), j2 = int(xor_lane(uint32_t(i2[t]), s));
-      offer(t, o1, j1);
-      offer(t, o2, j2);
-    }
-    if (!(b2[t] < INFINITY)) i2[t] = i1[t];
+    for (int s = 16; s < 64; s <<= 1) offer(t, xor_lane_f(best[t], s), int(xor_lane(uint32_t(at[t]), s)));
     const int64_t i = i0 + 16 * t + q16;
     if (g4 == t && i < n) {
-      const uint32_t k = uint32_t(rank[i1[t]]) << 8 | uint32_t(rank[i2[t]]);
+      uint32_t q[LOC_SUB], k = uint32_t(rank[at[t]]);
+#pragma unroll
+      for (int c = 0; c < LOC_SUB; ++c) {
+        const float o = c < d ? X[i * d + c] - bf16_to_f(piv[at[t] * kp + c]) : 0.0f;
+        q[c] = uint32_t(fminf(fmaxf(fmaf(o, scale[c], 0.5f) * 16.0f, 0.0f), 15.0f));  // (NaN: 0)
+      }
+#pragma unroll
+      for (int b = 3; b >= 0; --b)
+#pragma unroll
+        for (int c = 0; c < LOC_SUB; ++c) k = k << 1 | ((q[c] >> b) & 1u);
       key[i] = uint16_t(k);
       atomicAdd(&hist[k], 1);
     }
@@ -1006,9 +1036,9 @@ __device__ __forceinline__ void lds_read2_b128(uint32_t at0, uint32_t at1, bf16x
 // QT = 1 up to B_SMALL_N points, 2 above: few queries a wave make a narrow
 // box, little to wait for in the other waves of a block, five waves a SIMD
 // and short last blocks; many share a tile's load.  Whole calls on the c5
-// points, k = 90, QT = 1 / 2: 20,000 0.92 / 1.24 ms, 250,000 6.0 / 6.8, 600,000
-// 20.6 / 20.0, 1,000,000 45 / 40; without clusters 200,000 18.5 / 18.1, 600,000
-// 109 / 87.  (QT = 4: 1.4 to 2 times QT = 1 up to 100,000 points, 3 % more
+// points, k = 90, QT = 1 / 2: 20,000 0.92 / 1.22 ms, 250,000 5.7 / 6.8, 600,000
+// 18.4 / 17.8, 1,000,000 39 / 35; without clusters 200,000 18.0 / 17.6, 600,000
+// 106 / 84.  (QT = 4: 1.4 to 2 times QT = 1 up to 100,000 points, 3 % more
 // than QT = 2 at 1,000,000.)
 // The kernel is bound by the instructions of the appends (half of a wave's
 // time), the waits of its four waves for each other and the last blocks (the
@@ -1432,7 +1462,7 @@ __global__ __launch_bounds__(256) void count_nonfinite_kernel(const float* __res
 
 struct KnnLayout {
   int epl;
-  size_t o_buf, o_xq, o_xc, o_xs, o_xp, o_cand, o_perm, o_key, o_piv, o_pnorm, o_prank, o_hist, o_cur, o_off, o_bsum, o_box, o_tnrm,
+  size_t o_buf, o_xq, o_xc, o_xs, o_xp, o_cand, o_perm, o_key, o_piv, o_pnorm, o_prank, o_scale, o_hist, o_cur, o_off, o_bsum, o_box, o_tnrm,
       bytes;
   static KnnLayout make(int64_t n, int d, int precision, int ncand) {
     KnnLayout L;
@@ -1445,6 +1475,7 @@ struct KnnLayout {
     L.o_piv = c.take(sizeof(uint16_t) * size_t(loc_kpad(d)) * LOC_PIV);
     L.o_pnorm = c.take(sizeof(float) * LOC_PIV);
     L.o_prank = c.take(sizeof(int) * LOC_PIV);
+    L.o_scale = c.take(sizeof(float) * LOC_SUB);
     L.o_hist = c.take(sizeof(int) * LOC_BINS);
     L.o_cur = c.take(sizeof(int) * LOC_BINS);
     L.o_off = c.take(sizeof(int64_t) * (LOC_BINS + 1));
@@ -1499,6 +1530,7 @@ extern "C" int tsne_knn(const float* X, int64_t n, int32_t d, int32_t k, int32_t
   uint16_t* piv = reinterpret_cast<uint16_t*>(ws + L.o_piv);
   float* pnorm = reinterpret_cast<float*>(ws + L.o_pnorm);
   int* prank = reinterpret_cast<int*>(ws + L.o_prank);
+  float* scale = reinterpret_cast<float*>(ws + L.o_scale);
   uint16_t* key = reinterpret_cast<uint16_t*>(ws + L.o_key);
   int* hist = reinterpret_cast<int*>(ws + L.o_hist);
   int* cur = reinterpret_cast<int*>(ws + L.o_cur);
@@ -1515,10 +1547,10 @@ extern "C" int tsne_knn(const float* X, int64_t n, int32_t d, int32_t k, int32_t
     const int m = loc_pivots(n), kp = loc_kpad(d);
     hipLaunchKernelGGL(loc_pivot_kernel, dim3(LOC_PIV / 4), dim3(256), 0, s, X, n, d, m, kp, piv, pnorm);
     TSNE_CHECK_LAUNCH();
-    hipLaunchKernelGGL(loc_rank_kernel, dim3(1), dim3(LOC_PIV), 0, s, piv, pnorm, kp, prank);
+    hipLaunchKernelGGL(loc_rank_kernel, dim3(1), dim3(LOC_PIV), 0, s, piv, pnorm, kp, prank, scale);
     TSNE_CHECK_LAUNCH();
     hipLaunchKernelGGL(loc_key_kernel, dim3(unsigned(ceil_div(n, 128))), dim3(256), 0, s, X, n, d, m, kp, piv, pnorm,
-                       prank, key, hist);
+                       prank, scale, key, hist);
     TSNE_CHECK_LAUNCH();
     if ((rc = exclusive_scan<int>(hist, LOC_BINS, off, bsum, s))) return rc;
     hipLaunchKernelGGL(loc_scatter_kernel, lgrid, dim3(256), 0, s, key, n, off, cur, perm);

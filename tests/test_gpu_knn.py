@@ -190,7 +190,7 @@ def test_knn_bf16_tile_skipping_nonfinite_rows(dev):
 @pytest.mark.parametrize("n,d,k", [(31, 31, 30), (33, 1, 7), (127, 32, 96), (129, 33, 97), (1023, 56, 128),
                                    (8257, 57, 90), (4100, 113, 129)])
 def test_knn_fp32_tiles_and_chunks(dev, n, d, k):
-    # rows per block (32), columns per tile (128), coordinates per step (56)
+    # rows per block (16, 32), columns per tile (128), coordinates per step (56)
     # and per box (32), keys per short sort (128), each from both sides;
     # clusters of very different sizes, sorted, so that blocks hold rows of
     # two clusters and short clusters lie far from their tiles
@@ -276,3 +276,38 @@ def test_knn_own_order(dev, n, prec):
     oi, od = oracle.knn(X, k)
     gi, gd = gpu_knn(dev, X, k, prec, n_cand=2 * k if prec == "bf16" else None)
     check_knn(X, np.arange(n), gi, gd, oi, od, **({"min_agree": 0.999} if prec == "bf16" else {}))
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+@pytest.mark.parametrize("kind", ["one coordinate", "two", "constant first", "outliers", "line", "one point twice"])
+def test_knn_locality_order_offsets(dev, prec, kind):
+    # the order within a pivot's cell comes from the first two coordinates of
+    # the offset from the pivot, in units of their spread: one or two
+    # coordinates in all, a spread of zero, a few points far outside it
+    say("knn locality order", prec, kind)
+    n, k = 4200, 20
+    rng = np.random.default_rng(17)
+    X = rng.standard_normal((n, {"one coordinate": 1, "two": 2}.get(kind, 9))).astype(np.float32)
+    if kind == "constant first":
+        X[:, 0] = 3.0
+    elif kind == "outliers":
+        X[::500, :2] *= 1e4
+    elif kind == "line":
+        X[:, 1:] = X[:, :1]
+    elif kind == "one point twice":  # (all others the same point: ties, by index)
+        X[2:] = X[0]
+    oi, od = oracle.knn(X, k)
+    gi, gd = gpu_knn(dev, X, k, prec, n_cand=2 * k if prec == "bf16" else None)
+    if kind == "one point twice":
+        if prec == "fp32":
+            np.testing.assert_array_equal(gi, oi)
+        assert (gd[2:] == 0).all()
+        return
+    if prec == "fp32":
+        check_knn(X, np.arange(n), gi, gd, oi, od)
+    else:
+        # a point's rounding moves it by at most 2^-9 |x|, so a distance to a
+        # neighbour within r by e <= 2^-9 (2 |x| + r), and the k-th candidate
+        # is within r + 2 e
+        r = np.sqrt(od[:, -1])
+        assert np.all(np.sqrt(gd[:, -1]) <= (r + 2.0**-7 * (np.linalg.norm(X, axis=1) + r)) * (1 + 1e-5))
