@@ -1046,7 +1046,7 @@ __device__ __forceinline__ void lds_read2_b128(uint32_t at0, uint32_t at1, bf16x
 // found by clocks in a copy: the compiler's wait for the prefetch of the next
 // tile before every LDS read (lds_read_b128), the code and masks of unrolled
 // subtiles and sorts (instruction cache, spills), box tests with 64 lines per
-// load.  This kernel alone, c5, k = 90: 55 -> 35 ms.
+// load.  This kernel alone, c5, k = 90: 55 -> 30 ms.
 // Tile skipping.  A wave does not evaluate a tile in which no distance can
 // pass the threshold of any of its queries, and the block does not
 // fetch a tile that none of its waves evaluates.  With B the box of the

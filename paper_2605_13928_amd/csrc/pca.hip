@@ -456,7 +456,7 @@ __device__ __forceinline__ double readlane_d(double v, int src) {
 // rows by lane reads, then one LDS write, one barrier, and the update of the
 // rows below from the four rows' broadcast.  With both matrices in LDS and
 // one row per step a launch took 87 us (48 LDS reads, a root and two divisions
-// per step); one row per step in registers 39; now 24.  Entries of A left of
+// per step); one row per step in registers 39; now 26 to 38.  Entries of A left of
 // the current columns are not kept and reach no result.
 __global__ __launch_bounds__(256, 1) void pca_cholinv_kernel(const double* __restrict__ Gin, double shift,
                                                           float* __restrict__ Rinv) {
